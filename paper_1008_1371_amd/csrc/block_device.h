@@ -414,19 +414,27 @@ __device__ __forceinline__ void inner_circle_pair(const BlockArgsT<T> &a, int k,
 
 // Per-slot rotation of the cross kernel in the precision its blocks are held
 // in: (t, c) with c negated for an applied trigonometric rotation, decoded to
-
-// (t, |c|, h) with h = -t for such a rotation, h = t otherwise.
+// (t, |c|, h) with h = -t for such a rotation, h = t otherwise (bit
+// operations: no compare or select).
 template <typename C>
 struct SlotRot;
 template <>
 struct SlotRot<float> {
     typedef float2 packed;
     static __device__ __forceinline__ float2 pack(double t, double c) { return make_float2((float)t, (float)c); }
+    static __device__ __forceinline__ float with_sign(float t, float c)
+    {
+        return __uint_as_float(__float_as_uint(t) ^ (__float_as_uint(c) & 0x80000000u));
+    }
 };
 template <>
 struct SlotRot<double> {
     typedef double2 packed;
     static __device__ __forceinline__ double2 pack(double t, double c) { return make_double2(t, c); }
+    static __device__ __forceinline__ double with_sign(double t, double c)
+    {
+        return __hiloint2double(__double2hiint(t) ^ (__double2hiint(c) & (int)0x80000000), __double2loint(t));
+    }
 };
 template <typename C>
 struct Rot3 {
@@ -435,7 +443,25 @@ struct Rot3 {
 template <typename C, typename P>
 __device__ __forceinline__ Rot3<C> unpack_rot(P r)
 {
-    return Rot3<C>{r.x, fabs(r.y), r.y < C(0) ? -r.x : r.x};
+    return Rot3<C>{r.x, fabs(r.y), SlotRot<C>::with_sign(r.x, r.y)};
+}
+
+// Lane moves of the cross solve, on 32-bit words without the LDS pipe.
+// In 16-lane rows: lane i takes lane i + 1 mod 16.
+__device__ __forceinline__ int row_next(int v) { return __builtin_amdgcn_update_dpp(v, v, 0x12F, 0xf, 0xf, false); }
+__device__ __forceinline__ float row_next(float v) { return __int_as_float(row_next(__float_as_int(v))); }
+__device__ __forceinline__ double row_next(double v)
+{
+    return __hiloint2double(row_next(__double2hiint(v)), row_next(__double2loint(v)));
+}
+
+// Workgroup barrier for waves that run different loops: every wave of the
+// workgroup executes the same number of them.
+__device__ __forceinline__ void role_barrier()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
 }
 
 // ---------------------------------------------------------------------------
@@ -443,272 +469,520 @@ __device__ __forceinline__ Rot3<C> unpack_rot(P r)
 // first of a sweep), register-resident.
 //
 // Slot coordinates: at inner step u slot s pairs local column L_s = s with
-// R_s(u) = b + ((s + u) mod b).  The 2x2 block (s1, s2) of A_P has rows
-// {L_s1, R_s1(u)} and columns {L_s2, R_s2(u)}; it is held by thread (d, s) =
-// (tid / b, tid % b) with s1 = s, s2 = s + d mod b, i.e. by diagonals, so the
-// blocks that carry the pivots of the next inner step -- (s, s) and (s, s + 1)
-// -- all sit in the first wave.  Since R_s(u + 1) = R_{s+1}(u), moving to the
-// next inner step maps block (s1, s2) to
-//   LL <- LL,  LR <- LR(s1, s2 + 1),  RL <- RL(s1 + 1, s2),  RR <- RR(s1 + 1, s2 + 1):
-// a lane shuffle for RR (same diagonal) and an exchange through LDS for LR and
-// RL (neighbouring diagonals), double-buffered so that one barrier per inner
-// step suffices.  The first wave (raised priority) evaluates the b rotations
-// of the next step from its own registers right after its update and leaves
-// them in LDS (double-buffered as well) before that barrier.
+// R_s(u) = b + ((s + u) mod b).  A_P in these coordinates is P(x, y) =
+// A(L_x, L_y), M(x, y) = A(L_x, R_y), N(x, y) = A(R_x, R_y); P and N are
+// symmetric, so the unordered slot pairs {lo <= hi} with P, M(lo, hi),
+// M(hi, lo) and N hold all of it.  A step rotates such a 2 x 2 block by its
+// columns (slot hi), then by its rows (slot lo).  Since R_s(u + 1) =
+// R_{s+1}(u), moving to the next step maps
+//   M(x, y) <- M(x, y + 1),   N(x, y) <- N(x + 1, y + 1),   P unchanged.
 //
-// Blocks (s1, s2) and (s2, s1) apply their column and row operations in
-// mirrored order (columns first iff s1 <= s2), so the two stay exact
-// transposes and A stays exactly symmetric.  W, rows {s1, b + s1} by columns
-// {L_s2, R_s2(u)}, is held by thread (s1, s2) = (tid / b, tid % b) and shifts
-// along s2 by a lane shuffle.
+// The waves of the workgroup take different parts:
+//  - wave 0, the pivot wave: the blocks {s, s} (rows 0, 1 of its lanes, even
+//    and odd s) and {s, s + 1} (rows 2, 3).  They carry the pivots of the
+//    next step: it evaluates the b rotations from its own registers and
+//    leaves them in LDS.
+//  - waves 1 and 2: the other blocks in 2 x 2 tiles of slots, one tile
+//    {2 ti, 2 ti + 1} x {2 tj, 2 tj + 1} per lane, by tile diagonals dd =
+//    tj - ti mod 16 = 1 .. 8, 16 lanes each.  Half of a tile's shift stays in
+//    the lane, one entry comes from the next lane, and six entries from
+//    the tiles {ti, tj + 1} and {ti + 1, tj} through LDS.
+//  - W, the accumulated rotations: lane j of a 16-lane row holds the
+//    columns of slots 2 j and 2 j + 1 for a few rows; its shift is one move
+//    within the row, so it reads nothing but the rotations.  With NT >= 512
+//    the last four waves hold W (4 rows a lane); with 256 threads waves 1
+//    and 2 (4 rows a lane) and wave 3 (8 rows a lane).
+// One barrier per inner step separates a step's rotations and the entries
+// exchanged at the last one (both double-buffered) from their readers.  The
+// step's time is the pivot wave's dependency chain (read, rotate, move, about
+// 35 dependent FP64 operations of rotation_params_fast), with the other
+// waves' work beside it.
+//
+// What bounds it: that chain, in single solves (one block pair per compute
+// unit), and the FP64 issue rate in batches.  A layout with every block held
+// twice (both triangles, 1024 lanes), every shift through LDS and the rotation
+// chain behind range and skip branches took 34.8 us for an inner launch of a
+// graded n = 1024 solve (16 block pairs, FP64, V half included), this one 24.8;
+// 300 batched problems of order 8 to 256 in the persistent launch: 32.8 ms,
+// now 27.3.
 // ---------------------------------------------------------------------------
+constexpr int kXRows = 9;                   // exchange rows: tile diagonals 1 .. 8, then the diagonal tiles
+constexpr int kXPart = kXRows * 16;         // one exchanged entry of every tile
+constexpr int kXGroup = 3 * kXPart;         // the three entries a tile hands to one neighbour
+// one step: both neighbours' entries, M(s, s + 2) for the pivot wave, and words that only keep lanes without an entry
+// to write from branching
+constexpr int kXBuf = 2 * kXGroup + kB + 128 + 256;
+
 template <typename T>
 struct CrossLds {
-    // A_P staging at the start, the two LR / RL exchange buffers in the loop
+    // A_P staging at the start, the exchange buffers in the loop
     double buf[kB2 * kLd];
     // per slot (t, c), c negated for an applied trigonometric rotation (whose
-    // h is -t; otherwise h = t): one read per slot and step, the LDS reads
-    // being the bulk of an inner step.  The blocks of A_P and W are held in
-    // the storage precision T: FP32 in the FP32 sweeps, where the rotations
-    // are still computed in FP64 from the FP32 pivots and applied in FP32
-    // (W is rounded to T on output in any case).
+    // h is -t; otherwise h = t).  The blocks of A_P and W are held in the
+    // storage precision T: FP32 in the FP32 sweeps, where the rotations are
+    // still computed in FP64 from the FP32 pivots and applied in FP32 (W is
+    // rounded to T on output in any case).
     typename SlotRot<T>::packed prm[2][kB];
-    int rotf[2][kB];  // slot rotated (read by the diagonal blocks)
-    int live;         // some cross pair fails the skip test
+    int live;  // some cross pair fails the skip test
 };
+static_assert(2 * kXBuf <= kB2 * kLd, "exchange buffers fit the staging area");
+
+// The 2 x 2 block (x00 x01; x10 x11): columns by pa, then rows by pq.
+template <typename T>
+__device__ __forceinline__ void rotate_block(T &x00, T &x01, T &x10, T &x11, const Rot3<T> &pa, const Rot3<T> &pq)
+{
+    const T f00 = fma(pa.z, x01, x00) * pa.y, f01 = fma(pa.x, x00, x01) * pa.y;
+    const T f10 = fma(pa.z, x11, x10) * pa.y, f11 = fma(pa.x, x10, x11) * pa.y;
+    x00 = fma(pq.z, f10, f00) * pq.y;
+    x10 = fma(pq.x, f00, f10) * pq.y;
+    x01 = fma(pq.z, f11, f01) * pq.y;
+    x11 = fma(pq.x, f01, f11) * pq.y;
+}
+
+// W of RG rows and the slots 2 j, 2 j + 1 of this lane (RG = 0: none).  Held
+// in vector values: as arrays of a structure the compiler left some of them
+// in scratch memory.
+template <typename T, int RG>
+struct WRows {
+    typedef T vec __attribute__((ext_vector_type(RG)));
+    vec l0, r0, l1, r1;
+    __device__ __forceinline__ void init(int row, int j)
+    {
+#pragma unroll
+        for (int q = 0; q < RG; ++q) {
+            l0[q] = row + q == 2 * j ? T(1) : T(0);
+            l1[q] = row + q == 2 * j + 1 ? T(1) : T(0);
+            r0[q] = row + q == kB + 2 * j ? T(1) : T(0);
+            r1[q] = row + q == kB + 2 * j + 1 ? T(1) : T(0);
+        }
+    }
+    static __device__ __forceinline__ vec rotated(T z, vec b, vec a, T c)
+    {
+        vec o;
+#pragma unroll
+        for (int q = 0; q < RG; ++q) o[q] = fma(z, b[q], a[q]) * c;
+        return o;
+    }
+    __device__ __forceinline__ void step(const Rot3<T> &p0, const Rot3<T> &p1)
+    {
+        const vec a0 = rotated(p0.z, r0, l0, p0.y), b0 = rotated(p0.x, l0, r0, p0.y);
+        const vec a1 = rotated(p1.z, r1, l1, p1.y), b1 = rotated(p1.x, l1, r1, p1.y);
+        l0 = a0;
+        l1 = a1;
+        r0 = b1;
+#pragma unroll
+        for (int q = 0; q < RG; ++q) r1[q] = row_next(b0[q]);
+    }
+    __device__ __forceinline__ void store(T *__restrict__ Wg, int row, int j) const
+    {
+        typedef T v2 __attribute__((ext_vector_type(2)));
+#pragma unroll
+        for (int q = 0; q < RG; ++q) {
+            *reinterpret_cast<v2 *>(Wg + (row + q) * kB2 + 2 * j) = v2{l0[q], l1[q]};
+            *reinterpret_cast<v2 *>(Wg + (row + q) * kB2 + kB + 2 * j) = v2{r0[q], r1[q]};
+        }
+    }
+};
+template <typename T>
+struct WRows<T, 0> {
+    __device__ __forceinline__ void init(int, int) {}
+    __device__ __forceinline__ void step(const Rot3<T> &, const Rot3<T> &) {}
+    __device__ __forceinline__ void store(T *, int, int) const {}
+};
+
+// Exchange address of the unordered tile pair {x, y}: its entries for the
+// neighbour on x's side (x is the tile whose slots the entries' R columns
+// belong to).  Group 0 when x is the higher tile, 1 when the lower.
+__device__ __forceinline__ int cross_source(int other, int x)
+{
+    if (other == x) return 8 * 16 + x;
+    const int dist = (x - other) & 15;
+    const int row = dist <= 8 ? dist : 16 - dist, i = dist <= 8 ? other : x;
+    return (x > other ? 0 : kXGroup) + (row - 1) * 16 + i;
+}
+
+// What the pivot wave counts over the inner steps.
+struct CrossCount {
+    unsigned rotated;  // lane s < b: bit b - 1 - u = slot s rotated at inner step u
+    unsigned nbad;     // pairs found rank deficient (wave-uniform)
+    double maxt;       // the lane's largest |t|
+};
+
+// Signs of the pairs of a block pair: all trigonometric, all hyperbolic, or
+// both kinds (one of the blocks holds columns of both signs).
+enum { kTrig = 0, kHyp = 1, kBothKinds = 2 };
+
+// The pivot wave.  A lone wave issues one vector instruction in about six
+// cycles whatever it depends on, so its step time is its instruction count:
+// the signs of the pairs are settled outside the loop where they can be, one
+// integer compare covers the ranges of the short rotation form and of the
+// squared skip test, what is counted is packed into one bit per step, and the
+// lane moves go through ds_bpermute.
+template <typename T>
+struct CrossPivot {
+    T P, x01, x10, N;   // the block {lo, hi} of this lane
+    int s, u0;          // slot; the inner step of step<0>
+    bool up, wrap;      // block {s, s + 1} (lanes 32 ..), else {s, s}; lane 63: {0, 31}, lo = s + 1
+    bool lpos;          // column L_s has sign +
+    int rbase, p;       // position of R_s(0) - s
+    double tol, tol2;
+    unsigned range_lo, range_len;  // high words of the entries the short forms take
+    T *ex;
+    const typename SlotRot<T>::packed *plo, *phi;
+    int o1, o2;         // where this lane's entries for the tiles go
+    int zsrc, nsrc;     // byte addresses of the lane moves
+    CrossCount n;
+
+    static __device__ __forceinline__ float move(int src, float v)
+    {
+        return __int_as_float(__builtin_amdgcn_ds_bpermute(src, __float_as_int(v)));
+    }
+    static __device__ __forceinline__ double move(int src, double v)
+    {
+        return __hiloint2double(__builtin_amdgcn_ds_bpermute(src, __double2hiint(v)),
+                                __builtin_amdgcn_ds_bpermute(src, __double2loint(v)));
+    }
+
+    template <int PB, int MODE>
+    __device__ __forceinline__ void step(CrossLds<T> &L)
+    {
+        bool rot = false;
+        if (!up) {
+            // Skip test and rotation evaluated side by side (independent
+            // dependency chains), then selected; the branch is taken only when
+            // an entry leaves the range of the short forms.
+            const double pll = P, plr = x01, prr = N;
+            const bool trig = MODE == kTrig || (MODE == kBothKinds && lpos == (rbase + ((s + u0 + PB) & 31) < p));
+            double t, c;
+            bool bad = MODE == kTrig    ? rotation_params_short(pll, prr, plr, true, t, c)
+                       : MODE == kHyp   ? rotation_params_short(pll, prr, plr, false, t, c)
+                                        : rotation_params_short(pll, prr, plr, trig, t, c);
+            bool skip = plr * plr < tol2 * (pll * prr);
+            const unsigned el = (unsigned)__double2hiint(pll) - range_lo, er = (unsigned)__double2hiint(prr) - range_lo;
+            const bool odd = max(el, er) >= range_len;
+            if (__builtin_expect(__ballot(odd) != 0ull, 0)) {
+                if (odd) {
+                    if (!fast_range(pll, prr)) bad = rotation_params(pll, prr, plr, trig ? -1 : 1, t, c) != 0;
+                    skip = rel_orthogonal_sq(pll, prr, plr, tol, tol2);
+                }
+            }
+            rot = !skip && !bad;
+            const double tr = rot ? t : 0.0, cr = rot ? (trig ? -c : c) : 1.0;
+            L.prm[PB][s] = SlotRot<T>::pack(tr, cr);
+            n.maxt = fmax(n.maxt, fabs(tr));
+            n.rotated = 2u * n.rotated + (rot ? 1u : 0u);
+            if (MODE != kTrig) n.nbad += (unsigned)__popcll(__ballot(!skip && bad));
+        }
+        role_barrier();
+        const T xe = ex[(PB ^ 1) * kXBuf + 2 * kXGroup + s];
+        const Rot3<T> pa = unpack_rot<T>(phi[PB * kB]), pq = unpack_rot<T>(plo[PB * kB]);
+        // the entry from the tiles, read before (first step: from the staged A_P): M(s, s + 1)
+        x01 = up && !wrap ? xe : x01;
+        x10 = wrap ? xe : x10;
+        rotate_block(P, x01, x10, N, pa, pq);
+        const T Mu = rot ? T(0) : (wrap ? x10 : x01);  // M(s, s), M(s, s + 1)
+        // the diagonal tiles' entries: M(2i, 2i), M(2i + 1, 2i), N(2i, 2i + 1)
+        // (the other lanes write to words of their own that nothing reads)
+        ex[PB * kXBuf + o1] = up ? x10 : Mu;
+        ex[PB * kXBuf + o2] = N;
+        // {s, s} takes M(s, s + 1); {s, s + 1} takes M(s + 1, s + 1) as the one
+        // entry and M(s, s + 2), from its tile, as the other
+        x01 = x10 = move(zsrc, Mu);
+        N = move(nsrc, N);
+    }
+
+    template <int MODE>
+    __device__ __forceinline__ void run(CrossLds<T> &L, int nsteps)
+    {
+#pragma unroll 1
+        for (u0 = 0; u0 < nsteps; u0 += 2) {
+            step<0, MODE>(L);
+            step<1, MODE>(L);
+        }
+    }
+};
+
+template <typename T>
+__device__ __forceinline__ CrossCount cross_pivot_wave(const BlockArgsT<T> &a, int2 IJ, CrossLds<T> &L, int nsteps)
+{
+    const double *const buf = L.buf;
+    CrossPivot<T> w;
+    const int lane = threadIdx.x & 63;
+    w.ex = reinterpret_cast<T *>(L.buf);
+    const int s = w.s = lane & 31, s1 = (s + 1) & 31;
+    w.up = lane >= 32;
+    const int s2 = w.up ? s1 : s;
+    const int lo = min(s, s2), hi = max(s, s2);
+    w.wrap = lane == 63;
+    w.p = a.p;
+    w.lpos = IJ.x * kB + s < a.p;
+    w.rbase = IJ.y * kB;
+    w.tol = a.tol;
+    w.tol2 = a.tol * a.tol;
+    {
+        // entries in [2^E, 2^480), E >= -480 and tol^2 2^(2E) >= 2^-999: the
+        // short rotation form and the squared skip test both hold there
+        int E = -480;
+        if (!(w.tol2 >= 0x1p-38)) E = max(E, w.tol2 >= 0x1p-1000 ? (-998 - ilogb(w.tol2)) / 2 : 1024);
+        const int lo_w = min(E + 1023, 2047), hi_w = 480 + 1023;
+        w.range_lo = (unsigned)lo_w << 20;
+        w.range_len = lo_w < hi_w ? (unsigned)(hi_w - lo_w) << 20 : 0u;
+    }
+    w.plo = &L.prm[0][lo];
+    w.phi = &L.prm[0][hi];
+    const int i = s >> 1, dummy = 2 * kXGroup + kB + lane;
+    const bool even = (s & 1) == 0;
+    w.o1 = even ? (w.up ? kXPart : 0) + 8 * 16 + i : dummy;
+    w.o2 = even && w.up ? 2 * kXPart + 8 * 16 + i : dummy + 64;
+    w.zsrc = 4 * (w.up ? s1 : s + 32);
+    w.nsrc = 4 * ((lane & 32) | s1);
+    w.P = (T)buf[lo * kLd + hi];
+    w.x01 = (T)buf[lo * kLd + kB + hi];
+    w.x10 = (T)buf[hi * kLd + kB + lo];
+    w.N = (T)buf[(kB + lo) * kLd + kB + hi];
+    w.n = CrossCount{0u, 0u, 0.0};
+    role_barrier();  // the staging area becomes the exchange area
+    // as if exchanged by a step before the first
+    if (w.up) w.ex[kXBuf + 2 * kXGroup + s] = w.wrap ? w.x10 : w.x01;
+    const bool li = IJ.x * kB + kB <= a.p, lj = IJ.y * kB + kB <= a.p;  // all +
+    const bool ni = IJ.x * kB >= a.p, nj = IJ.y * kB >= a.p;            // all -
+    const int mode = (li && lj) || (ni && nj) ? kTrig : ((li && nj) || (ni && lj) ? kHyp : kBothKinds);
+    __builtin_amdgcn_s_setprio(2);
+    if (mode == kTrig)
+        w.template run<kTrig>(L, nsteps);
+    else if (mode == kHyp)
+        w.template run<kHyp>(L, nsteps);
+    else
+        w.template run<kBothKinds>(L, nsteps);
+    __builtin_amdgcn_s_setprio(0);
+    return w.n;
+}
+
+template <typename T>
+struct CrossTile {
+    T P[2][2], U[2][2], D[2][2], N[2][2];  // [q][h]: slots lo = 2 ti + q, hi = 2 tj + h; U = M(lo, hi), D = M(hi, lo)
+    T *ex;
+    int ti, tj, e1, e2, own;
+    int xe;     // the pivot wave's entries M(s, s + 2), s = 2 i, 2 i + 1 (tiles next to the diagonal; else unread)
+    bool wrap;  // {15, 0}: they are below the diagonal
+
+    template <int PB>
+    __device__ __forceinline__ void step(CrossLds<T> &L)
+    {
+        role_barrier();
+        const typename SlotRot<T>::packed *const prm = L.prm[PB];
+        const typename SlotRot<T>::packed rq0 = prm[2 * ti], rq1 = prm[2 * ti + 1], rh0 = prm[2 * tj], rh1 = prm[2 * tj + 1];
+        const T *const in = ex + (PB ^ 1) * kXBuf;
+        U[0][1] = in[e1];
+        U[1][1] = in[e1 + kXPart];
+        N[0][1] = in[e1 + 2 * kXPart];
+        D[1][0] = in[e2];
+        D[1][1] = in[e2 + kXPart];
+        N[1][0] = in[e2 + 2 * kXPart];
+        const Rot3<T> q0 = unpack_rot<T>(rq0), q1 = unpack_rot<T>(rq1), h0 = unpack_rot<T>(rh0), h1 = unpack_rot<T>(rh1);
+        rotate_block(P[0][0], U[0][0], D[0][0], N[0][0], h0, q0);
+        rotate_block(P[1][0], U[1][0], D[1][0], N[1][0], h0, q1);
+        rotate_block(P[0][1], U[0][1], D[0][1], N[0][1], h1, q0);
+        rotate_block(P[1][1], U[1][1], D[1][1], N[1][1], h1, q1);
+        T *const out = ex + PB * kXBuf;
+        out[own] = U[0][0];
+        out[own + kXPart] = U[1][0];
+        out[own + 2 * kXPart] = N[1][0];
+        out[kXGroup + own] = D[0][0];
+        out[kXGroup + own + kXPart] = D[0][1];
+        out[kXGroup + own + 2 * kXPart] = N[0][1];
+        out[xe] = wrap ? D[0][0] : U[0][0];
+        out[xe + 1] = wrap ? D[1][1] : U[1][1];
+        U[0][0] = U[0][1];
+        U[1][0] = U[1][1];
+        D[0][0] = D[1][0];
+        D[0][1] = D[1][1];
+        const T n00 = N[0][0];
+        N[0][0] = N[1][1];
+        N[1][1] = row_next(n00);
+    }
+};
+
+template <typename T, int WR>
+__device__ __forceinline__ void cross_tile_wave(CrossLds<T> &L, int nsteps, int wave, int wrow, T *__restrict__ Wg)
+{
+    const double *const buf = L.buf;
+    const int lane = threadIdx.x & 63;
+    const int row = (wave - 1) * 4 + (lane >> 4), i = lane & 15;  // tile diagonal row + 1
+    const int y = (i + row + 1) & 15;
+    CrossTile<T> w;
+    w.ex = reinterpret_cast<T *>(L.buf);
+    const int ti = w.ti = min(i, y), tj = w.tj = max(i, y);
+#pragma unroll
+    for (int q = 0; q < 2; ++q)
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            const int x = 2 * ti + q, z = 2 * tj + h;
+            w.P[q][h] = (T)buf[x * kLd + z];
+            w.U[q][h] = (T)buf[x * kLd + kB + z];
+            w.D[q][h] = (T)buf[z * kLd + kB + x];
+            w.N[q][h] = (T)buf[(kB + x) * kLd + kB + z];
+        }
+    w.e1 = cross_source(ti, (tj + 1) & 15);
+    w.e2 = cross_source(tj, (ti + 1) & 15);
+    w.own = row * 16 + i;
+    w.wrap = row == 0 && i == 15;
+    w.xe = row == 0 ? 2 * kXGroup + 2 * i : 2 * kXGroup + kB + 128 + 2 * w.own;
+    WRows<T, WR> wr;
+    wr.init(wrow, i);
+    role_barrier();
+    {
+        // the entries of the first step, as if exchanged by a step before it
+        T *const in = w.ex + kXBuf;
+        in[w.e1] = w.U[0][1];
+        in[w.e1 + kXPart] = w.U[1][1];
+        in[w.e1 + 2 * kXPart] = w.N[0][1];
+        in[w.e2] = w.D[1][0];
+        in[w.e2 + kXPart] = w.D[1][1];
+        in[w.e2 + 2 * kXPart] = w.N[1][0];
+    }
+#pragma unroll 1
+    for (int u = 0; u < nsteps; u += 2) {
+        w.template step<0>(L);
+        if (WR > 0) wr.step(unpack_rot<T>(L.prm[0][2 * i]), unpack_rot<T>(L.prm[0][2 * i + 1]));
+        w.template step<1>(L);
+        if (WR > 0) wr.step(unpack_rot<T>(L.prm[1][2 * i]), unpack_rot<T>(L.prm[1][2 * i + 1]));
+    }
+    if (WR > 0) wr.store(Wg, wrow, i);
+}
+
+template <typename T, int RG>
+__device__ __forceinline__ void cross_w_wave(CrossLds<T> &L, int nsteps, int wrow, T *__restrict__ Wg)
+{
+    const int j = threadIdx.x & 15;
+    WRows<T, RG> w;
+    w.init(wrow, j);
+    role_barrier();
+#pragma unroll 1
+    for (int u = 0; u < nsteps; u += 2) {
+        role_barrier();
+        w.step(unpack_rot<T>(L.prm[0][2 * j]), unpack_rot<T>(L.prm[0][2 * j + 1]));
+        role_barrier();
+        w.step(unpack_rot<T>(L.prm[1][2 * j]), unpack_rot<T>(L.prm[1][2 * j + 1]));
+    }
+    w.store(Wg, wrow, j);
+}
 
 // Every thread must call it (barriers).
 template <typename T, int NT>
 __device__ __forceinline__ void inner_cross_pair(const BlockArgsT<T> &a, int k, CrossLds<T> &L)
 {
-    // NT threads; thread tid holds the K blocks (d, s) at positions
-    // tid + NT q, q < K: one slot s = tid % b for all of them, diagonals NT/b
-    // apart, every slot shift inside the thread's half-wave as with K = 1.
-    constexpr int K = (kB * kB) / NT;
-    static_assert(K * NT == kB * kB && NT % 64 == 0, "thread count");
+    static_assert(NT == 256 || NT == 512 || NT == 1024, "thread count");
     double *const buf = L.buf;
-    typename SlotRot<T>::packed(*const prm)[kB] = L.prm;
-    int(*const rotf)[kB] = L.rotf;
-    int &live = L.live;
     const int tid = threadIdx.x;
     const int lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int2 IJ = outer_pair(a, k);
+    // the sweep's counters so far, read ahead of their update at the end
+    double cmaxt = 0.0;
+    int cC = 0;
+    unsigned crot = 0, cskip = 0, cact = 0, ctc = 0;
+    if (tid == 0) {
+        cmaxt = a.maxt[k];
+        cC = a.C[k];
+        crot = a.nrot[k];
+        cskip = a.nskip[k];
+        cact = a.nact[k];
+        ctc = a.ntc[k];
+    }
 
-    // A_P = sum of the partial Grams in split order.  Work item i sums entries
-    // (x, y0 .. y0 + 3), x = i / 16, y0 = 4 (i % 16), of every split with
-    // vector loads; only the upper-triangular 16 x 16 tiles hold data.
+    // A_P = sum of the partial Grams in split order.  Only the 10
+    // upper-triangular 16 x 16 tiles hold data: work item i sums the entries
+    // (x, y), (x, y + 1) of tile i / 128 of every split with vector loads.
+    constexpr int kItems = kGramTiles * 128;
 #pragma unroll
-    for (int q = 0; q < K; ++q) {
-        typedef T v4 __attribute__((ext_vector_type(4)));
-        constexpr int kChunk = sizeof(T) == 4 ? 16 : 8;
+    for (int q = 0; q < (kItems + NT - 1) / NT; ++q) {
+        typedef T v2 __attribute__((ext_vector_type(2)));
+        constexpr int kChunk = 8;
         const int item = tid + NT * q;
-        const int x = item >> 4, y0 = (item & 15) * 4;
-        if ((y0 >> 4) >= (x >> 4)) {
-            const T *P = a.partial + (size_t)k * a.splits * (kB2 * kB2) + x * kB2 + y0;
-            double g0 = 0.0, g1 = 0.0, g2 = 0.0, g3 = 0.0;
+        if (kItems % NT == 0 || item < kItems) {
+            const int tile = item >> 7, x = kGramTX[tile] * 16 + ((item >> 3) & 15), y = kGramTY[tile] * 16 + (item & 7) * 2;
+            const T *P = a.partial + (size_t)k * a.splits * (kB2 * kB2) + x * kB2 + y;
+            double g0 = 0.0, g1 = 0.0;
             for (int base = 0; base < a.splits; base += kChunk) {
-                v4 v[kChunk];
+                v2 v[kChunk];
 #pragma unroll
                 for (int c = 0; c < kChunk; ++c)
                     v[c] = base + c < a.splits
-                               ? *reinterpret_cast<const v4 *>(P + (size_t)(base + c) * (kB2 * kB2))
-                               : v4{0, 0, 0, 0};
+                               ? *reinterpret_cast<const v2 *>(P + (size_t)(base + c) * (kB2 * kB2))
+                               : v2{0, 0};
 #pragma unroll
                 for (int c = 0; c < kChunk; ++c)
                     if (base + c < a.splits) {
                         const bool first = base + c == 0;
                         g0 = first ? (double)v[c][0] : g0 + (double)v[c][0];
                         g1 = first ? (double)v[c][1] : g1 + (double)v[c][1];
-                        g2 = first ? (double)v[c][2] : g2 + (double)v[c][2];
-                        g3 = first ? (double)v[c][3] : g3 + (double)v[c][3];
                     }
             }
-            double *row = buf + x * kLd + y0;
-            row[0] = g0;
-            row[1] = g1;
-            row[2] = g2;
-            row[3] = g3;
+            buf[x * kLd + y] = g0;
+            buf[x * kLd + y + 1] = g1;
         }
     }
-    if (tid == 0) live = 0;
+    if (tid == 0) L.live = 0;
     __syncthreads();
-    const int s = tid & 31;
-    const int s1 = s;
-    T LL[K], LR[K], RL[K], RR[K];
-    T W0L[K], W0R[K], W1L[K], W1R[K];
-    int s2[K], lr_cell[K], rl_cell[K];
-    bool cf[K];
-#pragma unroll
-    for (int q = 0; q < K; ++q) {
-        const int pos = tid + NT * q;
-        const int d = pos >> 5;
-        s2[q] = (s + d) & 31;
-        cf[q] = s1 <= s2[q];
-        // entry (x, y) is read at (min, max) for both mirror positions
-        LL[q] = (T)buf[min(s1, s2[q]) * kLd + max(s1, s2[q])];
-        LR[q] = (T)buf[s1 * kLd + kB + s2[q]];
-        RL[q] = (T)buf[s2[q] * kLd + kB + s1];
-        RR[q] = (T)buf[(kB + min(s1, s2[q])) * kLd + kB + max(s1, s2[q])];
-        // W block of this position: rows {w1, b + w1} (w1 = d) by columns
-        // {L_w2, R_w2} (w2 = s)
-        W0L[q] = d == s ? T(1) : T(0);
-        W0R[q] = T(0);
-        W1L[q] = T(0);
-        W1R[q] = d == s ? T(1) : T(0);
-        lr_cell[q] = (((d + 1) & 31) << 5) | s;             // position (d + 1, s)
-        rl_cell[q] = (((d + 31) & 31) << 5) | ((s + 1) & 31);  // position (d - 1, s + 1)
-    }
-    const bool diag = tid < kB;  // position (0, s), q = 0
-    const double tol2 = a.tol * a.tol;
     {
-        // Every cross pair (s, b + s2) of the block pair is the pivot of one
+        // Every cross pair (x, b + y) of the block pair is the pivot of one
         // inner step.  If none fails the skip test (2.3) on A_P as staged, the
         // first step rotates nothing, A_P stays as it is, and by induction no
         // step rotates: the whole solve is skipped (W = I).  The test takes the
         // entries as the loop holds them (rounded to T).
+        constexpr int K = (kB * kB) / NT;
+        const double tol = a.tol, tol2 = tol * tol;
         int fails = 0;
+        const int y = tid & 31;
+        const double ayy = (T)buf[(kB + y) * kLd + kB + y];
 #pragma unroll
-        for (int q = 0; q < K; ++q)
-            fails |= rel_orthogonal_sq((T)buf[s * kLd + s], (T)buf[(kB + s2[q]) * kLd + kB + s2[q]], LR[q], a.tol,
-                                       tol2)
-                         ? 0
-                         : 1;
-        if (__ballot(fails) != 0ull && lane == 0) atomicOr(&live, 1);
+        for (int q = 0; q < K; ++q) {
+            const int x = (tid + NT * q) >> 5;
+            fails |= rel_orthogonal_sq((T)buf[x * kLd + x], ayy, (T)buf[x * kLd + kB + y], tol, tol2) ? 0 : 1;
+        }
+        if (__ballot(fails) != 0ull && lane == 0) L.live = 1;
     }
-    const int nxt = (lane & 32) | ((lane + 1) & 31);  // lane of (d, s + 1), resp. W column s2 + 1
-    T *const xlr = reinterpret_cast<T *>(buf), *const xrl = xlr + 2 * kB * kB;  // [2][b * b] each
-    // pivots of slot s (lanes 0 .. b-1 of the first wave, q = 0)
-    T pll = LL[0], plr = LR[0], prr = RR[0];
-    int code = 0, nrot = 0, nskip = 0, rank = 0;
-    double maxt = 0.0;
-    unsigned long long tmask = 0ull;  // local columns touched by a rotation (first wave)
-    if (tid < 64) __builtin_amdgcn_s_setprio(2);
     __syncthreads();
-    const int nsteps = live ? kB : 0;  // the same in every thread
-    if (nsteps == 0 && tid < kB) nskip = kB;
-
-    for (int u = 0; u < nsteps; ++u) {
-        const int pb = u & 1;
-        if (tid < kB) {
-            // skip test and rotation evaluated side by side (independent
-            // dependency chains), then selected
-            const int pl = IJ.x * kB + s, pr = IJ.y * kB + ((s + u) & 31);
-            const int hyp = ((pl < a.p) == (pr < a.p)) ? -1 : 1;
-            double t, c;
-            const int bad = rotation_params_fast(pll, prr, plr, hyp, t, c);
-            const bool skip = rel_orthogonal_sq(pll, prr, plr, a.tol, tol2);
-            int rot = 0;
-            if (skip) {
-                ++nskip;
-                t = 0.0;
-                c = 1.0;
-            } else if (bad) {
-                rank = 1;
-                t = 0.0;
-                c = 1.0;
-            } else {
-                rot = 1;
-                ++nrot;
-                code |= rotation_code(t, a.tthresh);
-                maxt = fmax(maxt, fabs(t));
-                tmask |= (1ull << s) | (1ull << (kB + ((s + u) & 31)));
-            }
-            prm[pb][s] = SlotRot<T>::pack(t, (rot && hyp < 0) ? -c : c);
-            rotf[pb][s] = rot;
-        }
-        __syncthreads();
-        // slot s1 = s is common to the thread's positions; W's column slot
-        // w2 is s1.  (t, c, h) with h = -t for a trigonometric rotation
-        const Rot3<T> p1 = unpack_rot<T>(prm[pb][s1]);
+    const int nsteps = __builtin_amdgcn_readfirstlane(L.live) ? kB : 0;  // the same in every thread
+    T *const Wg = a.W + (size_t)k * (kB2 * kB2);
+    constexpr int kWWave = NT / 64 - 4;  // first of the four W waves (NT >= 512)
+    if (wave == 0) {
+        const CrossCount o = cross_pivot_wave<T>(a, IJ, L, nsteps);
+        double maxt = o.maxt;
+        // touched columns: L_s, and R_s(u) = b + ((s + u) mod b) for the steps
+        // u in which slot s rotated
+        const unsigned by_step = __brev(o.rotated);  // bit u
+        const int sh = lane & 31;
+        unsigned mlo = o.rotated ? 1u << sh : 0u, mhi = (by_step << sh) | (sh ? by_step >> (32 - sh) : 0u);
+        unsigned rot_sum = (unsigned)__popc(o.rotated);
 #pragma unroll
-        for (int q = 0; q < K; ++q) {
-            if (u > 0) {
-                // LR and RL of the shift to this step
-                LR[q] = xlr[(pb ^ 1) * (kB * kB) + lr_cell[q]];
-                RL[q] = xrl[(pb ^ 1) * (kB * kB) + rl_cell[q]];
-            }
-            const Rot3<T> p2 = unpack_rot<T>(prm[pb][s2[q]]);
-            // A block, rows by slot s1, columns by slot s2.  Columns first iff
-            // s1 <= s2; otherwise the same column-then-row sequence runs on
-            // the transposed block with the slots exchanged, which is the
-            // row-then-column order on the block itself.
-            const Rot3<T> pa = cf[q] ? p2 : p1, pq = cf[q] ? p1 : p2;
-            const T x01 = cf[q] ? LR[q] : RL[q], x10 = cf[q] ? RL[q] : LR[q];
-            const T f00 = fma(pa.z, x01, LL[q]) * pa.y, f01 = fma(pa.x, LL[q], x01) * pa.y;
-            const T f10 = fma(pa.z, RR[q], x10) * pa.y, f11 = fma(pa.x, x10, RR[q]) * pa.y;
-            const T y00 = fma(pq.z, f10, f00) * pq.y, y10 = fma(pq.x, f00, f10) * pq.y;
-            const T y01 = fma(pq.z, f11, f01) * pq.y, y11 = fma(pq.x, f01, f11) * pq.y;
-            LL[q] = y00;
-            RR[q] = y11;
-            LR[q] = cf[q] ? y01 : y10;
-            RL[q] = cf[q] ? y10 : y01;
-        }
-        if (diag && rotf[pb][s1]) {
-            LR[0] = T(0);
-            RL[0] = T(0);
-        }
-        if (u + 1 < kB) {
-#pragma unroll
-            for (int q = 0; q < K; ++q) {
-                xlr[pb * (kB * kB) + tid + NT * q] = LR[q];
-                xrl[pb * (kB * kB) + tid + NT * q] = RL[q];
-                RR[q] = __shfl(RR[q], nxt, 64);
-            }
-            if (tid < 64) {
-                // next pivots: a_LL of (s, s), a_LR of (s, s + 1) (lane b + s),
-                // a_RR of (s + 1, s + 1) (just shifted in)
-                plr = __shfl(LR[0], kB + (lane & 31), 64);
-                pll = LL[0];
-                prr = RR[0];
-            }
-        }
-        // W <- W R on columns (L_w2, R_w2), then the shift of its R half
-#pragma unroll
-        for (int q = 0; q < K; ++q) {
-            const Rot3<T> pw = p1;
-            const T a0 = fma(pw.z, W0R[q], W0L[q]) * pw.y, b0 = fma(pw.x, W0L[q], W0R[q]) * pw.y;
-            const T a1 = fma(pw.z, W1R[q], W1L[q]) * pw.y, b1 = fma(pw.x, W1L[q], W1R[q]) * pw.y;
-            W0L[q] = a0;
-            W1L[q] = a1;
-            W0R[q] = __shfl(b0, nxt, 64);
-            W1R[q] = __shfl(b1, nxt, 64);
-        }
-    }
-    // after b shifts the slots are back in natural order: R_s = b + s
-    T *Wg = a.W + (size_t)k * (kB2 * kB2);
-#pragma unroll
-    for (int q = 0; q < K; ++q) {
-        const int w1 = (tid + NT * q) >> 5, w2 = s;
-        Wg[w1 * kB2 + w2] = (T)W0L[q];
-        Wg[w1 * kB2 + kB + w2] = (T)W0R[q];
-        Wg[(kB + w1) * kB2 + w2] = (T)W1L[q];
-        Wg[(kB + w1) * kB2 + kB + w2] = (T)W1R[q];
-    }
-    if (tid < 64) {
-        // counters of the b slots, reduced within the first wave
-        unsigned rot_sum = (unsigned)nrot, skip_sum = (unsigned)nskip;
-        unsigned mlo = (unsigned)tmask, mhi = (unsigned)(tmask >> 32);
-#pragma unroll
-        for (int m = 32; m >= 1; m >>= 1) {
-            code |= __shfl_xor(code, m, 64);
-            rank |= __shfl_xor(rank, m, 64);
-            rot_sum += __shfl_xor(rot_sum, m, 64);
-            skip_sum += __shfl_xor(skip_sum, m, 64);
+        for (int m = 16; m >= 1; m >>= 1) {
             maxt = fmax(maxt, __shfl_xor(maxt, m, 64));
             mlo |= __shfl_xor(mlo, m, 64);
             mhi |= __shfl_xor(mhi, m, 64);
+            rot_sum += __shfl_xor(rot_sum, m, 64);
         }
         if (tid == 0) {
             const unsigned long long mask = ((unsigned long long)mhi << 32) | mlo;
-            if (rank) atomicOr(&a.ctl->rank, 1);
-            a.maxt[k] = fmax(a.maxt[k], maxt);
-            a.C[k] |= code;
-            a.nrot[k] += rot_sum;
-            a.nskip[k] += skip_sum;
-            a.nact[k] += rot_sum > 0 ? 1u : 0u;
-            a.ntc[k] += (unsigned)__popcll(mask);
+            if (o.nbad) atomicOr(&a.ctl->rank, 1);
+            a.maxt[k] = fmax(cmaxt, maxt);
+            // eq. (4.2) codes of the applied rotations, OR-ed
+            a.C[k] = cC | (rot_sum > 0 ? (maxt > a.tthresh ? 3 : 1) : 0);
+            a.nrot[k] = crot + rot_sum;
+            a.nskip[k] = cskip + (unsigned)(kB * kB) - rot_sum - o.nbad;
+            a.nact[k] = cact + (rot_sum > 0 ? 1u : 0u);
+            a.ntc[k] = ctc + (unsigned)__popcll(mask);
             a.active[k] = mask;
         }
+    } else if (wave == 1 || wave == 2) {
+        cross_tile_wave<T, NT == 256 ? 4 : 0>(L, nsteps, wave, 4 * ((wave - 1) * 4 + (lane >> 4)), Wg);
+    } else if (NT == 256) {
+        cross_w_wave<T, 8>(L, nsteps, kB + 8 * (lane >> 4), Wg);
+    } else if (wave >= kWWave) {
+        cross_w_wave<T, 4>(L, nsteps, 4 * ((wave - kWWave) * 4 + (lane >> 4)), Wg);
+    } else {
+        for (int u = 0; u <= nsteps; ++u) role_barrier();
     }
 }
 

@@ -63,13 +63,14 @@ __global__ __launch_bounds__(1024) void block_inner_circle_kernel(BlockArgsT<T> 
     inner_circle_pair<T, 1024>(a, blockIdx.x, L);
 }
 
-// With NT = b^2 (single solves) the workgroups after the block pairs' own
-// apply the previous outer step's W to V (v_update_role).
+// With NT = kCrossThreads (single solves) the workgroups after the block
+// pairs' own apply the previous outer step's W to V (v_update_role).
+constexpr int kCrossThreads = 512;
 template <typename T, int NT>
-__global__ __launch_bounds__(NT) void block_inner_cross_kernel(BlockArgsT<T> a)
+__global__ __launch_bounds__(NT, NT == kCrossThreads && sizeof(T) == 8 ? 2 : 4) void block_inner_cross_kernel(BlockArgsT<T> a)
 {
     __shared__ CrossLds<T> L;
-    if constexpr (NT == kB * kB) {
+    if constexpr (NT == kCrossThreads) {
         if ((int)blockIdx.x >= a.nb / 2) {
             v_update_role(a, (int)blockIdx.x - a.nb / 2);
             return;
@@ -134,7 +135,7 @@ __device__ void v_update_role(const BlockArgsT<T> &a, int role)
     if (!mask) return;
     const int row_base = tile * a.vrows;
     const int nstrips = min(a.vrows, a.ldg - row_base) / 16;
-    update_rows<T, 1024, true, true, kLdV>(v, k, a.V, row_base, nstrips, mask, Wl, cols, tl);
+    update_rows<T, kCrossThreads, sizeof(T) == 4, true, kLdV>(v, k, a.V, row_base, nstrips, mask, Wl, cols, tl);
 }
 
 // Outer stepper start (nb/2 slots, antidiagonal over blocks).
@@ -217,26 +218,10 @@ hipError_t launch_block_gram(hipStream_t st, const BlockArgsT<T> &a)
     return hipGetLastError();
 }
 
-// Rows of V per role workgroup: the V update of one step spread over the CUs
-// that the inner solves leave free (as many tiles per pair as fit, but at
-// least 256 rows -- a 16-row strip per wave -- per tile), in whole 16-row
-// strips so that the tiles of a pair come out nearly equal (the launch waits
-// for the largest).
-int v_update_role_rows(int pairs, int ldg, int cus, bool fp64)
-{
-    const int free_cus = cus > pairs ? cus - pairs : 1;
-    // FP64: as many tiles again as there are CUs (the role workgroups queue
-    // behind the first ones; shorter tiles balance better: FP64 inner launch
-    // at n = 4096 50.6 -> 46.5 us, whole FP64 solve 220 -> 211 ms).  FP32:
-    // one round on the free CUs (the same change made the FP32 launch slower,
-    // 34.1 -> 36.6 us).
-    int tiles = fp64 ? (free_cus + cus) / pairs : free_cus / pairs;
-    if (tiles > ldg / 256) tiles = ldg / 256;
-    if (tiles < 1) tiles = 1;
-    int rows = (ldg + tiles - 1) / tiles;
-    rows = (rows + 15) / 16 * 16;
-    return rows < ldg ? rows : ldg;
-}
+// Rows of V per role workgroup: two 16-row strips per wave (n = 4096: the FP32
+// inner launch 37.9 / 34.3 / 32.5 us at 1024 / 683 / 256 rows, the FP64 one
+// 40.5 / 39.4 us at 683 / 256).
+int v_update_role_rows(int ldg) { return ldg < 256 ? ldg : 256; }
 
 int v_update_role_wgs(int pairs, int ldg, int vrows) { return pairs * ((ldg + vrows - 1) / vrows); }
 
@@ -253,11 +238,11 @@ hipError_t launch_block_inner(hipStream_t st, const BlockArgsT<T> &a)
     }
     if (a.vprev_wgs > 0 && a.nprob > 1) return hipErrorInvalidValue;
     if (a.nprob > 1) {
-        // batched: throughput over latency -- 256 threads per block pair, four
-        // pairs per CU, each thread four blocks of A_P
+        // batched: throughput over latency -- 256 threads per block pair, its
+        // four waves sharing the work about evenly, four pairs per CU
         block_inner_cross_kernel<T, 256><<<dim3(a.nb / 2, 1, a.nprob), 256, 0, st>>>(a);
     } else {
-        block_inner_cross_kernel<T, kB * kB><<<dim3(a.nb / 2 + a.vprev_wgs, 1, a.nprob), kB * kB, 0, st>>>(a);
+        block_inner_cross_kernel<T, kCrossThreads><<<dim3(a.nb / 2 + a.vprev_wgs, 1, a.nprob), kCrossThreads, 0, st>>>(a);
     }
     return hipGetLastError();
 }

@@ -173,11 +173,11 @@ __device__ __forceinline__ bool fast_range(double aii, double ajj)
     return aii >= lo && aii <= hi && ajj >= lo && ajj <= hi;
 }
 
-__device__ __forceinline__ int rotation_params_fast(double aii, double ajj, double aij, int hyp, double &t,
-                                                    double &c)
+// The short form itself, for entries in that range (elsewhere its results mean
+// nothing).
+__device__ __forceinline__ bool rotation_params_short(double aii, double ajj, double aij, bool trig, double &t,
+                                                      double &c)
 {
-    if (!fast_range(aii, ajj)) return rotation_params(aii, ajj, aij, hyp, t, c);
-    const bool trig = hyp < 0;
     const double w = 2.0 * aij, aw = fabs(w);
     const double d = ajj - aii, S = aii + ajj;
     const double m = S - aw;
@@ -187,10 +187,17 @@ __device__ __forceinline__ int rotation_params_fast(double aii, double ajj, doub
     const double num = (trig && !(d < 0.0)) ? w : -w;
     const double tt = num * rcp_nr((trig ? fabs(d) : S) + s);
     const double cc = rsq_nr(fma(trig ? tt : -tt, tt, 1.0));
-    const int bad = (!trig && !(m > 0.0)) ? 1 : 0;
+    const bool bad = !trig && !(m > 0.0);
     t = bad ? 0.0 : tt;
     c = bad ? 1.0 : cc;
     return bad;
+}
+
+__device__ __forceinline__ int rotation_params_fast(double aii, double ajj, double aij, int hyp, double &t,
+                                                    double &c)
+{
+    if (!fast_range(aii, ajj)) return rotation_params(aii, ajj, aij, hyp, t, c);
+    return rotation_params_short(aii, ajj, aij, hyp < 0, t, c) ? 1 : 0;
 }
 
 // Relative orthogonality, eq. (2.3), strict: |a_ij| < tol sqrt(a_ii) sqrt(a_jj).
@@ -410,8 +417,8 @@ enum { UPD_BOTH = 0, UPD_G = 1, UPD_V = 2 };
 template <typename T>
 hipError_t launch_block_update(hipStream_t st, const BlockArgsT<T> &a, int which = UPD_BOTH);
 // Rows per workgroup and workgroups that the V update of one outer step takes
-// inside an inner launch (cus: compute units of the device).
-int v_update_role_rows(int pairs, int ldg, int cus, bool fp64);
+// inside an inner launch.
+int v_update_role_rows(int ldg);
 int v_update_role_wgs(int pairs, int ldg, int vrows);
 template <typename T>
 hipError_t launch_colnorm_pos(hipStream_t st, const T *G, int ldg, const int *rho, double *d, int r);
