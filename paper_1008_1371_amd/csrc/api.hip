@@ -454,8 +454,7 @@ hsvd_status block_sweeps(hsvd_ctx *ctx, const Workspace &w, BlockArgsT<T> &ba, c
     T *const Wb = ba.W;
     unsigned long long *const Ab = ba.active;
     const bool fuse = ba.V != nullptr && ba.inner_sweeps == 0 && ba.nprob <= 1;
-    ba.vrows = fuse ? v_update_role_rows(ldg) : 0;
-    const int vwgs = fuse ? v_update_role_wgs(pairs, ldg, ba.vrows) : 0;
+    const int vwgs = fuse ? v_update_role_wgs(pairs, ldg) : 0;
     for (int sw = 0; sw < max_sweeps; ++sw) {
         for (int k = 0; k < steps_per_sweep; ++k, ++gstep) {
             const int par = (int)(gstep & 1);

@@ -996,31 +996,18 @@ __device__ __forceinline__ void inner_cross_pair(const BlockArgsT<T> &a, int k, 
 // (i = output column, j = row) store 16 consecutive rows likewise -- no LDS
 // staging of the data.  W sits in LDS for all strips of the workgroup.
 // ---------------------------------------------------------------------------
-// Per storage type: FP32 re-reads W from LDS for every strip and keeps the
-// next strip's rows in flight in registers (low register use, high
-// occupancy); FP64, at twice the registers per operand, holds all 64 W
-// operands in registers across strips instead (measured faster for it).
+// One strip per wave: 64 rows per 256-thread workgroup.  Every workgroup then
+// runs one chain -- column list and W, the strip's rows, 64 products, stores --
+// and the many short workgroups of a compute unit overlap theirs.  Longer
+// tiles kept W for several strips (FP64: in 128 registers) at a fraction of
+// the waves: with 256 rows the FP64 launch of a graded n = 1024 solve took
+// 18 us against 10.2, at n = 4096 33.7 us against 31.1; with 128 rows the FP32
+// launch at n = 1024 took 15.8 us against 13.7 (n = 4096: the same).
 template <typename T>
-struct UpdCfg;
-template <>
-struct UpdCfg<float> {
-    // rows per workgroup: in the solve many pairs update few or no columns,
-    // and a launch lasts as long as the workgroups of fully active pairs,
-    // whose waves stream their strips one after another; 128 rows (2 strips
-    // per wave) measured 29.9 us per launch against 31.7 us at 512 (64 rows:
-    // the same as 128)
-    static constexpr int rows = 128;
-    static constexpr int ld = kB2 + 16;    // LDS row stride of W: a read's 4 row groups in distinct banks
-    static constexpr bool w_lds = true;    // W re-read from LDS per strip
-    static constexpr int min_blocks = 4;   // workgroups per CU to fit
+struct UpdCfg {
+    static constexpr int ld = sizeof(T) == 4 ? kB2 + 16 : kB2 + 8;  // LDS row stride of W: a read's 4 row groups in distinct banks
 };
-template <>
-struct UpdCfg<double> {
-    static constexpr int rows = 256;
-    static constexpr int ld = kB2 + 1;
-    static constexpr bool w_lds = false;
-    static constexpr int min_blocks = 1;
-};
+constexpr int kUpdRows = 64;
 
 // Compact update of a block pair whose rotations touched only m <= NC of its
 // 2b local columns (list tl, physical columns cols): the other columns of W
@@ -1078,8 +1065,9 @@ __device__ __forceinline__ void update_compact(const BlockArgsT<T> &a, int k, T 
 // touched local columns (nonzero).  kWLds: W re-read from LDS for every
 // 16-row strip with the next strip's rows prefetched into registers when
 // kPrefetch (else the compiler keeps all 64 W operands in registers across
-// strips); kLd: LDS row stride of W.  Every thread must call it (barriers).
-template <typename T, int NT, bool kWLds, bool kPrefetch, int kLd>
+// strips); kOne: at most one strip per wave (nstrips <= NT / 64), no loop;
+// kLd: LDS row stride of W.  Every thread must call it (barriers).
+template <typename T, int NT, bool kWLds, bool kPrefetch, int kLd, bool kOne = false>
 __device__ __forceinline__ void update_rows(const BlockArgsT<T> &a, int k, T *__restrict__ M, int row_base,
                                             int nstrips, unsigned long long mask, T *Wl, int *cols, int *tl)
 {
@@ -1100,9 +1088,16 @@ __device__ __forceinline__ void update_rows(const BlockArgsT<T> &a, int k, T *__
             update_compact<T, 32, NT>(a, k, M, row_base, nstrips, Wl, cols, tl, m);
         return;
     }
+    // W on its way while the column list is made; the first strip's rows on
+    // theirs while W goes to LDS
+    typedef T v4 __attribute__((ext_vector_type(4)));
+    constexpr int kW4 = kB2 * kB2 / 4 / NT;
+    static_assert(kW4 * NT * 4 == kB2 * kB2, "thread count");
+    const v4 *Wg = reinterpret_cast<const v4 *>(a.W + (size_t)k * (kB2 * kB2));
+    v4 wreg[kW4];
+#pragma unroll
+    for (int q = 0; q < kW4; ++q) wreg[q] = Wg[threadIdx.x + q * NT];
     if (threadIdx.x < kB2) cols[threadIdx.x] = a.rho[local_pos(threadIdx.x, IJ.x, IJ.y)];
-    const T *Wg = a.W + (size_t)k * (kB2 * kB2);
-    for (int idx = threadIdx.x; idx < kB2 * kB2; idx += NT) Wl[(idx / kB2) * kLd + idx % kB2] = Wg[idx];
     __syncthreads();
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int lr = lane & 15, lk = lane >> 4;
@@ -1118,18 +1113,26 @@ __device__ __forceinline__ void update_rows(const BlockArgsT<T> &a, int k, T *__
         for (int kk = 0; kk < 16; ++kk)
             bv[kk] = *reinterpret_cast<const T *>(base + ((unsigned)cp[4 * kk + lk] * col_bytes + rb));
     };
-    constexpr bool kPre = kWLds && kPrefetch;
+    constexpr bool kPre = kWLds && kPrefetch && !kOne;
     T bv[16], nx[16];
-    if (kPre && wave < nstrips) load(wave, bv, cols);
+    if (wave < nstrips) load(wave, bv, cols);
+#pragma unroll
+    for (int q = 0; q < kW4; ++q) {
+        const int idx = (threadIdx.x + q * NT) * 4;
+        T *const w = Wl + (idx / kB2) * kLd + idx % kB2;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) w[e] = wreg[q][e];
+    }
+    __syncthreads();
 #pragma unroll 1
-    for (int strip = wave; strip < nstrips; strip += NW) {
+    for (int strip = wave; strip < nstrips; strip += kOne ? nstrips : NW) {
         // With kWLds, the opaque zero wz keeps the compiler from hoisting the
         // column offsets and the 64 W operands into registers across strips.
         int wz = 0;
-        if (kWLds) asm volatile("" : "+v"(wz));
+        if (kWLds && !kOne) asm volatile("" : "+v"(wz));
         if (kPre)  // next strip in flight during the products; the last re-reads its own rows
             load(strip + NW < nstrips ? strip + NW : strip, nx, cols + wz);
-        else
+        else if (!kOne && strip != wave)
             load(strip, bv, cols + wz);
         const T *Wp = Wl + wz + lk * kLd + lr;
         typename MF<T>::acc acc[4];

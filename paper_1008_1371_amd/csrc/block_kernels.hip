@@ -67,7 +67,7 @@ __global__ __launch_bounds__(1024) void block_inner_circle_kernel(BlockArgsT<T> 
 // pairs' own apply the previous outer step's W to V (v_update_role).
 constexpr int kCrossThreads = 512;
 template <typename T, int NT>
-__global__ __launch_bounds__(NT, NT == kCrossThreads && sizeof(T) == 8 ? 2 : 4) void block_inner_cross_kernel(BlockArgsT<T> a)
+__global__ __launch_bounds__(NT, 4) void block_inner_cross_kernel(BlockArgsT<T> a)
 {
     __shared__ CrossLds<T> L;
     if constexpr (NT == kCrossThreads) {
@@ -90,9 +90,9 @@ __global__ __launch_bounds__(NT, NT == kCrossThreads && sizeof(T) == 8 ? 2 : 4) 
 // or with few touched columns do little, the busiest XCD set the launch time
 // (FP32 update at n = 4096: 29.7 -> 25.3 us per launch, bit-identical).
 template <typename T>
-__global__ __launch_bounds__(256, UpdCfg<T>::min_blocks) void block_update_kernel(BlockArgsT<T> a)
+__global__ __launch_bounds__(256, 4) void block_update_kernel(BlockArgsT<T> a)
 {
-    constexpr int kRows = UpdCfg<T>::rows, kUpdLd = UpdCfg<T>::ld;
+    constexpr int kRows = kUpdRows, kUpdLd = UpdCfg<T>::ld;
     __shared__ T Wl[kB2 * kUpdLd];
     __shared__ int cols[kB2];
     __shared__ int tl[kB2];
@@ -107,24 +107,24 @@ __global__ __launch_bounds__(256, UpdCfg<T>::min_blocks) void block_update_kerne
     T *__restrict__ M = t < tiles_g ? a.G : a.V;
     const int row_base = (t < tiles_g ? t : t - tiles_g) * kRows;
     const int nstrips = min(kRows, a.ldg - row_base) / 16;
-    update_rows<T, 256, UpdCfg<T>::w_lds, true, kUpdLd>(a, k, M, row_base, nstrips, mask, Wl, cols, tl);
+    update_rows<T, 256, true, false, kUpdLd, true>(a, k, M, row_base, nstrips, mask, Wl, cols, tl);
 }
 
 // V update of the previous outer step inside an inner-solve launch: workgroup
-// `role` (after the block pairs' own workgroups) takes rows [tile * a.vrows,
-// ...) of V for block pair role / tiles.  The inner solve holds only one
-// workgroup per block pair, most CUs are free meanwhile, and the next step's
-// Gram needs G alone, so V's half of the update runs here instead of after
-// the inner solve.  1024 threads: W from LDS (the 64 W operands do not fit
-// the register budget of a 1024-thread workgroup), prefetch for FP32 only.
+// `role` (after the block pairs' own workgroups) takes rows [tile * kRoleRows,
+// ...) of V for block pair role / tiles, one strip per wave as the update
+// kernel.  The inner solve holds only one workgroup per block pair, most CUs
+// are free meanwhile, and the next step's Gram needs G alone, so V's half of
+// the update runs here instead of after the inner solve.
+constexpr int kRoleRows = kCrossThreads / 64 * 16;
 template <typename T>
 __device__ void v_update_role(const BlockArgsT<T> &a, int role)
 {
-    constexpr int kLdV = sizeof(T) == 8 ? kB2 + 8 : kB2 + 16;
+    constexpr int kLdV = UpdCfg<T>::ld;
     __shared__ T Wl[kB2 * kLdV];
     __shared__ int cols[kB2];
     __shared__ int tl[kB2];
-    const int tiles = (a.ldg + a.vrows - 1) / a.vrows;
+    const int tiles = (a.ldg + kRoleRows - 1) / kRoleRows;
     const int k = role / tiles, tile = role - k * tiles;
     BlockArgsT<T> v = a;
     v.W = a.W_prev;
@@ -133,9 +133,9 @@ __device__ void v_update_role(const BlockArgsT<T> &a, int role)
     v.step = a.step_prev;
     const unsigned long long mask = v.active[k];
     if (!mask) return;
-    const int row_base = tile * a.vrows;
-    const int nstrips = min(a.vrows, a.ldg - row_base) / 16;
-    update_rows<T, kCrossThreads, sizeof(T) == 4, true, kLdV>(v, k, a.V, row_base, nstrips, mask, Wl, cols, tl);
+    const int row_base = tile * kRoleRows;
+    const int nstrips = min(kRoleRows, a.ldg - row_base) / 16;
+    update_rows<T, kCrossThreads, true, false, kLdV, true>(v, k, a.V, row_base, nstrips, mask, Wl, cols, tl);
 }
 
 // Outer stepper start (nb/2 slots, antidiagonal over blocks).
@@ -218,12 +218,7 @@ hipError_t launch_block_gram(hipStream_t st, const BlockArgsT<T> &a)
     return hipGetLastError();
 }
 
-// Rows of V per role workgroup: two 16-row strips per wave (n = 4096: the FP32
-// inner launch 37.9 / 34.3 / 32.5 us at 1024 / 683 / 256 rows, the FP64 one
-// 40.5 / 39.4 us at 683 / 256).
-int v_update_role_rows(int ldg) { return ldg < 256 ? ldg : 256; }
-
-int v_update_role_wgs(int pairs, int ldg, int vrows) { return pairs * ((ldg + vrows - 1) / vrows); }
+int v_update_role_wgs(int pairs, int ldg) { return pairs * ((ldg + kRoleRows - 1) / kRoleRows); }
 
 template <typename T>
 hipError_t launch_block_inner(hipStream_t st, const BlockArgsT<T> &a)
@@ -250,7 +245,7 @@ hipError_t launch_block_inner(hipStream_t st, const BlockArgsT<T> &a)
 template <typename T>
 hipError_t launch_block_update(hipStream_t st, const BlockArgsT<T> &a, int which)
 {
-    const int tiles_g = (a.ldg + UpdCfg<T>::rows - 1) / UpdCfg<T>::rows;
+    const int tiles_g = (a.ldg + kUpdRows - 1) / kUpdRows;
     BlockArgsT<T> b = a;
     int tiles = tiles_g * (a.V ? 2 : 1);
     b.tile0 = 0;

@@ -380,7 +380,6 @@ struct BlockArgsT {
     // previous outer step's W (W_prev, active_prev, its outer pairs from S_prev
     // or step_prev) to V.
     int vprev_wgs = 0;
-    int vrows = 0;           // rows of V per V-update workgroup
     T *W_prev = nullptr;
     unsigned long long *active_prev = nullptr;
     const int4 *S_prev = nullptr;
@@ -416,10 +415,8 @@ hipError_t launch_block_inner(hipStream_t st, const BlockArgsT<T> &a);
 enum { UPD_BOTH = 0, UPD_G = 1, UPD_V = 2 };
 template <typename T>
 hipError_t launch_block_update(hipStream_t st, const BlockArgsT<T> &a, int which = UPD_BOTH);
-// Rows per workgroup and workgroups that the V update of one outer step takes
-// inside an inner launch.
-int v_update_role_rows(int ldg);
-int v_update_role_wgs(int pairs, int ldg, int vrows);
+// Workgroups that the V update of one outer step takes inside an inner launch.
+int v_update_role_wgs(int pairs, int ldg);
 template <typename T>
 hipError_t launch_colnorm_pos(hipStream_t st, const T *G, int ldg, const int *rho, double *d, int r);
 hipError_t launch_block_trace(hipStream_t st, int ordering, int r, int b, int step, int4 *S, int *out,
