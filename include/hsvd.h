@@ -97,7 +97,9 @@ typedef struct {
                         group's)                                               */
     int persistent;  /* pairwise path: 0 = one launch per parallel step (replayed from a
                         HIP graph when graph = 1) and the stop rule checked on the host
-                        after every sweep; 1 = all sweeps in one persistent cooperative
+                        after every sweep -- except bordered orders up to 128 with the
+                        modified modulus ordering, which one workgroup solves in one
+                        launch; 1 = all sweeps in one persistent cooperative
                         launch: a pair waits only for the two visits of the previous
                         step that last held its columns (per-column visit counts), and
                         the diagonal sort and the stop rule (eq. 4.2) run on the device

@@ -872,9 +872,40 @@ hsvd_status solve_canonical(hsvd_ctx *ctx, const double *G, int lda, int n, int 
         HSVD_TRY(hipStreamSynchronize(st));
         return HSVD_OK;
     };
+    // Pairwise orders that one workgroup holds in its registers: the whole
+    // solve in one launch (n = 128: 5.2 ms in per-step launches, where each of
+    // the 1152 steps is one; above, G and V no longer fit, and round-robin
+    // moves both columns of every slot between steps).
+    const bool small = !block && !prm.persistent && prm.ordering == HSVD_ORD_MODMOD && r <= kSmallMaxOrder;
     if (timing) HSVD_TRY(hipEventRecord(ev[0], st));
-    s = start();
-    if (s != HSVD_OK) return s;
+    if (!small) {
+        s = start();
+        if (s != HSVD_OK) return s;
+    } else {
+        SmallArgs a;
+        a.G = G;
+        a.lda = lda;
+        a.n = n;
+        a.r = r;
+        a.p = p;
+        a.sort = prm.sort ? 1 : 0;
+        a.max_sweeps = max_sweeps;
+        a.want_v = want_v ? 1 : 0;
+        a.tol = tol;
+        a.tthresh = tthresh;
+        a.sigma = sigma;
+        a.U = U;
+        a.V = V;
+        a.lambda = lambda;
+        a.ldu = ldu;
+        a.ldv = ldv;
+        a.perm = perm;
+        a.ctl = w.ctl;
+        HSVD_TRY(launch_pair_small(st, a));
+        if (timing) HSVD_TRY(hipEventRecord(ev[1], st));
+        HSVD_TRY(hipMemcpyAsync(ctx->host_ctl, w.ctl, sizeof(Ctl), hipMemcpyDeviceToHost, st));
+        HSVD_TRY(hipStreamSynchronize(st));
+    }
 
     hsvd_status status = HSVD_OK;
     int sweeps = 0, sweeps32 = 0, code = 0, ns_iters = 0, restarted = 0;
@@ -890,7 +921,20 @@ hsvd_status solve_canonical(hsvd_ctx *ctx, const double *G, int lda, int n, int 
 
     bool converged = false;
     long long gstep = 0;
-    if (status == HSVD_OK && !block) {
+    if (small) {
+        sweeps = ctx->host_ctl->sweeps;
+        steps = (long long)sweeps * steps_per_sweep;
+        code = ctx->host_ctl->code;
+        maxt_last = ctx->host_ctl->maxt;
+        if (status == HSVD_OK && (code & 2) != 0) status = HSVD_E_NOCONV;
+        klaunch[HSVD_K_PAIR_STEP] += 1;
+        ktimed[HSVD_K_PAIR_STEP] += timing ? 1 : 0;
+        if (timing) {
+            float ms = 0.f;
+            HSVD_TRY(hipEventElapsedTime(&ms, ev[0], ev[1]));
+            kms[HSVD_K_PAIR_STEP] += ms;
+        }
+    } else if (status == HSVD_OK && !block) {
         StepArgs a;
         a.G = w.G;
         a.V = want_v ? w.V : nullptr;
@@ -1167,9 +1211,11 @@ hsvd_status solve_canonical(hsvd_ctx *ctx, const double *G, int lda, int n, int 
         if (status == HSVD_E_DEVICE) return status;
     }
 
-    HSVD_TRY(launch_finalize(st, fin, n, r, p, ldg, sigma, U, ldu, V, ldv, lambda, perm));
-    if (timing) HSVD_TRY(hipEventRecord(ev[1], st));
-    HSVD_TRY(hipStreamSynchronize(st));
+    if (!small) {
+        HSVD_TRY(launch_finalize(st, fin, n, r, p, ldg, sigma, U, ldu, V, ldv, lambda, perm));
+        if (timing) HSVD_TRY(hipEventRecord(ev[1], st));
+        HSVD_TRY(hipStreamSynchronize(st));
+    }
     if (info) {
         float ms = 0.f;
         if (timing) hipEventElapsedTime(&ms, ev[0], ev[1]);

@@ -220,7 +220,7 @@ __global__ void batch_zero_ctl_kernel(Ctl *ctl, int nprob, int *active_count, co
     ctl[z].code = 0;
     ctl[z].rank = 0;
     ctl[z].inval = 0;
-    ctl[z].pad = 0;
+    ctl[z].sweeps = 0;
     ctl[z].rot = 0;
     ctl[z].skip = 0;
     ctl[z].act = 0;

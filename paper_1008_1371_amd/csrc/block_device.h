@@ -455,15 +455,6 @@ __device__ __forceinline__ double row_next(double v)
     return __hiloint2double(row_next(__double2hiint(v)), row_next(__double2loint(v)));
 }
 
-// Workgroup barrier for waves that run different loops: every wave of the
-// workgroup executes the same number of them.
-__device__ __forceinline__ void role_barrier()
-{
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
-    __builtin_amdgcn_s_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
-}
-
 // ---------------------------------------------------------------------------
 // Inner solve of one block pair for the cross steps (every outer step but the
 // first of a sweep), register-resident.

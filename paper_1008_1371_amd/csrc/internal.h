@@ -21,7 +21,7 @@ struct Ctl {
     int code;          // OR of the eq. (4.2) codes of the sweep just reduced
     int rank;          // set when a pair is numerically rank deficient
     int inval;         // set when the input holds a non-finite value
-    int pad;
+    int sweeps;        // sweeps run (the one-workgroup pairwise kernel; else 0)
     unsigned long long rot;    // rotations, cumulative
     unsigned long long skip;   // skipped pair visits, cumulative
     unsigned long long act;    // block pair steps with a rotation, cumulative
@@ -326,6 +326,15 @@ __device__ __forceinline__ void block_sum2(double &a, double &b, double *sh)
     b = sb;
 }
 
+// Workgroup barrier for waves that run different loops: every wave of the
+// workgroup executes the same number of them.
+__device__ __forceinline__ void role_barrier()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+}
+
 // ---------------------------------------------------------------------------
 // Kernel launchers (pairwise path), all on `st`.
 // ---------------------------------------------------------------------------
@@ -363,6 +372,20 @@ struct PairPersistArgs {
     PersistCtl *pc;
     long long spin_limit;  // wall-clock ticks one wait may take before the launch gives up
 };
+
+// Pairwise solves with r <= kSmallMaxOrder (modified modulus ordering) in one
+// workgroup, from the caller's G to the caller's outputs (pair_small.hip).
+constexpr int kSmallMaxOrder = 128;
+struct SmallArgs {
+    const double *G;
+    int lda, n, r, p, sort, max_sweeps, want_v;
+    double tol, tthresh;
+    double *sigma, *U, *V, *lambda;  // U, V, lambda, perm may be null
+    int ldu, ldv;
+    int *perm;
+    Ctl *ctl;
+};
+hipError_t launch_pair_small(hipStream_t st, const SmallArgs &a);
 
 template <typename T>
 struct BlockArgsT {

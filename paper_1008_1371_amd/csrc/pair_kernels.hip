@@ -551,7 +551,7 @@ __global__ void zero_ctl_kernel(Ctl *ctl)
         ctl->code = 0;
         ctl->rank = 0;
         ctl->inval = 0;
-        ctl->pad = 0;
+        ctl->sweeps = 0;
         ctl->rot = 0;
         ctl->skip = 0;
         ctl->act = 0;
