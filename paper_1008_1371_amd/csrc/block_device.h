@@ -199,218 +199,75 @@ __device__ __forceinline__ void gram_pair(const BlockArgsT<T> &a, int k, int spl
     }
 }
 
-// ---------------------------------------------------------------------------
-// Inner solve of one block pair over all pairs of its 2b columns: sweeps of the
-// circle method over 2b indices (2b - 1 inner steps of b pairs each).  One
-// sweep in the first outer step of a sweep of the block-oriented method;
-// repeated until a sweep applies no rotation (at most a.inner_sweeps) in every
-// outer step of the full-block method.
-//
-// A_P and W live in LDS.  At an inner step every local index belongs to
-// exactly one slot, so the 2x2 block (s1, s2) of A_P -- rows of slot s1's
-// pair, columns of slot s2's -- is read and written by thread (s1, s2) alone,
-// and W's columns of slot q by the 32 threads of that slot; the first wave
-// evaluates the b rotations.  Mirrored blocks apply row and column operations
-// in mirrored order (the transposed block runs the same column-then-row
-// sequence), so A_P stays exactly symmetric.  Two barriers per inner step.
-// ---------------------------------------------------------------------------
-struct CircleLds {
-    double A[kB2 * kLd];
-    double Wl[kB2 * kLd];
-    double4 prm[kB];  // (t, c, t or -t, rotated) of each slot
-    int2 pxy[kB];     // local indices (x < y) of each slot's pair
-    int s_any, s_sweep_any;
-};
-
-// NT threads (a multiple of 64 dividing b^2 = 1024): thread tid takes the A
-// blocks and W items at positions tid + NT q, q < 1024 / NT.  Every thread
-// must call it (barriers).
-template <typename T, int NT>
-__device__ __forceinline__ void inner_circle_pair(const BlockArgsT<T> &a, int k, CircleLds &L)
+// A_P = sum of the partial Grams in split order into buf (row stride LD), by
+// NT threads.  Only the 10 upper-triangular 16 x 16 tiles hold data: work item
+// i sums the entries (x, y), (x, y + 1) of tile i / 128 of every split with
+// vector loads.
+template <typename T, int NT, int LD>
+__device__ __forceinline__ void stage_gram(const BlockArgsT<T> &a, int k, double *buf)
 {
-    constexpr int KC = (kB * kB) / NT;
-    static_assert(KC * NT == kB * kB && NT % 64 == 0, "thread count");
-    double *const A = L.A, *const Wl = L.Wl;
-    double4 *const prm = L.prm;
-    int2 *const pxy = L.pxy;
-    int &s_any = L.s_any, &s_sweep_any = L.s_sweep_any;
+    constexpr int kItems = kGramTiles * 128;
+    typedef T v2 __attribute__((ext_vector_type(2)));
+    constexpr int kChunk = 8;
     const int tid = threadIdx.x;
-    const int2 IJ = outer_pair(a, k);
-
-    // A_P = sum of the partial Grams in split order (upper-triangular tiles,
-    // vector loads), then every entry (x, y) taken from (min, max)
-    {
-        typedef T v4 __attribute__((ext_vector_type(4)));
-        constexpr int kChunk = sizeof(T) == 4 ? 16 : 8;
 #pragma unroll
-        for (int qi = 0; qi < KC; ++qi) {
-            const int item = tid + NT * qi;
-            const int x = item >> 4, y0 = (item & 15) * 4;
-            if ((y0 >> 4) >= (x >> 4)) {
-                const T *P = a.partial + (size_t)k * a.splits * (kB2 * kB2) + x * kB2 + y0;
-                double g0 = 0.0, g1 = 0.0, g2 = 0.0, g3 = 0.0;
-                for (int base = 0; base < a.splits; base += kChunk) {
-                    v4 v[kChunk];
+    for (int q = 0; q < (kItems + NT - 1) / NT; ++q) {
+        const int item = tid + NT * q;
+        if (kItems % NT == 0 || item < kItems) {
+            const int tile = item >> 7, x = kGramTX[tile] * 16 + ((item >> 3) & 15), y = kGramTY[tile] * 16 + (item & 7) * 2;
+            const T *P = a.partial + (size_t)k * a.splits * (kB2 * kB2) + x * kB2 + y;
+            double g0 = 0.0, g1 = 0.0;
+            for (int base = 0; base < a.splits; base += kChunk) {
+                v2 v[kChunk];
 #pragma unroll
-                    for (int q = 0; q < kChunk; ++q)
-                        v[q] = base + q < a.splits
-                                   ? *reinterpret_cast<const v4 *>(P + (size_t)(base + q) * (kB2 * kB2))
-                                   : v4{0, 0, 0, 0};
+                for (int c = 0; c < kChunk; ++c)
+                    v[c] = base + c < a.splits
+                               ? *reinterpret_cast<const v2 *>(P + (size_t)(base + c) * (kB2 * kB2))
+                               : v2{0, 0};
 #pragma unroll
-                    for (int q = 0; q < kChunk; ++q)
-                        if (base + q < a.splits) {
-                            const bool first = base + q == 0;
-                            g0 = first ? (double)v[q][0] : g0 + (double)v[q][0];
-                            g1 = first ? (double)v[q][1] : g1 + (double)v[q][1];
-                            g2 = first ? (double)v[q][2] : g2 + (double)v[q][2];
-                            g3 = first ? (double)v[q][3] : g3 + (double)v[q][3];
-                        }
-                }
-                double *row = A + x * kLd + y0;
-                row[0] = g0;
-                row[1] = g1;
-                row[2] = g2;
-                row[3] = g3;
-            }
-        }
-    }
-    if (tid == 0) {
-        s_any = 0;
-        s_sweep_any = 0;
-    }
-    __syncthreads();
-    for (int idx = tid; idx < kB2 * kB2; idx += NT) {
-        const int x = idx >> 6, y = idx & 63;
-        if (x > y) A[x * kLd + y] = A[y * kLd + x];
-        Wl[x * kLd + y] = x == y ? 1.0 : 0.0;
-    }
-    __syncthreads();
-
-    int code = 0, nrot = 0, nskip = 0, rank = 0;
-    double maxt = 0.0;
-    unsigned long long tmask = 0ull;
-    const double tol2 = a.tol * a.tol;
-    const int nsweeps = a.inner_sweeps > 0 ? a.inner_sweeps : 1;
-    int mark = 0;  // index of the current inner step, from 1
-    for (int sw = 0; sw < nsweeps; ++sw) {
-        for (int u = 0; u < kB2 - 1; ++u) {
-            ++mark;
-            if (tid < kB) {
-                const int q = tid;
-                const int2 xy = block_inner_pair(q, u, true, kB);
-                const int x = xy.x, y = xy.y;
-                const double axx = A[x * kLd + x], ayy = A[y * kLd + y], axy = A[x * kLd + y];
-                double t = 0.0, c = 1.0, h = 0.0;
-                int rot = 0;
-                if (rel_orthogonal_sq(axx, ayy, axy, a.tol, tol2)) {
-                    ++nskip;
-                } else {
-                    const int px_ = local_pos(x, IJ.x, IJ.y), py_ = local_pos(y, IJ.x, IJ.y);
-                    const int hyp = ((px_ < a.p) == (py_ < a.p)) ? -1 : 1;
-                    if (rotation_params_fast(axx, ayy, axy, hyp, t, c)) {
-                        rank = 1;
-                        t = 0.0;
-                        c = 1.0;
-                    } else {
-                        rot = 1;
-                        ++nrot;
-                        code |= rotation_code(t, a.tthresh);
-                        maxt = fmax(maxt, fabs(t));
-                        h = hyp < 0 ? -t : t;
-                        tmask |= (1ull << x) | (1ull << y);
+                for (int c = 0; c < kChunk; ++c)
+                    if (base + c < a.splits) {
+                        const bool first = base + c == 0;
+                        g0 = first ? (double)v[c][0] : g0 + (double)v[c][0];
+                        g1 = first ? (double)v[c][1] : g1 + (double)v[c][1];
                     }
-                }
-                prm[q] = make_double4(t, c, h, rot ? 1.0 : 0.0);
-                pxy[q] = xy;
-                if (rot) {
-                    s_any = mark;
-                    s_sweep_any = sw + 1;
-                }
             }
-            __syncthreads();
-            // no rotation in this inner step: A and W unchanged.  The first wave
-            // may already be writing the next step's mark, but only after this
-            // step had none, so a late reader still sees a mismatch.
-            if (s_any != mark) continue;
-#pragma unroll
-            for (int qa = 0; qa < KC; ++qa) {
-                // A block: rows (x1, y1) by slot s1, columns (x2, y2) by slot s2
-                const int pos = tid + NT * qa;
-                const int s1 = pos >> 5, s2 = pos & 31;
-                const bool cf = s1 <= s2;
-                const int2 r1 = pxy[s1], r2 = pxy[s2];
-                const double4 pa = prm[cf ? s2 : s1], pq = prm[cf ? s1 : s2];
-                const double e00 = A[r1.x * kLd + r2.x], e01 = A[r1.x * kLd + r2.y];
-                const double e10 = A[r1.y * kLd + r2.x], e11 = A[r1.y * kLd + r2.y];
-                const double x01 = cf ? e01 : e10, x10 = cf ? e10 : e01;
-                const double f00 = fma(pa.z, x01, e00) * pa.y, f01 = fma(pa.x, e00, x01) * pa.y;
-                const double f10 = fma(pa.z, e11, x10) * pa.y, f11 = fma(pa.x, x10, e11) * pa.y;
-                const double y00 = fma(pq.z, f10, f00) * pq.y, y10 = fma(pq.x, f00, f10) * pq.y;
-                const double y01 = fma(pq.z, f11, f01) * pq.y, y11 = fma(pq.x, f01, f11) * pq.y;
-                double o01 = cf ? y01 : y10, o10 = cf ? y10 : y01;
-                if (s1 == s2 && pa.w != 0.0) {
-                    o01 = 0.0;
-                    o10 = 0.0;
-                }
-                A[r1.x * kLd + r2.x] = y00;
-                A[r1.x * kLd + r2.y] = o01;
-                A[r1.y * kLd + r2.x] = o10;
-                A[r1.y * kLd + r2.y] = y11;
-            }
-#pragma unroll
-            for (int qw = 0; qw < KC; ++qw) {
-                // W <- W R on the columns of slot wq, rows wr and wr + 32
-                const int pos = tid + NT * qw;
-                const int wq = pos & 31, wr = pos >> 5;
-                const int2 xy = pxy[wq];
-                const double4 pw = prm[wq];
-                if (pw.w != 0.0) {
-#pragma unroll
-                    for (int h2 = 0; h2 < 2; ++h2) {
-                        const int w = wr + 32 * h2;
-                        const double wx = Wl[w * kLd + xy.x], wy = Wl[w * kLd + xy.y];
-                        Wl[w * kLd + xy.x] = fma(pw.z, wy, wx) * pw.y;
-                        Wl[w * kLd + xy.y] = fma(pw.x, wx, wy) * pw.y;
-                    }
-                }
-            }
-            __syncthreads();
-        }
-        // a sweep without rotations: the block is diagonal.  s_sweep_any only
-        // grows (the first wave starts sweep sw + 1, and may raise it, only
-        // after sweep sw rotated), so every thread takes the same decision
-        // even if it reads the flag late.
-        if (s_sweep_any < sw + 1) break;
-    }
-    T *Wg = a.W + (size_t)k * (kB2 * kB2);
-    for (int idx = tid; idx < kB2 * kB2; idx += NT) Wg[idx] = (T)Wl[(idx >> 6) * kLd + (idx & 63)];
-    if (tid < 64) {
-        // counters of the b slots, reduced within the first wave
-        unsigned rot_sum = (unsigned)nrot, skip_sum = (unsigned)nskip;
-        unsigned mlo = (unsigned)tmask, mhi = (unsigned)(tmask >> 32);
-#pragma unroll
-        for (int m = 32; m >= 1; m >>= 1) {
-            code |= __shfl_xor(code, m, 64);
-            rank |= __shfl_xor(rank, m, 64);
-            rot_sum += __shfl_xor(rot_sum, m, 64);
-            skip_sum += __shfl_xor(skip_sum, m, 64);
-            maxt = fmax(maxt, __shfl_xor(maxt, m, 64));
-            mlo |= __shfl_xor(mlo, m, 64);
-            mhi |= __shfl_xor(mhi, m, 64);
-        }
-        if (tid == 0) {
-            const unsigned long long mask = ((unsigned long long)mhi << 32) | mlo;
-            if (rank) atomicOr(&a.ctl->rank, 1);
-            a.maxt[k] = fmax(a.maxt[k], maxt);
-            a.C[k] |= code;
-            a.nrot[k] += rot_sum;
-            a.nskip[k] += skip_sum;
-            a.nact[k] += rot_sum > 0 ? 1u : 0u;
-            a.ntc[k] += (unsigned)__popcll(mask);
-            a.active[k] = mask;
+            buf[x * LD + y] = g0;
+            buf[x * LD + y + 1] = g1;
         }
     }
 }
+
+// The sweep's counters of a slot, read ahead of an inner solve and written
+// after it (one thread).
+struct SweepSoFar {
+    double maxt = 0.0;
+    int C = 0;
+    unsigned rot = 0, skip = 0, act = 0, tc = 0;
+    template <typename T>
+    __device__ __forceinline__ void read(const BlockArgsT<T> &a, int k)
+    {
+        maxt = a.maxt[k];
+        C = a.C[k];
+        rot = a.nrot[k];
+        skip = a.nskip[k];
+        act = a.nact[k];
+        tc = a.ntc[k];
+    }
+    template <typename T>
+    __device__ __forceinline__ void write(const BlockArgsT<T> &a, int k, int code, int rank, double mt, unsigned nrot,
+                                          unsigned nskip, unsigned long long mask) const
+    {
+        if (rank) atomicOr(&a.ctl->rank, 1);
+        a.maxt[k] = fmax(maxt, mt);
+        a.C[k] = C | code;
+        a.nrot[k] = rot + nrot;
+        a.nskip[k] = skip + nskip;
+        a.nact[k] = act + (nrot > 0 ? 1u : 0u);
+        a.ntc[k] = tc + (unsigned)__popcll(mask);
+        a.active[k] = mask;
+    }
+};
 
 // Per-slot rotation of the cross kernel in the precision its blocks are held
 // in: (t, c) with c negated for an applied trigonometric rotation, decoded to
@@ -592,6 +449,49 @@ __device__ __forceinline__ int cross_source(int other, int x)
     return (x > other ? 0 : kXGroup) + (row - 1) * 16 + i;
 }
 
+// Signs of the pairs of a block pair: all trigonometric, all hyperbolic, or
+// both kinds (one of the blocks holds columns of both signs, or the pairs lie
+// within blocks of different signs).
+enum { kTrig = 0, kHyp = 1, kBothKinds = 2 };
+
+// Skip test and rotation of one slot for the inner solves' rotation waves,
+// evaluated side by side (independent dependency chains).  A lone wave issues
+// one vector instruction in about six cycles whatever it depends on, so the
+// step time of an inner solve is this instruction count: the signs of the
+// pairs are settled outside the loop where they can be, and one integer
+// compare covers the ranges of the short rotation form and of the squared skip
+// test; the branch is taken only when an entry leaves them.
+struct SlotRotator {
+    double tol, tol2;
+    unsigned range_lo, range_len;  // high words of the entries the short forms take
+    __device__ __forceinline__ explicit SlotRotator(double tol_) : tol(tol_), tol2(tol_ * tol_)
+    {
+        // entries in [2^E, 2^480), E >= -480 and tol^2 2^(2E) >= 2^-999
+        int E = -480;
+        if (!(tol2 >= 0x1p-38)) E = max(E, tol2 >= 0x1p-1000 ? (-998 - ilogb(tol2)) / 2 : 1024);
+        const int lo_w = min(E + 1023, 2047), hi_w = 480 + 1023;
+        range_lo = (unsigned)lo_w << 20;
+        range_len = lo_w < hi_w ? (unsigned)(hi_w - lo_w) << 20 : 0u;
+    }
+    template <int MODE>
+    __device__ __forceinline__ void operator()(double aii, double ajj, double aij, bool trig, double &t, double &c,
+                                               bool &skip, bool &bad) const
+    {
+        bad = MODE == kTrig  ? rotation_params_short(aii, ajj, aij, true, t, c)
+              : MODE == kHyp ? rotation_params_short(aii, ajj, aij, false, t, c)
+                             : rotation_params_short(aii, ajj, aij, trig, t, c);
+        skip = aij * aij < tol2 * (aii * ajj);
+        const unsigned ei = (unsigned)__double2hiint(aii) - range_lo, ej = (unsigned)__double2hiint(ajj) - range_lo;
+        const bool odd = max(ei, ej) >= range_len;
+        if (__builtin_expect(__ballot(odd) != 0ull, 0)) {
+            if (odd) {
+                if (!fast_range(aii, ajj)) bad = rotation_params(aii, ajj, aij, trig ? -1 : 1, t, c) != 0;
+                skip = rel_orthogonal_sq(aii, ajj, aij, tol, tol2);
+            }
+        }
+    }
+};
+
 // What the pivot wave counts over the inner steps.
 struct CrossCount {
     unsigned rotated;  // lane s < b: bit b - 1 - u = slot s rotated at inner step u
@@ -599,16 +499,8 @@ struct CrossCount {
     double maxt;       // the lane's largest |t|
 };
 
-// Signs of the pairs of a block pair: all trigonometric, all hyperbolic, or
-// both kinds (one of the blocks holds columns of both signs).
-enum { kTrig = 0, kHyp = 1, kBothKinds = 2 };
-
-// The pivot wave.  A lone wave issues one vector instruction in about six
-// cycles whatever it depends on, so its step time is its instruction count:
-// the signs of the pairs are settled outside the loop where they can be, one
-// integer compare covers the ranges of the short rotation form and of the
-// squared skip test, what is counted is packed into one bit per step, and the
-// lane moves go through ds_bpermute.
+// The pivot wave; what it counts is packed into one bit per step, and the lane
+// moves go through ds_bpermute.
 template <typename T>
 struct CrossPivot {
     T P, x01, x10, N;   // the block {lo, hi} of this lane
@@ -616,8 +508,6 @@ struct CrossPivot {
     bool up, wrap;      // block {s, s + 1} (lanes 32 ..), else {s, s}; lane 63: {0, 31}, lo = s + 1
     bool lpos;          // column L_s has sign +
     int rbase, p;       // position of R_s(0) - s
-    double tol, tol2;
-    unsigned range_lo, range_len;  // high words of the entries the short forms take
     T *ex;
     const typename SlotRot<T>::packed *plo, *phi;
     int o1, o2;         // where this lane's entries for the tiles go
@@ -635,28 +525,15 @@ struct CrossPivot {
     }
 
     template <int PB, int MODE>
-    __device__ __forceinline__ void step(CrossLds<T> &L)
+    __device__ __forceinline__ void step(CrossLds<T> &L, const SlotRotator &rotator)
     {
         bool rot = false;
         if (!up) {
-            // Skip test and rotation evaluated side by side (independent
-            // dependency chains), then selected; the branch is taken only when
-            // an entry leaves the range of the short forms.
             const double pll = P, plr = x01, prr = N;
             const bool trig = MODE == kTrig || (MODE == kBothKinds && lpos == (rbase + ((s + u0 + PB) & 31) < p));
             double t, c;
-            bool bad = MODE == kTrig    ? rotation_params_short(pll, prr, plr, true, t, c)
-                       : MODE == kHyp   ? rotation_params_short(pll, prr, plr, false, t, c)
-                                        : rotation_params_short(pll, prr, plr, trig, t, c);
-            bool skip = plr * plr < tol2 * (pll * prr);
-            const unsigned el = (unsigned)__double2hiint(pll) - range_lo, er = (unsigned)__double2hiint(prr) - range_lo;
-            const bool odd = max(el, er) >= range_len;
-            if (__builtin_expect(__ballot(odd) != 0ull, 0)) {
-                if (odd) {
-                    if (!fast_range(pll, prr)) bad = rotation_params(pll, prr, plr, trig ? -1 : 1, t, c) != 0;
-                    skip = rel_orthogonal_sq(pll, prr, plr, tol, tol2);
-                }
-            }
+            bool skip, bad;
+            rotator.template operator()<MODE>(pll, prr, plr, trig, t, c, skip, bad);
             rot = !skip && !bad;
             const double tr = rot ? t : 0.0, cr = rot ? (trig ? -c : c) : 1.0;
             L.prm[PB][s] = SlotRot<T>::pack(tr, cr);
@@ -683,12 +560,12 @@ struct CrossPivot {
     }
 
     template <int MODE>
-    __device__ __forceinline__ void run(CrossLds<T> &L, int nsteps)
+    __device__ __forceinline__ void run(CrossLds<T> &L, const SlotRotator &rotator, int nsteps)
     {
 #pragma unroll 1
         for (u0 = 0; u0 < nsteps; u0 += 2) {
-            step<0, MODE>(L);
-            step<1, MODE>(L);
+            step<0, MODE>(L, rotator);
+            step<1, MODE>(L, rotator);
         }
     }
 };
@@ -708,17 +585,7 @@ __device__ __forceinline__ CrossCount cross_pivot_wave(const BlockArgsT<T> &a, i
     w.p = a.p;
     w.lpos = IJ.x * kB + s < a.p;
     w.rbase = IJ.y * kB;
-    w.tol = a.tol;
-    w.tol2 = a.tol * a.tol;
-    {
-        // entries in [2^E, 2^480), E >= -480 and tol^2 2^(2E) >= 2^-999: the
-        // short rotation form and the squared skip test both hold there
-        int E = -480;
-        if (!(w.tol2 >= 0x1p-38)) E = max(E, w.tol2 >= 0x1p-1000 ? (-998 - ilogb(w.tol2)) / 2 : 1024);
-        const int lo_w = min(E + 1023, 2047), hi_w = 480 + 1023;
-        w.range_lo = (unsigned)lo_w << 20;
-        w.range_len = lo_w < hi_w ? (unsigned)(hi_w - lo_w) << 20 : 0u;
-    }
+    const SlotRotator rotator(a.tol);
     w.plo = &L.prm[0][lo];
     w.phi = &L.prm[0][hi];
     const int i = s >> 1, dummy = 2 * kXGroup + kB + lane;
@@ -740,11 +607,11 @@ __device__ __forceinline__ CrossCount cross_pivot_wave(const BlockArgsT<T> &a, i
     const int mode = (li && lj) || (ni && nj) ? kTrig : ((li && nj) || (ni && lj) ? kHyp : kBothKinds);
     __builtin_amdgcn_s_setprio(2);
     if (mode == kTrig)
-        w.template run<kTrig>(L, nsteps);
+        w.template run<kTrig>(L, rotator, nsteps);
     else if (mode == kHyp)
-        w.template run<kHyp>(L, nsteps);
+        w.template run<kHyp>(L, rotator, nsteps);
     else
-        w.template run<kBothKinds>(L, nsteps);
+        w.template run<kBothKinds>(L, rotator, nsteps);
     __builtin_amdgcn_s_setprio(0);
     return w.n;
 }
@@ -870,50 +737,9 @@ __device__ __forceinline__ void inner_cross_pair(const BlockArgsT<T> &a, int k, 
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int2 IJ = outer_pair(a, k);
     // the sweep's counters so far, read ahead of their update at the end
-    double cmaxt = 0.0;
-    int cC = 0;
-    unsigned crot = 0, cskip = 0, cact = 0, ctc = 0;
-    if (tid == 0) {
-        cmaxt = a.maxt[k];
-        cC = a.C[k];
-        crot = a.nrot[k];
-        cskip = a.nskip[k];
-        cact = a.nact[k];
-        ctc = a.ntc[k];
-    }
-
-    // A_P = sum of the partial Grams in split order.  Only the 10
-    // upper-triangular 16 x 16 tiles hold data: work item i sums the entries
-    // (x, y), (x, y + 1) of tile i / 128 of every split with vector loads.
-    constexpr int kItems = kGramTiles * 128;
-#pragma unroll
-    for (int q = 0; q < (kItems + NT - 1) / NT; ++q) {
-        typedef T v2 __attribute__((ext_vector_type(2)));
-        constexpr int kChunk = 8;
-        const int item = tid + NT * q;
-        if (kItems % NT == 0 || item < kItems) {
-            const int tile = item >> 7, x = kGramTX[tile] * 16 + ((item >> 3) & 15), y = kGramTY[tile] * 16 + (item & 7) * 2;
-            const T *P = a.partial + (size_t)k * a.splits * (kB2 * kB2) + x * kB2 + y;
-            double g0 = 0.0, g1 = 0.0;
-            for (int base = 0; base < a.splits; base += kChunk) {
-                v2 v[kChunk];
-#pragma unroll
-                for (int c = 0; c < kChunk; ++c)
-                    v[c] = base + c < a.splits
-                               ? *reinterpret_cast<const v2 *>(P + (size_t)(base + c) * (kB2 * kB2))
-                               : v2{0, 0};
-#pragma unroll
-                for (int c = 0; c < kChunk; ++c)
-                    if (base + c < a.splits) {
-                        const bool first = base + c == 0;
-                        g0 = first ? (double)v[c][0] : g0 + (double)v[c][0];
-                        g1 = first ? (double)v[c][1] : g1 + (double)v[c][1];
-                    }
-            }
-            buf[x * kLd + y] = g0;
-            buf[x * kLd + y + 1] = g1;
-        }
-    }
+    SweepSoFar so_far;
+    if (tid == 0) so_far.read(a, k);
+    stage_gram<T, NT, kLd>(a, k, buf);
     if (tid == 0) L.live = 0;
     __syncthreads();
     {
@@ -954,18 +780,10 @@ __device__ __forceinline__ void inner_cross_pair(const BlockArgsT<T> &a, int k, 
             mhi |= __shfl_xor(mhi, m, 64);
             rot_sum += __shfl_xor(rot_sum, m, 64);
         }
-        if (tid == 0) {
-            const unsigned long long mask = ((unsigned long long)mhi << 32) | mlo;
-            if (o.nbad) atomicOr(&a.ctl->rank, 1);
-            a.maxt[k] = fmax(cmaxt, maxt);
-            // eq. (4.2) codes of the applied rotations, OR-ed
-            a.C[k] = cC | (rot_sum > 0 ? (maxt > a.tthresh ? 3 : 1) : 0);
-            a.nrot[k] = crot + rot_sum;
-            a.nskip[k] = cskip + (unsigned)(kB * kB) - rot_sum - o.nbad;
-            a.nact[k] = cact + (rot_sum > 0 ? 1u : 0u);
-            a.ntc[k] = ctc + (unsigned)__popcll(mask);
-            a.active[k] = mask;
-        }
+        // eq. (4.2) codes of the applied rotations, OR-ed
+        if (tid == 0)
+            so_far.write(a, k, rot_sum > 0 ? (maxt > a.tthresh ? 3 : 1) : 0, (int)o.nbad, maxt, rot_sum,
+                         (unsigned)(kB * kB) - rot_sum - o.nbad, ((unsigned long long)mhi << 32) | mlo);
     } else if (wave == 1 || wave == 2) {
         cross_tile_wave<T, NT == 256 ? 4 : 0>(L, nsteps, wave, 4 * ((wave - 1) * 4 + (lane >> 4)), Wg);
     } else if (NT == 256) {
@@ -977,6 +795,278 @@ __device__ __forceinline__ void inner_cross_pair(const BlockArgsT<T> &a, int k, 
     }
 }
 
+
+// ---------------------------------------------------------------------------
+// Inner solve of one block pair over all pairs of its 2b columns: sweeps of the
+// circle method over 2b indices (2b - 1 inner steps of b pairs each).  One
+// sweep in the first outer step of a sweep of the block-oriented method;
+// repeated until a sweep applies no rotation (at most a.inner_sweeps) in every
+// outer step of the full-block method.
+//
+// A_P sits in LDS, entry (i, j) at (min, max).  At an inner step every local
+// index belongs to exactly one slot, so the 2 x 2 block of the slot pair
+// {sl <= sh} is read and written by one thread alone (columns of slot sh
+// first, then rows of slot sl); the first wave evaluates the b rotations.  W
+// is held by rows in registers: lane j of a 16-lane row has the columns of
+// slots 2 j and 2 j + 1, and the circle's shift (L_k <- L_{k+1}, R_k <-
+// R_{k-1}, the ends crossing over) is a lane move within the row.  Two barriers
+// per inner step: rotations out, blocks written; the blocks' entries are
+// fetched while the rotations are evaluated.
+//
+// What bounds it: the block waves' address, read and write instructions and the
+// two barriers; the first wave (pivots from LDS 0.27, rotation 0.34 thousand
+// cycles) no longer does.  A launch over 64 pairs (FP64, one sweep): 72 us at
+// 1024 threads, 83 at 512, 113 at 256; with every block held twice, W in LDS
+// and 32-byte parameters it was bound by LDS traffic (107 us at 1024).
+// ---------------------------------------------------------------------------
+// Row stride of A_P: from slot to slot the indices of an entry move by (1, 1)
+// or (1, -1), so the addresses by kLdC + 1 or kLdC - 1 doubles: both odd, no
+// bank conflicts (at a stride of 65 every (1, -1) access of a wave met one
+// bank).
+constexpr int kLdC = kB2 + 2;
+struct CircleLds {
+    double A[kB2 * kLdC];
+    double2 prm[kB];   // (t, c) of each slot, as in the cross solve
+    unsigned rotated;  // slots that rotate in this step
+};
+
+__device__ __forceinline__ int sym_at(int i, int j) { return min(i, j) * kLdC + max(i, j); }
+
+// The two indices of slot s at inner step u, L first (roundrobin_pair without
+// its ordering), and their next values.
+struct CircleSlot {
+    int l, r;
+    __device__ __forceinline__ void start(int s)
+    {
+        l = s;
+        r = kB2 - 1 - s;
+    }
+    __device__ __forceinline__ void next()
+    {
+        l = l == 0 ? 0 : (l == kB2 - 1 ? 1 : l + 1);  // index 0 stays in slot 0
+        r = r == kB2 - 1 ? 1 : r + 1;
+    }
+};
+
+// W of RG rows and the slots 2 j, 2 j + 1.
+template <int RG>
+struct CircleW {
+    typedef double vec __attribute__((ext_vector_type(RG)));
+    vec l0, r0, l1, r1;
+    CircleSlot s0, s1;
+    __device__ __forceinline__ void init(int row, int j)
+    {
+        s0.start(2 * j);
+        s1.start(2 * j + 1);
+#pragma unroll
+        for (int q = 0; q < RG; ++q) {
+            l0[q] = row + q == s0.l ? 1.0 : 0.0;
+            r0[q] = row + q == s0.r ? 1.0 : 0.0;
+            l1[q] = row + q == s1.l ? 1.0 : 0.0;
+            r1[q] = row + q == s1.r ? 1.0 : 0.0;
+        }
+    }
+    template <int kCtrl>
+    static __device__ __forceinline__ double shifted(double edge, double v)
+    {
+        return __hiloint2double(
+            __builtin_amdgcn_update_dpp(__double2hiint(edge), __double2hiint(v), kCtrl, 0xf, 0xf, false),
+            __builtin_amdgcn_update_dpp(__double2loint(edge), __double2loint(v), kCtrl, 0xf, 0xf, false));
+    }
+    __device__ __forceinline__ void step(const double2 *prm, int j)
+    {
+        const Rot3<double> p0 = unpack_rot<double>(prm[2 * j]), p1 = unpack_rot<double>(prm[2 * j + 1]);
+        // the smaller index of a pair takes h, the other t
+        const double a0 = s0.l < s0.r ? p0.z : p0.x, b0 = s0.l < s0.r ? p0.x : p0.z;
+        const double a1 = s1.l < s1.r ? p1.z : p1.x, b1 = s1.l < s1.r ? p1.x : p1.z;
+#pragma unroll
+        for (int q = 0; q < RG; ++q) {
+            const double nl0 = fma(a0, r0[q], l0[q]) * p0.y, nr0 = fma(b0, l0[q], r0[q]) * p0.y;
+            const double nl1 = fma(a1, r1[q], l1[q]) * p1.y, nr1 = fma(b1, l1[q], r1[q]) * p1.y;
+            l0[q] = j == 0 ? nl0 : nl1;
+            l1[q] = shifted<0x101>(nr1, nl0);  // row_shl:1, lane 15 from its own R
+            r0[q] = shifted<0x111>(nl1, nr1);  // row_shr:1, lane 0 from its own L
+            r1[q] = nr0;
+        }
+        s0.next();
+        s1.next();
+    }
+    template <typename T>
+    __device__ __forceinline__ void store(T *__restrict__ Wg, int row, int j) const
+    {
+        typedef T v2 __attribute__((ext_vector_type(2)));
+#pragma unroll
+        for (int q = 0; q < RG; ++q) {
+            *reinterpret_cast<v2 *>(Wg + (row + q) * kB2 + 2 * j) = v2{(T)l0[q], (T)l1[q]};
+            *reinterpret_cast<v2 *>(Wg + (row + q) * kB2 + kB2 - 2 - 2 * j) = v2{(T)r1[q], (T)r0[q]};
+        }
+    }
+};
+
+// What the rotation wave counts, per lane (slot).
+struct CircleCount {
+    unsigned nrot, nskip, rank;
+    double maxt;
+    unsigned long long tmask;
+};
+
+template <int MODE, bool kWTurn>
+__device__ __forceinline__ CircleCount circle_rotation_wave(const SlotRotator &rotator, int p, int2 IJ, CircleLds &L,
+                                                            int nsweeps, CircleW<4> &w)
+{
+    const int lane = threadIdx.x & 63, s = lane & 31, j = lane & 15;
+    const bool own = lane < kB;
+    CircleSlot sl;
+    sl.start(s);
+    CircleCount n{0u, 0u, 0u, 0.0, 0ull};
+    int x, y;
+    bool trig;
+    auto look = [&] {
+        x = min(sl.l, sl.r);
+        y = max(sl.l, sl.r);
+        trig = MODE == kTrig || (local_pos(x, IJ.x, IJ.y) < p) == (local_pos(y, IJ.x, IJ.y) < p);
+    };
+    look();
+    __builtin_amdgcn_s_setprio(2);
+    for (int sw = 0; sw < nsweeps; ++sw) {
+        unsigned any = 0;
+#pragma unroll 1
+        for (int u = 0; u < kB2 - 1; ++u) {
+            double t, c;
+            bool skip, bad;
+            rotator.template operator()<MODE>(L.A[x * (kLdC + 1)], L.A[y * (kLdC + 1)], L.A[x * kLdC + y], trig, t, c, skip,
+                                              bad);
+            const bool rot = !skip && !bad;
+            const double tr = rot ? t : 0.0;
+            const unsigned mask = (unsigned)__ballot(rot);  // lanes 0 .. b - 1
+            if (own) L.prm[s] = make_double2(tr, rot ? (trig ? -c : c) : 1.0);
+            if (lane == 0) L.rotated = mask;
+            role_barrier();
+            any |= mask;
+            n.nrot += rot ? 1u : 0u;
+            n.nskip += skip ? 1u : 0u;
+            if (MODE != kTrig) n.rank |= !skip && bad ? 1u : 0u;
+            n.maxt = fmax(n.maxt, fabs(tr));
+            n.tmask |= rot ? (1ull << x) | (1ull << y) : 0ull;
+            sl.next();
+            look();
+            if (kWTurn) w.step(L.prm, j);
+            role_barrier();
+        }
+        if (!any) break;  // a sweep without rotations: the block is diagonal
+    }
+    __builtin_amdgcn_s_setprio(0);
+    return n;
+}
+
+// NB blocks of A_P per thread (items tid0 + nthreads q), and W when kWTurn.
+template <int NB, bool kWTurn>
+__device__ __forceinline__ void circle_block_wave(CircleLds &L, int nsweeps, int tid0, int nthreads, CircleW<4> &w)
+{
+    const int j = threadIdx.x & 15;
+    constexpr int kItems = kB * (kB + 1) / 2;
+    int sl[NB], sh[NB];
+    CircleSlot lo[NB], hi[NB];
+    bool have[NB];
+#pragma unroll
+    for (int q = 0; q < NB; ++q) {
+        const int item = tid0 + nthreads * q;
+        have[q] = item < kItems;
+        const int s = item & 31, s2 = (s + (item >> 5)) & 31;
+        sl[q] = min(s, s2);
+        sh[q] = max(s, s2);
+        lo[q].start(sl[q]);
+        hi[q].start(sh[q]);
+    }
+    for (int sw = 0; sw < nsweeps; ++sw) {
+        unsigned any = 0;
+#pragma unroll 1
+        for (int u = 0; u < kB2 - 1; ++u) {
+            double e[NB][4];
+            int at[NB][4];
+#pragma unroll
+            for (int q = 0; q < NB; ++q) {
+                const int xl = min(lo[q].l, lo[q].r), yl = max(lo[q].l, lo[q].r);
+                const int xh = min(hi[q].l, hi[q].r), yh = max(hi[q].l, hi[q].r);
+                at[q][0] = sym_at(xl, xh);
+                at[q][1] = sym_at(xl, yh);
+                at[q][2] = sym_at(yl, xh);
+                at[q][3] = sym_at(yl, yh);
+                if (have[q])
+#pragma unroll
+                    for (int v = 0; v < 4; ++v) e[q][v] = L.A[at[q][v]];
+                lo[q].next();
+                hi[q].next();
+            }
+            role_barrier();
+            const unsigned mask = L.rotated;
+            any |= mask;
+            // blocks neither of whose slots rotates stay as they are
+#pragma unroll
+            for (int q = 0; q < NB; ++q) {
+                if (!have[q] || !(((mask >> sl[q]) | (mask >> sh[q])) & 1u)) continue;
+                const Rot3<double> pa = unpack_rot<double>(L.prm[sh[q]]), pq = unpack_rot<double>(L.prm[sl[q]]);
+                rotate_block(e[q][0], e[q][1], e[q][2], e[q][3], pa, pq);
+                if (sl[q] == sh[q]) e[q][1] = e[q][2] = 0.0;
+#pragma unroll
+                for (int v = 0; v < 4; ++v) L.A[at[q][v]] = e[q][v];
+            }
+            if (kWTurn) w.step(L.prm, j);
+            role_barrier();
+        }
+        if (!__builtin_amdgcn_readfirstlane(any)) break;
+    }
+}
+
+// NT threads.  Every thread must call it (barriers).
+template <typename T, int NT>
+__device__ __forceinline__ void inner_circle_pair(const BlockArgsT<T> &a, int k, CircleLds &L)
+{
+    static_assert(NT == 256 || NT == 512 || NT == 1024, "thread count");
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int2 IJ = outer_pair(a, k);
+    // the sweep's counters so far, read ahead of their update at the end
+    SweepSoFar so_far;
+    if (tid == 0) so_far.read(a, k);
+    stage_gram<T, NT, kLdC>(a, k, L.A);
+    __syncthreads();
+    const int nsweeps = a.inner_sweeps > 0 ? a.inner_sweeps : 1;
+    // W, four rows a lane: every wave of 256 threads, else the last four
+    constexpr int kWWave = NT / 64 - 4;
+    const bool wturn = wave >= kWWave;
+    const int wrow = 4 * ((wave - kWWave) * 4 + (lane >> 4)), j = lane & 15;
+    CircleW<4> w;
+    w.init(wrow, j);
+    // the blocks of A_P: 528 over the waves after the first
+    constexpr int kA = NT - 64, kNB = (kB * (kB + 1) / 2 + kA - 1) / kA;
+    if (wave == 0) {
+        const SlotRotator rotator(a.tol);
+        const bool same = (IJ.x * kB + kB <= a.p && IJ.y * kB + kB <= a.p) || (IJ.x * kB >= a.p && IJ.y * kB >= a.p);
+        const double tthresh = a.tthresh;
+        CircleCount o = same ? circle_rotation_wave<kTrig, kWWave == 0>(rotator, a.p, IJ, L, nsweeps, w)
+                             : circle_rotation_wave<kBothKinds, kWWave == 0>(rotator, a.p, IJ, L, nsweeps, w);
+        unsigned mlo = (unsigned)o.tmask, mhi = (unsigned)(o.tmask >> 32);
+#pragma unroll
+        for (int m = 16; m >= 1; m >>= 1) {
+            o.rank |= __shfl_xor(o.rank, m, 64);
+            o.nrot += __shfl_xor(o.nrot, m, 64);
+            o.nskip += __shfl_xor(o.nskip, m, 64);
+            o.maxt = fmax(o.maxt, __shfl_xor(o.maxt, m, 64));
+            mlo |= __shfl_xor(mlo, m, 64);
+            mhi |= __shfl_xor(mhi, m, 64);
+        }
+        // eq. (4.2) codes of the applied rotations, OR-ed
+        if (tid == 0)
+            so_far.write(a, k, o.nrot > 0 ? (o.maxt > tthresh ? 3 : 1) : 0, (int)o.rank, o.maxt, o.nrot, o.nskip,
+                         ((unsigned long long)mhi << 32) | mlo);
+    } else if (wturn) {
+        circle_block_wave<kNB, true>(L, nsweeps, tid - 64, kA, w);
+    } else {
+        circle_block_wave<kNB, false>(L, nsweeps, tid - 64, kA, w);
+    }
+    if (wturn) w.store(a.W + (size_t)k * (kB2 * kB2), wrow, j);
+}
 
 // ---------------------------------------------------------------------------
 // Update: [G_P | V_P] <- [G_P | V_P] W.
