@@ -199,12 +199,12 @@ __device__ __forceinline__ void gram_pair(const BlockArgsT<T> &a, int k, int spl
     }
 }
 
-// A_P = sum of the partial Grams in split order into buf (row stride LD), by
-// NT threads.  Only the 10 upper-triangular 16 x 16 tiles hold data: work item
-// i sums the entries (x, y), (x, y + 1) of tile i / 128 of every split with
+// A_P = sum of the partial Grams in split order, put(x, y, A_P(x, y)), by NT
+// threads.  Only the 10 upper-triangular 16 x 16 tiles hold data: work item i
+// sums the entries (x, y), (x, y + 1) of tile i / 128 of every split with
 // vector loads.
-template <typename T, int NT, int LD>
-__device__ __forceinline__ void stage_gram(const BlockArgsT<T> &a, int k, double *buf)
+template <typename T, int NT, typename Put>
+__device__ __forceinline__ void stage_gram(const BlockArgsT<T> &a, int k, Put put)
 {
     constexpr int kItems = kGramTiles * 128;
     typedef T v2 __attribute__((ext_vector_type(2)));
@@ -232,8 +232,8 @@ __device__ __forceinline__ void stage_gram(const BlockArgsT<T> &a, int k, double
                         g1 = first ? (double)v[c][1] : g1 + (double)v[c][1];
                     }
             }
-            buf[x * LD + y] = g0;
-            buf[x * LD + y + 1] = g1;
+            put(x, y, g0);
+            put(x, y + 1, g1);
         }
     }
 }
@@ -739,7 +739,7 @@ __device__ __forceinline__ void inner_cross_pair(const BlockArgsT<T> &a, int k, 
     // the sweep's counters so far, read ahead of their update at the end
     SweepSoFar so_far;
     if (tid == 0) so_far.read(a, k);
-    stage_gram<T, NT, kLd>(a, k, buf);
+    stage_gram<T, NT>(a, k, [&](int x, int y, double v) { buf[x * kLd + y] = v; });
     if (tid == 0) L.live = 0;
     __syncthreads();
     {
@@ -803,37 +803,58 @@ __device__ __forceinline__ void inner_cross_pair(const BlockArgsT<T> &a, int k, 
 // repeated until a sweep applies no rotation (at most a.inner_sweeps) in every
 // outer step of the full-block method.
 //
-// A_P sits in LDS, entry (i, j) at (min, max).  At an inner step every local
-// index belongs to exactly one slot, so the 2 x 2 block of the slot pair
-// {sl <= sh} is read and written by one thread alone (columns of slot sh
-// first, then rows of slot sl); the first wave evaluates the b rotations.  W
-// is held by rows in registers: lane j of a 16-lane row has the columns of
-// slots 2 j and 2 j + 1, and the circle's shift (L_k <- L_{k+1}, R_k <-
-// R_{k-1}, the ends crossing over) is a lane move within the row.  Two barriers
-// per inner step: rotations out, blocks written; the blocks' entries are
-// fetched while the rotations are evaluated.
+// At an inner step every local index sits in one slot s, on its left or its
+// right (L_s, R_s); the slots' indices then move on by one place of the circle
+// (L_0 stays, L_1 -> R_0, L_k -> L_{k-1}, R_k -> R_{k+1}, R_{b-1} -> L_{b-1}).
+// A_P sits in LDS by places, one 2 x 2 block (L, R) x (L, R) per slot pair
+// {sl <= sh}: one thread reads the block, turns it (columns of slot sh first,
+// then rows of slot sl) and writes each entry to the place where the next step
+// reads it.  The moves are the same in every step, so all addresses are
+// settled before the loop, and the entries of consecutive blocks are
+// consecutive.  The first wave evaluates the b rotations from the diagonal
+// blocks, oriented to (L, R).  W is held by rows in registers: lane j of a
+// 16-lane row has the columns of slots 2 j and 2 j + 1, and the same moves are
+// lane moves within the row.  Two barriers per inner step: rotations out (the
+// blocks have been read by then), blocks written.
 //
-// What bounds it: the block waves' address, read and write instructions and the
-// two barriers; the first wave (pivots from LDS 0.27, rotation 0.34 thousand
-// cycles) no longer does.  A launch over 64 pairs (FP64, one sweep): 72 us at
-// 1024 threads, 83 at 512, 113 at 256; with every block held twice, W in LDS
-// and 32-byte parameters it was bound by LDS traffic (107 us at 1024).
+// What bounds it: the rotation wave's chain (read, rotate, write: about 650
+// cycles of 1500) and then the block waves' one (parameters, rotation, writes),
+// a barrier between them; with four pairs per compute unit the vector
+// instructions.  Launches over 64 pairs (FP64, one sweep): 45 us at 1024
+// threads, 50 at 512, 70 at 256; 1024 pairs at 256 threads: 120 us.  With A_P
+// by indices (addresses computed anew in every step) 72, 83, 113 and 241 us;
+// with every block held twice, W in LDS and 32-byte parameters 107 us at 1024.
 // ---------------------------------------------------------------------------
-// Row stride of A_P: from slot to slot the indices of an entry move by (1, 1)
-// or (1, -1), so the addresses by kLdC + 1 or kLdC - 1 doubles: both odd, no
-// bank conflicts (at a stride of 65 every (1, -1) access of a wave met one
-// bank).
-constexpr int kLdC = kB2 + 2;
+constexpr int kCircleBlocks = kB * (kB + 1) / 2;
 struct CircleLds {
-    double A[kB2 * kLdC];
-    double2 prm[kB];   // (t, c) of each slot, as in the cross solve
+    // entries LL, LR, RL, RR of the blocks (a diagonal block's LR stands for its RL too)
+    double X[4][kCircleBlocks];
+    double2 prm[kB];   // (t, c) of each slot, as in the cross solve, L the first index
     unsigned rotated;  // slots that rotate in this step
 };
 
-__device__ __forceinline__ int sym_at(int i, int j) { return min(i, j) * kLdC + max(i, j); }
+// A place is 2 s + side (0: L_s, 1: R_s).  Address of entry (u, v) of A_P, u
+// and v places of the slots sl <= sh (block item (sh - sl) mod b, the shorter
+// way round, times b, plus the slot it starts from).
+__device__ __forceinline__ int circle_at(int u, int v)
+{
+    const int su = u >> 1, sv = v >> 1, lo = min(su, sv), hi = max(su, sv), d = hi - lo;
+    const int item = d <= kB / 2 ? d * kB + lo : (kB - d) * kB + hi;
+    const int first = su <= sv ? u : v, second = su <= sv ? v : u;
+    const int entry = d == 0 ? (u & 1) + (v & 1) + ((u & v) & 1) : 2 * (first & 1) + (second & 1);
+    return entry * kCircleBlocks + item;
+}
+// Where the index at place u moves.
+__device__ __forceinline__ int circle_next(int u)
+{
+    if (u & 1) return u == 2 * kB - 1 ? u - 1 : u + 2;
+    return u == 0 ? 0 : (u == 2 ? 1 : u - 2);
+}
+// The place of local index i at the first step.
+__device__ __forceinline__ int circle_place(int i) { return i < kB ? 2 * i : 2 * (kB2 - 1 - i) + 1; }
 
-// The two indices of slot s at inner step u, L first (roundrobin_pair without
-// its ordering), and their next values.
+// The two indices of slot s at inner step u (roundrobin_pair without its
+// ordering), and their next values.
 struct CircleSlot {
     int l, r;
     __device__ __forceinline__ void start(int s)
@@ -853,17 +874,14 @@ template <int RG>
 struct CircleW {
     typedef double vec __attribute__((ext_vector_type(RG)));
     vec l0, r0, l1, r1;
-    CircleSlot s0, s1;
     __device__ __forceinline__ void init(int row, int j)
     {
-        s0.start(2 * j);
-        s1.start(2 * j + 1);
 #pragma unroll
         for (int q = 0; q < RG; ++q) {
-            l0[q] = row + q == s0.l ? 1.0 : 0.0;
-            r0[q] = row + q == s0.r ? 1.0 : 0.0;
-            l1[q] = row + q == s1.l ? 1.0 : 0.0;
-            r1[q] = row + q == s1.r ? 1.0 : 0.0;
+            l0[q] = row + q == 2 * j ? 1.0 : 0.0;
+            r0[q] = row + q == kB2 - 1 - 2 * j ? 1.0 : 0.0;
+            l1[q] = row + q == 2 * j + 1 ? 1.0 : 0.0;
+            r1[q] = row + q == kB2 - 2 - 2 * j ? 1.0 : 0.0;
         }
     }
     template <int kCtrl>
@@ -876,20 +894,15 @@ struct CircleW {
     __device__ __forceinline__ void step(const double2 *prm, int j)
     {
         const Rot3<double> p0 = unpack_rot<double>(prm[2 * j]), p1 = unpack_rot<double>(prm[2 * j + 1]);
-        // the smaller index of a pair takes h, the other t
-        const double a0 = s0.l < s0.r ? p0.z : p0.x, b0 = s0.l < s0.r ? p0.x : p0.z;
-        const double a1 = s1.l < s1.r ? p1.z : p1.x, b1 = s1.l < s1.r ? p1.x : p1.z;
 #pragma unroll
         for (int q = 0; q < RG; ++q) {
-            const double nl0 = fma(a0, r0[q], l0[q]) * p0.y, nr0 = fma(b0, l0[q], r0[q]) * p0.y;
-            const double nl1 = fma(a1, r1[q], l1[q]) * p1.y, nr1 = fma(b1, l1[q], r1[q]) * p1.y;
+            const double nl0 = fma(p0.z, r0[q], l0[q]) * p0.y, nr0 = fma(p0.x, l0[q], r0[q]) * p0.y;
+            const double nl1 = fma(p1.z, r1[q], l1[q]) * p1.y, nr1 = fma(p1.x, l1[q], r1[q]) * p1.y;
             l0[q] = j == 0 ? nl0 : nl1;
             l1[q] = shifted<0x101>(nr1, nl0);  // row_shl:1, lane 15 from its own R
             r0[q] = shifted<0x111>(nl1, nr1);  // row_shr:1, lane 0 from its own L
             r1[q] = nr0;
         }
-        s0.next();
-        s1.next();
     }
     template <typename T>
     __device__ __forceinline__ void store(T *__restrict__ Wg, int row, int j) const
@@ -919,27 +932,26 @@ __device__ __forceinline__ CircleCount circle_rotation_wave(const SlotRotator &r
     CircleSlot sl;
     sl.start(s);
     CircleCount n{0u, 0u, 0u, 0.0, 0ull};
-    int x, y;
-    bool trig;
-    auto look = [&] {
-        x = min(sl.l, sl.r);
-        y = max(sl.l, sl.r);
-        trig = MODE == kTrig || (local_pos(x, IJ.x, IJ.y) < p) == (local_pos(y, IJ.x, IJ.y) < p);
+    // ascending pair: L_s < R_s; else the smaller index is R_s
+    auto is_trig = [&] {
+        return MODE == kTrig || (local_pos(sl.l, IJ.x, IJ.y) < p) == (local_pos(sl.r, IJ.x, IJ.y) < p);
     };
-    look();
+    bool trig = is_trig();
     __builtin_amdgcn_s_setprio(2);
     for (int sw = 0; sw < nsweeps; ++sw) {
         unsigned any = 0;
 #pragma unroll 1
         for (int u = 0; u < kB2 - 1; ++u) {
+            const double ll = L.X[0][s], lr = L.X[1][s], rr = L.X[3][s];
+            const bool asc = sl.l < sl.r;
             double t, c;
             bool skip, bad;
-            rotator.template operator()<MODE>(L.A[x * (kLdC + 1)], L.A[y * (kLdC + 1)], L.A[x * kLdC + y], trig, t, c, skip,
-                                              bad);
+            rotator.template operator()<MODE>(asc ? ll : rr, asc ? rr : ll, lr, trig, t, c, skip, bad);
             const bool rot = !skip && !bad;
             const double tr = rot ? t : 0.0;
             const unsigned mask = (unsigned)__ballot(rot);  // lanes 0 .. b - 1
-            if (own) L.prm[s] = make_double2(tr, rot ? (trig ? -c : c) : 1.0);
+            // the smaller index takes h = -+t, the other t: oriented to (L, R)
+            if (own) L.prm[s] = make_double2(trig && !asc ? -tr : tr, rot ? (trig ? -c : c) : 1.0);
             if (lane == 0) L.rotated = mask;
             role_barrier();
             any |= mask;
@@ -947,9 +959,9 @@ __device__ __forceinline__ CircleCount circle_rotation_wave(const SlotRotator &r
             n.nskip += skip ? 1u : 0u;
             if (MODE != kTrig) n.rank |= !skip && bad ? 1u : 0u;
             n.maxt = fmax(n.maxt, fabs(tr));
-            n.tmask |= rot ? (1ull << x) | (1ull << y) : 0ull;
+            n.tmask |= rot ? (1ull << sl.l) | (1ull << sl.r) : 0ull;
             sl.next();
-            look();
+            trig = is_trig();
             if (kWTurn) w.step(L.prm, j);
             role_barrier();
         }
@@ -964,52 +976,41 @@ template <int NB, bool kWTurn>
 __device__ __forceinline__ void circle_block_wave(CircleLds &L, int nsweeps, int tid0, int nthreads, CircleW<4> &w)
 {
     const int j = threadIdx.x & 15;
-    constexpr int kItems = kB * (kB + 1) / 2;
-    int sl[NB], sh[NB];
-    CircleSlot lo[NB], hi[NB];
+    double *const X = &L.X[0][0];
+    int item[NB], to[NB][4];
+    const double2 *pa[NB], *pq[NB];
     bool have[NB];
 #pragma unroll
     for (int q = 0; q < NB; ++q) {
-        const int item = tid0 + nthreads * q;
-        have[q] = item < kItems;
-        const int s = item & 31, s2 = (s + (item >> 5)) & 31;
-        sl[q] = min(s, s2);
-        sh[q] = max(s, s2);
-        lo[q].start(sl[q]);
-        hi[q].start(sh[q]);
+        have[q] = tid0 + nthreads * q < kCircleBlocks;
+        item[q] = have[q] ? tid0 + nthreads * q : 0;
+        const int s = item[q] & 31, s2 = (s + (item[q] >> 5)) & 31, sl = min(s, s2), sh = max(s, s2);
+        pa[q] = &L.prm[sh];
+        pq[q] = &L.prm[sl];
+#pragma unroll
+        for (int v = 0; v < 4; ++v) to[q][v] = circle_at(circle_next(2 * sl + (v >> 1)), circle_next(2 * sh + (v & 1)));
     }
+    const bool diag = item[0] < kB;  // only a first block can be a diagonal one
     for (int sw = 0; sw < nsweeps; ++sw) {
         unsigned any = 0;
 #pragma unroll 1
         for (int u = 0; u < kB2 - 1; ++u) {
             double e[NB][4];
-            int at[NB][4];
 #pragma unroll
-            for (int q = 0; q < NB; ++q) {
-                const int xl = min(lo[q].l, lo[q].r), yl = max(lo[q].l, lo[q].r);
-                const int xh = min(hi[q].l, hi[q].r), yh = max(hi[q].l, hi[q].r);
-                at[q][0] = sym_at(xl, xh);
-                at[q][1] = sym_at(xl, yh);
-                at[q][2] = sym_at(yl, xh);
-                at[q][3] = sym_at(yl, yh);
-                if (have[q])
+            for (int q = 0; q < NB; ++q)
 #pragma unroll
-                    for (int v = 0; v < 4; ++v) e[q][v] = L.A[at[q][v]];
-                lo[q].next();
-                hi[q].next();
-            }
+                for (int v = 0; v < 4; ++v) e[q][v] = L.X[v][item[q]];
             role_barrier();
             const unsigned mask = L.rotated;
             any |= mask;
-            // blocks neither of whose slots rotates stay as they are
 #pragma unroll
             for (int q = 0; q < NB; ++q) {
-                if (!have[q] || !(((mask >> sl[q]) | (mask >> sh[q])) & 1u)) continue;
-                const Rot3<double> pa = unpack_rot<double>(L.prm[sh[q]]), pq = unpack_rot<double>(L.prm[sl[q]]);
-                rotate_block(e[q][0], e[q][1], e[q][2], e[q][3], pa, pq);
-                if (sl[q] == sh[q]) e[q][1] = e[q][2] = 0.0;
+                if (q == 0) e[0][2] = diag ? e[0][1] : e[0][2];
+                rotate_block(e[q][0], e[q][1], e[q][2], e[q][3], unpack_rot<double>(*pa[q]), unpack_rot<double>(*pq[q]));
+                if (q == 0 && diag) e[0][1] = e[0][2] = (mask >> item[0]) & 1u ? 0.0 : e[0][1];
+                if (have[q])
 #pragma unroll
-                for (int v = 0; v < 4; ++v) L.A[at[q][v]] = e[q][v];
+                    for (int v = 0; v < 4; ++v) X[to[q][v]] = e[q][v];
             }
             if (kWTurn) w.step(L.prm, j);
             role_barrier();
@@ -1029,7 +1030,9 @@ __device__ __forceinline__ void inner_circle_pair(const BlockArgsT<T> &a, int k,
     // the sweep's counters so far, read ahead of their update at the end
     SweepSoFar so_far;
     if (tid == 0) so_far.read(a, k);
-    stage_gram<T, NT, kLdC>(a, k, L.A);
+    stage_gram<T, NT>(a, k, [&](int x, int y, double v) {
+        if (x <= y) (&L.X[0][0])[circle_at(circle_place(x), circle_place(y))] = v;
+    });
     __syncthreads();
     const int nsweeps = a.inner_sweeps > 0 ? a.inner_sweeps : 1;
     // W, four rows a lane: every wave of 256 threads, else the last four
@@ -1039,7 +1042,7 @@ __device__ __forceinline__ void inner_circle_pair(const BlockArgsT<T> &a, int k,
     CircleW<4> w;
     w.init(wrow, j);
     // the blocks of A_P: 528 over the waves after the first
-    constexpr int kA = NT - 64, kNB = (kB * (kB + 1) / 2 + kA - 1) / kA;
+    constexpr int kA = NT - 64, kNB = (kCircleBlocks + kA - 1) / kA;
     if (wave == 0) {
         const SlotRotator rotator(a.tol);
         const bool same = (IJ.x * kB + kB <= a.p && IJ.y * kB + kB <= a.p) || (IJ.x * kB >= a.p && IJ.y * kB >= a.p);
