@@ -279,14 +279,14 @@ hsvd_status hsvd_autotune(hsvd_ctx *ctx, int n, int *best_algo, int *best_wg);
 
 /* Autotuner of the batched solver.  Block-oriented problems with n <= 256 run
  * in one persistent launch in which each workgroup solves whole problems;
- * its width (256, 512 or 1024 threads per problem: the inner rotations and the
- * column updates of a block pair spread over all of them) is a speed-only
- * choice.  This call times the three widths on a sample of at most 4096 of the
+ * its width (256, 512 or 1024 threads per problem: one, two or four of its
+ * block pairs at a time) is a speed-only choice.  This call times the three widths on a sample of at most 4096 of the
  * given problems (every k-th, the ones with n <= 256; seeded synthetic entries,
  * uniform in [-1, 1) from a counter-based hash; V accumulated) and keeps the
  * fastest for the bucket of the sample's largest order ((0, 64], (64, 128],
  * (128, 192], (192, 256]) in the context; later hsvd_solve_batched calls whose
- * persistent problems fall in that bucket use it (default before tuning: 256).
+ * persistent problems fall in that bucket use it (before tuning the width follows
+ * from the number of problems and the largest order).
  * The results of a batched solve do not depend on the width (bit-identical).
  * Then, with the chosen width, it times the two sweep schedules (one persistent
  * launch, launches grouped by order; batch_mode 0 and 1) in FP64 and in mixed

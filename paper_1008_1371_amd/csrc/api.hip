@@ -1510,7 +1510,7 @@ extern "C" hsvd_status hsvd_autotune_batched(hsvd_ctx *ctx, int batch, const int
     const int bucket = std::min(3, (nmax - 1) / 64);
     const int saved = ctx->persist_threads[bucket];
     const int cands[3] = {256, 512, 1024};
-    int best = kPersistDefaultThreads;
+    int best = cands[0];
     float best_ms = 1e30f;
     for (int ci = 0; ci < 3; ++ci) {
         ctx->persist_threads[bucket] = cands[ci];
@@ -1742,7 +1742,8 @@ static hsvd_status batch_persistent(hsvd_ctx *ctx, hipStream_t st, const std::ve
     int nmax = 0;
     for (int k : ids) nmax = std::max(nmax, n[k]);
     const int bucket = std::min(3, (nmax - 1) / 64);
-    const int threads = ctx->persist_threads[bucket] ? ctx->persist_threads[bucket] : kPersistDefaultThreads;
+    const int threads =
+        ctx->persist_threads[bucket] ? ctx->persist_threads[bucket] : persist_default_threads(K, nmax, cus);
     const int per_cu = persist_blocks_per_cu(threads);
     if (per_cu < 1 || cus < 1) return HSVD_E_DEVICE;
     const int wgs = std::min(K, per_cu * cus);

@@ -12,15 +12,23 @@
 // No host round trip and no other launch happens between the first problem
 // and the last.
 //
-// Several workgroups share a compute unit, so while one runs the
-// latency-bound inner solve of its block pair the others keep the matrix
-// cores busy with their Gram and update products.
+// A workgroup holds one, two or four groups of 256 threads, each with a block
+// pair of the outer step; whatever the width, 16 waves share a compute unit:
+// four problems side by side, whose phases interleave (while one runs the
+// latency-bound inner solve the others keep the matrix cores busy), or one
+// problem with its (up to four) pairs at a time, which then takes a third of
+// the time.  What bounds it, at n = 256, FP64, 88 outer steps: one problem of
+// 1024 threads per compute unit spends 3.5 ms on Grams, 4.4 on inner solves
+// and 6.3 on updates (16.1 in all), of which 7.0 are the matrix cores' time;
+// four problems of 256 threads take 12.7 ms per problem.  The earlier form --
+// all threads on one pair, the pairs one after the other, two workgroups of
+// 256 threads per compute unit -- took 18 ms per problem and compute unit.
 //
 // The building blocks are those of the per-launch kernels (block_device.h),
-// called with the same arguments and the same thread counts as the grouped
-// batched path (one row split, 256-thread inner solves and updates), and the
-// set-up, norm, sort and stop-rule steps repeat its arithmetic in the same
-// order: for the same problems the results are bit-identical to it.
+// called with the same arguments and 256 threads per block pair (one row
+// split), and the set-up, norm, sort and stop-rule steps repeat the grouped
+// batched path's arithmetic in the same order: for the same problems the
+// results are bit-identical to it.
 //
 // Mixed precision runs the whole mixed solve of a problem in its workgroup
 // too: FP32 block sweeps on FP32 copies (the same building blocks with
@@ -42,24 +50,29 @@ namespace {
 
 constexpr int kPMaxR = kPersistMaxOrder;       // largest bordered order
 constexpr int kPMaxPairs = kPMaxR / kB2;        // block pairs per step at most
-// The update re-reads W from LDS for every 16-row strip (the register-resident
-// W of the per-launch FP64 update would take the registers that let two
-// workgroups share a compute unit); the arithmetic is the same.
-constexpr int kPUpdLd = kB2 + 8;                // LDS row stride of W in the update
+constexpr int kPUpdLd = UpdCfg<double>::ld, kPUpdLd32 = UpdCfg<float>::ld;  // LDS row strides of W in the update
+constexpr int kPTile = 64;                      // tile of the re-orthogonalisation's products
 
-// LDS of one workgroup: the phases of a problem run one after the other, so
-// they share one area.
-union PersistLds {
+// LDS of one group of 256 threads: the phases of a block pair run one after
+// the other, so they share one area.
+union GroupLds {
     CircleLds circle;
     CrossLds<double> cross;
     CrossLds<float> cross32;
-    gemm::GemmLds gemm;
+    gemm::GemmLds<kPTile> gemm;
     double red[kGramRed];
     struct {
         double Wl[kB2 * kPUpdLd];
         int cols[kB2];
         int tl[kB2];
     } upd;
+};
+
+// LDS of a workgroup of GR groups.
+template <int GR>
+union PersistLds {
+    GroupLds group[GR];
+    double red[4 * GR];
     struct {
         long long key[kPMaxR];
         double dv[kPMaxR];
@@ -71,9 +84,19 @@ union PersistLds {
 // The workgroup's LDS and the block pair arguments of the problem it works
 // on.  The phases below are separate (not inlined) functions that reach both
 // by name: compiled as one function, the whole solve kept so many values live
-// at once that it no longer fitted the registers of two workgroups per
-// compute unit; as calls, each phase is allocated on its own.
-__shared__ PersistLds g_lds;
+// at once that it no longer fitted the registers of four waves per SIMD; as
+// calls, each phase is allocated on its own.
+__shared__ PersistLds<1> g_lds1;
+__shared__ PersistLds<2> g_lds2;
+__shared__ PersistLds<4> g_lds4;
+template <int GR>
+__device__ __forceinline__ PersistLds<GR> &lds()
+{
+    if constexpr (GR == 1) return g_lds1;
+    else if constexpr (GR == 2) return g_lds2;
+    else return g_lds4;
+}
+__shared__ int g_live;  // some cross pair of the workgroup's block pairs fails the skip test
 // raw storage: the argument struct has default member initialisers
 __shared__ __align__(16) unsigned char g_args[sizeof(BlockArgsT<double>)];
 
@@ -84,71 +107,127 @@ __device__ __forceinline__ BlockArgsT<double> &pargs() { return *reinterpret_cas
 __device__ __forceinline__ BlockArgsT<float> &pargs32() { return *reinterpret_cast<BlockArgsT<float> *>(g_args32); }
 __device__ __forceinline__ GemmArgs &pgemm() { return *reinterpret_cast<GemmArgs *>(g_gemm); }
 
-// NT threads per workgroup (256, 512 or 1024): the inner solves and the
-// update spread over all of them, the Gram runs on the first 256.
-__device__ __noinline__ void phase_gram(int q) { gram_pair<double>(pargs(), q, 0, g_lds.red); }
-template <int NT>
-__device__ __noinline__ void phase_circle(int q)
+// A workgroup is GR groups of 256 threads (GR 1, 2 or 4), each with one block
+// pair of the outer step at a time: the inner solve of a pair is a serial
+// chain that a few waves fill, so further threads work on further pairs.  The
+// groups pass the same workgroup barriers; one without a pair only those.
+__device__ __forceinline__ int group_index() { return __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 8); }
+// The thread's index in its group.  Group g starts its waves g places further
+// on, so that the rotation waves of the groups (the first of each) sit on
+// different SIMDs.
+__device__ __forceinline__ int group_tid() { return ((int)threadIdx.x - 64 * group_index()) & 255; }
+template <int N>
+__device__ __forceinline__ void idle_barriers()
 {
-    inner_circle_pair<double, NT>(pargs(), q, g_lds.circle);
-}
-template <int NT>
-__device__ __noinline__ void phase_cross(int q)
-{
-    inner_cross_pair<double, NT>(pargs(), q, g_lds.cross);
-}
-// M: 0 = G, 1 = V
-template <int NT>
-__device__ __noinline__ void phase_update(int q, int M, unsigned long long mask)
-{
-    const BlockArgsT<double> &a = pargs();
-    update_rows<double, NT, true, true, kPUpdLd>(a, q, M ? a.V : a.G, 0, a.ldg / 16, mask, g_lds.upd.Wl,
-                                               g_lds.upd.cols, g_lds.upd.tl);
+#pragma unroll
+    for (int u = 0; u < N; ++u) __syncthreads();
 }
 
-// The FP32 phases of a mixed solve: the same building blocks on the FP32
-// working copies (the rotations still computed in FP64); the FP32 update
-// re-reads W from LDS at the FP32 row stride of the per-launch update.
-constexpr int kPUpdLd32 = kB2 + 16;
-__device__ __noinline__ void phase_gram32(int q)
+template <typename T>
+__device__ __forceinline__ BlockArgsT<T> &args_of();
+template <>
+__device__ __forceinline__ BlockArgsT<double> &args_of<double>()
 {
-    gram_pair<float>(pargs32(), q, 0, reinterpret_cast<float *>(g_lds.red));
+    return pargs();
 }
-template <int NT>
-__device__ __noinline__ void phase_circle32(int q)
+template <>
+__device__ __forceinline__ BlockArgsT<float> &args_of<float>()
 {
-    inner_circle_pair<float, NT>(pargs32(), q, g_lds.circle);
+    return pargs32();
 }
-template <int NT>
-__device__ __noinline__ void phase_cross32(int q)
+template <typename T>
+__device__ __forceinline__ CrossLds<T> &cross_of(GroupLds &L)
 {
-    inner_cross_pair<float, NT>(pargs32(), q, g_lds.cross32);
+    if constexpr (sizeof(T) == 8) return L.cross;
+    else return L.cross32;
 }
-template <int NT>
-__device__ __noinline__ void phase_update32(int q, int M, unsigned long long mask)
+
+// The phases of an outer step for block pairs q0 .. q0 + GR - 1 (of `pairs`).
+template <typename T, int GR>
+__device__ __noinline__ void phase_gram(int q0, int pairs)
 {
-    const BlockArgsT<float> &a = pargs32();
-    update_rows<float, NT, true, true, kPUpdLd32>(a, q, M ? a.V : a.G, 0, a.ldg / 16, mask,
-                                                reinterpret_cast<float *>(g_lds.upd.Wl), g_lds.upd.cols,
-                                                g_lds.upd.tl);
+    const int g = group_index(), q = __builtin_amdgcn_readfirstlane(q0) + g;
+    if (q < __builtin_amdgcn_readfirstlane(pairs))
+        gram_pair<T>(args_of<T>(), q, 0, reinterpret_cast<T *>(lds<GR>().group[g].red), group_tid());
+    else
+        idle_barriers<kGramBarriers>();
+}
+template <typename T, int GR>
+__device__ __noinline__ void phase_circle(int q0, int pairs)
+{
+    const int g = group_index(), q = __builtin_amdgcn_readfirstlane(q0) + g;
+    if (q < __builtin_amdgcn_readfirstlane(pairs))
+        inner_circle_pair<T, 256>(args_of<T>(), q, lds<GR>().group[g].circle, group_tid());
+    else
+        inner_circle_idle();
+}
+template <typename T, int GR>
+__device__ __noinline__ void phase_cross(int q0, int pairs)
+{
+    const int g = group_index(), q = __builtin_amdgcn_readfirstlane(q0) + g;
+    if (q < __builtin_amdgcn_readfirstlane(pairs))
+        inner_cross_pair<T, 256>(args_of<T>(), q, cross_of<T>(lds<GR>().group[g]), g_live, group_tid());
+    else
+        inner_cross_idle(g_live);
+}
+template <typename T, int GR>
+__device__ __noinline__ void phase_update(int q0, int pairs)
+{
+    const BlockArgsT<T> &a = args_of<T>();
+    const int g = group_index(), q = __builtin_amdgcn_readfirstlane(q0) + g;
+    const unsigned long long mask = q < __builtin_amdgcn_readfirstlane(pairs) ? a.active[q] : 0ull;
+    if (__builtin_amdgcn_readfirstlane(mask != 0ull)) {
+        GroupLds &L = lds<GR>().group[g];
+        update_rows<T, 256, sizeof(T) == 8 ? kPUpdLd : kPUpdLd32, false>(
+            a, q, a.G, a.V, 0, a.ldg / 16, mask, reinterpret_cast<T *>(L.upd.Wl), L.upd.cols, L.upd.tl, group_tid());
+    } else {
+        idle_barriers<kUpdateBarriers>();
+    }
+}
+
+// One outer step.
+template <typename T, int GR>
+__device__ __forceinline__ void outer_step(int pairs, bool first)
+{
+    for (int q0 = 0; q0 < pairs; q0 += GR) {
+        phase_gram<T, GR>(q0, pairs);
+        __syncthreads();
+        if (first)
+            phase_circle<T, GR>(q0, pairs);
+        else
+            phase_cross<T, GR>(q0, pairs);
+        __syncthreads();
+        phase_update<T, GR>(q0, pairs);
+        __syncthreads();
+    }
 }
 
 // One r x r FP64 product of the re-orthogonalisation, C = op(A) S B
 // (arguments in pgemm(); S = diag(+1 x p, -1 x (r - p)) on the rows of B when
-// SGN), tile by tile (128 x 128, at most 2 x 2 of them) with the grid-wide
-// product kernel's tile code (gemm_device.h) on the first 256 threads: the
-// same arithmetic as the grouped launches' products.  SYM: the tiles on and
-// above the diagonal, each written to both triangles.
-template <bool TA, bool SGN, bool SYM, int NT>
+// SGN), tile by tile with the grid-wide product kernel's tile code
+// (gemm_device.h), GR tiles at a time: the same arithmetic as the grouped
+// launches' products.  SYM: the tiles on and above the diagonal, each written
+// to both triangles.
+template <bool TA, bool SGN, bool SYM, int GR>
 __device__ __noinline__ void phase_gemm()
 {
-    const GemmArgs &g = pgemm();
-    const int tiles = (g.M + gemm::kTM - 1) / gemm::kTM;
-    for (int tn = 0; tn < tiles; ++tn)
-        for (int tm = 0; tm < tiles; ++tm) {
-            if (SYM && tm > tn) continue;
-            gemm::gemm_tile<TA, SGN, SYM, (NT > 256)>(g, 0, 0, 0, tm, tn, g_lds.gemm);
+    const GemmArgs &a = pgemm();
+    const int tiles = __builtin_amdgcn_readfirstlane(a.M) / kPTile, g = group_index();
+    const int total = SYM ? tiles * (tiles + 1) / 2 : tiles * tiles;
+    for (int i0 = 0; i0 < total; i0 += GR) {
+        const int i = i0 + g;
+        if (i < total) {
+            int tm = i % tiles, tn = i / tiles;
+            if (SYM) {
+                tn = 0;
+                for (int left = i; left > tn; ++tn) left -= tn + 1;
+                tm = i - tn * (tn + 1) / 2;
+            }
+            gemm::gemm_tile<TA, SGN, SYM, kPTile>(a, 0, 0, 0, tm, tn, lds<GR>().group[g].gemm, group_tid());
+        } else {
+            for (int u = 0; u <= __builtin_amdgcn_readfirstlane(a.K) / gemm::kTK; ++u) __syncthreads();
         }
+    }
     __syncthreads();
 }
 
@@ -192,23 +271,23 @@ __host__ __device__ inline SlotLayout slot_layout()
     return s;
 }
 
-// d[q] = ||G[:, rho[q]]||^2 for q < r: thread `row` (of the first 256)
+// d[q] = ||G[:, rho[q]]||^2 for q < r: a group per column, its thread `row`
 // squares its entry, the waves add in butterfly order, the four wave sums are
 // added in wave order (the order of the grouped path's norm kernel for
 // ldg <= 256 rows).
-template <int NT, typename T>
+template <int GR, typename T>
 __device__ __forceinline__ void persist_colnorm(const T *G, int ldg, int r, const int *rho, bool init,
-                                                double *d, PersistLds &L)
+                                                double *d, PersistLds<GR> &L)
 {
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    for (int q = 0; q < r; ++q) {
+    const int row = threadIdx.x & 255, lane = row & 63, wave = row >> 6;
+    for (int q = group_index(); q < r; q += GR) {
         const int c = init ? q : rho[q];
-        const double x = tid < ldg ? (double)G[(size_t)c * ldg + tid] : 0.0;  // ldg <= 256
+        const double x = row < ldg ? (double)G[(size_t)c * ldg + row] : 0.0;  // ldg <= 256
         const double s = wave_sum(fma(x, x, 0.0));
-        if (lane == 0 && wave < 4) L.colsum[wave][q] = s;
+        if (lane == 0) L.colsum[wave][q] = s;
     }
     __syncthreads();
-    for (int q = tid; q < r; q += NT) {
+    for (int q = threadIdx.x; q < r; q += 256 * GR) {
         double s = L.colsum[0][q];
 #pragma unroll
         for (int w = 1; w < 4; ++w) s += L.colsum[w][q];
@@ -219,7 +298,8 @@ __device__ __forceinline__ void persist_colnorm(const T *G, int ldg, int r, cons
 
 // Stable sort of positions [0, p) by d decreasing and [p, r) by d increasing,
 // rho carried along (as the grouped path's sort).
-__device__ __forceinline__ void persist_sort(double *d, int *rho, int r, int p, PersistLds &L)
+template <int GR>
+__device__ __forceinline__ void persist_sort(double *d, int *rho, int r, int p, PersistLds<GR> &L)
 {
     const int q = threadIdx.x;
     if (q < r) {
@@ -246,9 +326,10 @@ __device__ __forceinline__ void persist_sort(double *d, int *rho, int r, int p, 
 
 // One problem, by the whole workgroup; A is the LDS copy of its block pair
 // arguments that the phases read.
-template <int NT>
-__device__ void persist_solve(const PersistArgs &pa, int z, char *slot, PersistLds &L, BlockArgsT<double> &A)
+template <int GR>
+__device__ void persist_solve(const PersistArgs &pa, int z, char *slot, PersistLds<GR> &L, BlockArgsT<double> &A)
 {
+    constexpr int NT = 256 * GR;
     const int tid = threadIdx.x;
     const SlotLayout sl = slot_layout();
     const int n = pa.n[z], p = pa.p[z];
@@ -331,7 +412,7 @@ __device__ void persist_solve(const PersistArgs &pa, int z, char *slot, PersistL
     }
     if (tid < r) rho[tid] = tid;
     __syncthreads();
-    persist_colnorm<NT>(G, ldg, r, rho, true, d, L);
+    persist_colnorm<GR>(G, ldg, r, rho, true, d, L);
     // a non-finite entry or a zero column ends the problem at once
     int status = HSVD_OK;
     {
@@ -406,27 +487,12 @@ __device__ void persist_solve(const PersistArgs &pa, int z, char *slot, PersistL
             for (int k = 0; k < steps_per_sweep; ++k) {
                 if (tid == 0) pargs32().step = k;
                 __syncthreads();
-                for (int q = 0; q < pairs; ++q) {
-                    phase_gram32(q);
-                    __syncthreads();
-                    if (k == 0)
-                        phase_circle32<NT>(q);
-                    else
-                        phase_cross32<NT>(q);
-                    __syncthreads();
-                    const unsigned long long mask = a.active[q];
-                    if (mask) {
-                        phase_update32<NT>(q, 0, mask);
-                        __syncthreads();
-                        phase_update32<NT>(q, 1, mask);
-                        __syncthreads();
-                    }
-                }
+                outer_step<float, GR>(pairs, k == 0);
                 if (pa.ordering == HSVD_ORD_MODMOD && tid < pairs) S[tid] = modmod_next(S[tid], nb);
                 __syncthreads();
             }
             ++sweeps32;
-            persist_colnorm<NT>(G32, ldg, r, rho, false, d, L);
+            persist_colnorm<GR>(G32, ldg, r, rho, false, d, L);
             if (pa.sort) persist_sort(d, rho, r, p, L);
             int c = 0;
             unsigned long long rt = 0, sk = 0, ac = 0;
@@ -485,7 +551,7 @@ __device__ void persist_solve(const PersistArgs &pa, int z, char *slot, PersistL
                     pgemm() = g;
                 }
                 __syncthreads();
-                phase_gemm<true, true, true, NT>();
+                phase_gemm<true, true, true, GR>();
                 double mxr = 0.0;
                 for (int e = tid; e < r * ldg; e += NT) {
                     const int c = e / ldg, row = e - c * ldg;
@@ -516,7 +582,7 @@ __device__ void persist_solve(const PersistArgs &pa, int z, char *slot, PersistL
                     pgemm() = g;
                 }
                 __syncthreads();
-                phase_gemm<false, false, false, NT>();
+                phase_gemm<false, false, false, GR>();
                 for (int e = tid; e < r * ldg; e += NT) V[e] = T1[e];
                 __syncthreads();
             }
@@ -535,7 +601,7 @@ __device__ void persist_solve(const PersistArgs &pa, int z, char *slot, PersistL
                 pgemm() = g;
             }
             __syncthreads();
-            phase_gemm<false, false, false, NT>();
+            phase_gemm<false, false, false, GR>();
             for (int e = tid; e < r * ldg; e += NT) G[e] = T1[e];
         } else {
             // FP64 from G: the bordered working copy again, V = I, rho = id
@@ -553,7 +619,7 @@ __device__ void persist_solve(const PersistArgs &pa, int z, char *slot, PersistL
         }
         __syncthreads();
         // the kept diagonal of the FP64 start and the sort, as after a sweep
-        persist_colnorm<NT>(G, ldg, r, rho, false, d, L);
+        persist_colnorm<GR>(G, ldg, r, rho, false, d, L);
         if (pa.sort) persist_sort(d, rho, r, p, L);
     }
     if (status == HSVD_OK) {
@@ -562,29 +628,12 @@ __device__ void persist_solve(const PersistArgs &pa, int z, char *slot, PersistL
             for (int k = 0; k < steps_per_sweep; ++k) {
                 if (tid == 0) A.step = k;
                 __syncthreads();
-                for (int q = 0; q < pairs; ++q) {
-                    phase_gram(q);
-                    __syncthreads();
-                    if (k == 0)
-                        phase_circle<NT>(q);
-                    else
-                        phase_cross<NT>(q);
-                    __syncthreads();
-                    const unsigned long long mask = a.active[q];
-                    if (mask) {
-                        phase_update<NT>(q, 0, mask);
-                        __syncthreads();
-                        if (V) {
-                            phase_update<NT>(q, 1, mask);
-                            __syncthreads();
-                        }
-                    }
-                }
+                outer_step<double, GR>(pairs, k == 0);
                 if (pa.ordering == HSVD_ORD_MODMOD && tid < pairs) S[tid] = modmod_next(S[tid], nb);
                 __syncthreads();
             }
             ++sweeps;
-            persist_colnorm<NT>(G, ldg, r, rho, false, d, L);
+            persist_colnorm<GR>(G, ldg, r, rho, false, d, L);
             if (pa.sort) persist_sort(d, rho, r, p, L);
             // the sweep's codes and counters (eq. 4.2)
             int c = 0;
@@ -664,12 +713,10 @@ __device__ void persist_solve(const PersistArgs &pa, int z, char *slot, PersistL
 
 }  // namespace
 
-// Two waves per SIMD at 256 threads (two workgroups per compute unit, some
-// registers spilled): 125 ms against 182 ms with the compiler's own
-// allocation (248 registers for the FP64 cross phase, 52 accumulation
-// registers more) on a 4096-problem sample of n ~ U{8..256}.
-template <int NT>
-__global__ __launch_bounds__(NT, NT == 1024 ? 4 : 2) void batch_persist_kernel(PersistArgs pa)
+// Four waves per SIMD: one workgroup of four groups per compute unit, two of
+// two, four of one.
+template <int GR>
+__global__ __launch_bounds__(256 * GR, 4) void batch_persist_kernel(PersistArgs pa)
 {
     __shared__ int s_idx;
     char *slot = pa.slots + (size_t)blockIdx.x * slot_layout().bytes;
@@ -679,7 +726,7 @@ __global__ __launch_bounds__(NT, NT == 1024 ? 4 : 2) void batch_persist_kernel(P
         const int idx = s_idx;
         __syncthreads();
         if (idx >= pa.batch) break;
-        persist_solve<NT>(pa, pa.order[idx], slot, g_lds, pargs());
+        persist_solve<GR>(pa, pa.order[idx], slot, lds<GR>(), pargs());
     }
 }
 
@@ -691,9 +738,9 @@ int persist_blocks_per_cu(int threads)
 {
     int blocks = 0;
     hipError_t e = hipErrorInvalidValue;
-    if (threads == 256) e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&blocks, batch_persist_kernel<256>, 256, 0);
-    if (threads == 512) e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&blocks, batch_persist_kernel<512>, 512, 0);
-    if (threads == 1024) e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&blocks, batch_persist_kernel<1024>, 1024, 0);
+    if (threads == 256) e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&blocks, batch_persist_kernel<1>, 256, 0);
+    if (threads == 512) e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&blocks, batch_persist_kernel<2>, 512, 0);
+    if (threads == 1024) e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&blocks, batch_persist_kernel<4>, 1024, 0);
     return e == hipSuccess ? blocks : 0;
 }
 
@@ -704,9 +751,9 @@ hipError_t launch_batch_persist(hipStream_t st, const PersistArgs &pa, int threa
     persist_zero_kernel<<<1, 1, 0, st>>>(pa.next);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    if (threads == 256) batch_persist_kernel<256><<<workgroups, 256, 0, st>>>(pa);
-    if (threads == 512) batch_persist_kernel<512><<<workgroups, 512, 0, st>>>(pa);
-    if (threads == 1024) batch_persist_kernel<1024><<<workgroups, 1024, 0, st>>>(pa);
+    if (threads == 256) batch_persist_kernel<1><<<workgroups, 256, 0, st>>>(pa);
+    if (threads == 512) batch_persist_kernel<2><<<workgroups, 512, 0, st>>>(pa);
+    if (threads == 1024) batch_persist_kernel<4><<<workgroups, 1024, 0, st>>>(pa);
     return hipGetLastError();
 }
 

@@ -112,12 +112,16 @@ constexpr int kGramTiles = 10;
 static __constant__ int kGramTX[kGramTiles] = {0, 0, 0, 0, 1, 1, 1, 2, 2, 3};
 static __constant__ int kGramTY[kGramTiles] = {0, 1, 2, 3, 1, 2, 3, 2, 3, 3};
 
-// The Gram of block pair k over the rows of `split`, by the first 256
-// threads of the workgroup (waves beyond the fourth only take part in the
-// barriers); red: kGramRed elements of LDS.  Every thread must call it.
+// The Gram of block pair k over the rows of `split`, by 256 threads (tid among
+// them); red: kGramRed elements of LDS.  kGramBarriers workgroup barriers.
+//
+// The functions of this file that take a tid work with NT threads of a
+// workgroup that may hold several such groups, each with a block pair of its
+// own: every group passes the same barriers.
+constexpr int kGramBarriers = 3;
 constexpr int kGramRed = 3 * (kGramTiles / 2) * 256;
 template <typename T>
-__device__ __forceinline__ void gram_pair(const BlockArgsT<T> &a, int k, int split, T *red)
+__device__ __forceinline__ void gram_pair(const BlockArgsT<T> &a, int k, int split, T *red, int tid)
 {
     constexpr int kV = 16 / (int)sizeof(T);  // rows per 16-byte load
     // loads per tile and chunk: FP32 one (16 rows), FP64 two (8 rows each)
@@ -126,7 +130,7 @@ __device__ __forceinline__ void gram_pair(const BlockArgsT<T> &a, int k, int spl
     typedef T vec __attribute__((ext_vector_type(kV)));
     constexpr int kHalf = kGramTiles / 2;
     const int2 IJ = outer_pair(a, k);
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int lane = tid & 63, wave = tid >> 6;
     const int lr = lane & 15, lk = lane >> 4;
     const int row_begin = split * a.rows_per_split;
     const int row_end = min(a.ldg, row_begin + a.rows_per_split);
@@ -143,7 +147,7 @@ __device__ __forceinline__ void gram_pair(const BlockArgsT<T> &a, int k, int spl
 #pragma unroll
     for (int q = 0; q < kGramTiles; ++q) acc[q] = MF<T>::zero();
     // no prefetch: the registers go to occupancy instead (measured faster)
-    for (int c = wave; c < (wave < 4 ? nchunk : 0); c += 4) {
+    for (int c = wave; c < nchunk; c += 4) {
         vec cur[4][NH];
         const unsigned rb = (unsigned)(c * kRC) * (unsigned)sizeof(T);
 #pragma unroll
@@ -174,7 +178,7 @@ __device__ __forceinline__ void gram_pair(const BlockArgsT<T> &a, int k, int spl
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
         if (h) __syncthreads();
-        if (wave > 0 && wave < 4) {
+        if (wave > 0) {
 #pragma unroll
             for (int j = 0; j < kHalf; ++j)
 #pragma unroll
@@ -204,12 +208,11 @@ __device__ __forceinline__ void gram_pair(const BlockArgsT<T> &a, int k, int spl
 // sums the entries (x, y), (x, y + 1) of tile i / 128 of every split with
 // vector loads.
 template <typename T, int NT, typename Put>
-__device__ __forceinline__ void stage_gram(const BlockArgsT<T> &a, int k, Put put)
+__device__ __forceinline__ void stage_gram(const BlockArgsT<T> &a, int k, int tid, Put put)
 {
     constexpr int kItems = kGramTiles * 128;
     typedef T v2 __attribute__((ext_vector_type(2)));
     constexpr int kChunk = 8;
-    const int tid = threadIdx.x;
 #pragma unroll
     for (int q = 0; q < (kItems + NT - 1) / NT; ++q) {
         const int item = tid + NT * q;
@@ -371,7 +374,6 @@ struct CrossLds {
     // still computed in FP64 from the FP32 pivots and applied in FP32 (W is
     // rounded to T on output in any case).
     typename SlotRot<T>::packed prm[2][kB];
-    int live;  // some cross pair fails the skip test
 };
 static_assert(2 * kXBuf <= kB2 * kLd, "exchange buffers fit the staging area");
 
@@ -728,19 +730,18 @@ __device__ __forceinline__ void cross_w_wave(CrossLds<T> &L, int nsteps, int wro
 
 // Every thread must call it (barriers).
 template <typename T, int NT>
-__device__ __forceinline__ void inner_cross_pair(const BlockArgsT<T> &a, int k, CrossLds<T> &L)
+__device__ __forceinline__ void inner_cross_pair(const BlockArgsT<T> &a, int k, CrossLds<T> &L, int &live, int tid)
 {
     static_assert(NT == 256 || NT == 512 || NT == 1024, "thread count");
     double *const buf = L.buf;
-    const int tid = threadIdx.x;
     const int lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int2 IJ = outer_pair(a, k);
     // the sweep's counters so far, read ahead of their update at the end
     SweepSoFar so_far;
     if (tid == 0) so_far.read(a, k);
-    stage_gram<T, NT>(a, k, [&](int x, int y, double v) { buf[x * kLd + y] = v; });
-    if (tid == 0) L.live = 0;
+    stage_gram<T, NT>(a, k, tid, [&](int x, int y, double v) { buf[x * kLd + y] = v; });
+    if (tid == 0) live = 0;
     __syncthreads();
     {
         // Every cross pair (x, b + y) of the block pair is the pivot of one
@@ -758,10 +759,10 @@ __device__ __forceinline__ void inner_cross_pair(const BlockArgsT<T> &a, int k, 
             const int x = (tid + NT * q) >> 5;
             fails |= rel_orthogonal_sq((T)buf[x * kLd + x], ayy, (T)buf[x * kLd + kB + y], tol, tol2) ? 0 : 1;
         }
-        if (__ballot(fails) != 0ull && lane == 0) L.live = 1;
+        if (__ballot(fails) != 0ull && lane == 0) live = 1;
     }
     __syncthreads();
-    const int nsteps = __builtin_amdgcn_readfirstlane(L.live) ? kB : 0;  // the same in every thread
+    const int nsteps = __builtin_amdgcn_readfirstlane(live) ? kB : 0;  // the same in every thread
     T *const Wg = a.W + (size_t)k * (kB2 * kB2);
     constexpr int kWWave = NT / 64 - 4;  // first of the four W waves (NT >= 512)
     if (wave == 0) {
@@ -793,6 +794,16 @@ __device__ __forceinline__ void inner_cross_pair(const BlockArgsT<T> &a, int k, 
     } else {
         for (int u = 0; u <= nsteps; ++u) role_barrier();
     }
+}
+
+// The barriers of inner_cross_pair, for threads of the workgroup without a
+// block pair.
+__device__ __forceinline__ void inner_cross_idle(const int &live)
+{
+    __syncthreads();
+    __syncthreads();
+    const int nsteps = __builtin_amdgcn_readfirstlane(live) ? kB : 0;
+    for (int u = 0; u <= nsteps; ++u) role_barrier();
 }
 
 
@@ -1021,16 +1032,16 @@ __device__ __forceinline__ void circle_block_wave(CircleLds &L, int nsweeps, int
 
 // NT threads.  Every thread must call it (barriers).
 template <typename T, int NT>
-__device__ __forceinline__ void inner_circle_pair(const BlockArgsT<T> &a, int k, CircleLds &L)
+__device__ __forceinline__ void inner_circle_pair(const BlockArgsT<T> &a, int k, CircleLds &L, int tid)
 {
     static_assert(NT == 256 || NT == 512 || NT == 1024, "thread count");
-    const int tid = threadIdx.x, lane = tid & 63;
+    const int lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int2 IJ = outer_pair(a, k);
     // the sweep's counters so far, read ahead of their update at the end
     SweepSoFar so_far;
     if (tid == 0) so_far.read(a, k);
-    stage_gram<T, NT>(a, k, [&](int x, int y, double v) {
+    stage_gram<T, NT>(a, k, tid, [&](int x, int y, double v) {
         if (x <= y) (&L.X[0][0])[circle_at(circle_place(x), circle_place(y))] = v;
     });
     __syncthreads();
@@ -1071,6 +1082,14 @@ __device__ __forceinline__ void inner_circle_pair(const BlockArgsT<T> &a, int k,
     if (wturn) w.store(a.W + (size_t)k * (kB2 * kB2), wrow, j);
 }
 
+// The barriers of inner_circle_pair with one sweep, for threads of the
+// workgroup without a block pair.
+__device__ __forceinline__ void inner_circle_idle()
+{
+    __syncthreads();
+    for (int u = 0; u < 2 * (kB2 - 1); ++u) role_barrier();
+}
+
 // ---------------------------------------------------------------------------
 // Update: [G_P | V_P] <- [G_P | V_P] W.
 //
@@ -1101,24 +1120,25 @@ constexpr int kUpdRows = 64;
 // columns, W_TT zero-padded to NC x NC; only the m touched columns are read
 // and written.  NT threads.
 template <typename T, int NC, int NT>
-__device__ __forceinline__ void update_compact(const BlockArgsT<T> &a, int k, T *__restrict__ M, int row_base,
-                                               int nstrips, T *Wl, const int *cols, const int *tl, int m)
+__device__ __forceinline__ void update_compact(const BlockArgsT<T> &a, int k, T *M, T *M2, int row_base,
+                                               int nstrips, T *Wl, const int *cols, const int *tl, int m, int tid)
 {
     constexpr int NW = NT / 64;
     const T *Wg = a.W + (size_t)k * (kB2 * kB2);
-    for (int idx = threadIdx.x; idx < NC * NC; idx += NT) {
+    for (int idx = tid; idx < NC * NC; idx += NT) {
         const int i = idx / NC, j = idx % NC;
         Wl[idx] = (i < m && j < m) ? Wg[tl[i] * kB2 + tl[j]] : T(0);
     }
     __syncthreads();
     constexpr int KK = NC / 4, YT = NC / 16;
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int lane = tid & 63, wave = tid >> 6;
     const int lr = lane & 15, lk = lane >> 4;
-    char *__restrict__ base = reinterpret_cast<char *>(M);
     const unsigned row_off = (unsigned)(row_base + lr) * (unsigned)sizeof(T);
     const unsigned col_bytes = (unsigned)a.ldg * (unsigned)sizeof(T);
 #pragma unroll 1
-    for (int strip = wave; strip < nstrips; strip += NW) {
+    for (int at = wave; at < (M2 ? 2 * nstrips : nstrips); at += NW) {
+        const int strip = at < nstrips ? at : at - nstrips;
+        char *const base = reinterpret_cast<char *>(at < nstrips ? M : M2);
         const unsigned rb = (unsigned)(strip * 16) * (unsigned)sizeof(T) + row_off;
         T bv[KK];
 #pragma unroll
@@ -1144,32 +1164,32 @@ __device__ __forceinline__ void update_compact(const BlockArgsT<T> &a, int k, T 
     }
 }
 
-// Rows [row_base, row_base + 16 nstrips) of the 2b columns of block pair k
-// in M (G or V) <- themselves times W, by NT threads; mask = the pair's
-// touched local columns (nonzero).  kWLds: W re-read from LDS for every
-// 16-row strip with the next strip's rows prefetched into registers when
-// kPrefetch (else the compiler keeps all 64 W operands in registers across
-// strips); kOne: at most one strip per wave (nstrips <= NT / 64), no loop;
-// kLd: LDS row stride of W.  Every thread must call it (barriers).
-template <typename T, int NT, bool kWLds, bool kPrefetch, int kLd, bool kOne = false>
-__device__ __forceinline__ void update_rows(const BlockArgsT<T> &a, int k, T *__restrict__ M, int row_base,
-                                            int nstrips, unsigned long long mask, T *Wl, int *cols, int *tl)
+// Rows [row_base, row_base + 16 nstrips) of the 2b columns of block pair k in
+// M (G or V), and in M2 when it is not null, <- themselves times W, by NT
+// threads; mask = the pair's touched local columns (nonzero).  kOne: one
+// matrix and at most one strip per wave (nstrips <= NT / 64), no loop; else W
+// is re-read from LDS for every strip.  kLd: LDS row stride of W.
+// kUpdateBarriers workgroup barriers.
+constexpr int kUpdateBarriers = 2;
+template <typename T, int NT, int kLd, bool kOne>
+__device__ __forceinline__ void update_rows(const BlockArgsT<T> &a, int k, T *M, T *M2, int row_base, int nstrips,
+                                            unsigned long long mask, T *Wl, int *cols, int *tl, int tid)
 {
     constexpr int NW = NT / 64;
     const int2 IJ = outer_pair(a, k);
     const int m = __popcll(mask);
     if (m <= 32) {
         // compact list of the touched local columns, in increasing order
-        if (threadIdx.x < kB2 && ((mask >> threadIdx.x) & 1ull)) {
-            const int i = __popcll(mask & ((1ull << threadIdx.x) - 1ull));
-            tl[i] = threadIdx.x;
-            cols[i] = a.rho[local_pos(threadIdx.x, IJ.x, IJ.y)];
+        if (tid < kB2 && ((mask >> tid) & 1ull)) {
+            const int i = __popcll(mask & ((1ull << tid) - 1ull));
+            tl[i] = tid;
+            cols[i] = a.rho[local_pos(tid, IJ.x, IJ.y)];
         }
         __syncthreads();
         if (m <= 16)
-            update_compact<T, 16, NT>(a, k, M, row_base, nstrips, Wl, cols, tl, m);
+            update_compact<T, 16, NT>(a, k, M, M2, row_base, nstrips, Wl, cols, tl, m, tid);
         else
-            update_compact<T, 32, NT>(a, k, M, row_base, nstrips, Wl, cols, tl, m);
+            update_compact<T, 32, NT>(a, k, M, M2, row_base, nstrips, Wl, cols, tl, m, tid);
         return;
     }
     // W on its way while the column list is made; the first strip's rows on
@@ -1180,44 +1200,46 @@ __device__ __forceinline__ void update_rows(const BlockArgsT<T> &a, int k, T *__
     const v4 *Wg = reinterpret_cast<const v4 *>(a.W + (size_t)k * (kB2 * kB2));
     v4 wreg[kW4];
 #pragma unroll
-    for (int q = 0; q < kW4; ++q) wreg[q] = Wg[threadIdx.x + q * NT];
-    if (threadIdx.x < kB2) cols[threadIdx.x] = a.rho[local_pos(threadIdx.x, IJ.x, IJ.y)];
+    for (int q = 0; q < kW4; ++q) wreg[q] = Wg[tid + q * NT];
+    if (tid < kB2) cols[tid] = a.rho[local_pos(tid, IJ.x, IJ.y)];
     __syncthreads();
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int lane = tid & 63, wave = tid >> 6;
     const int lr = lane & 15, lk = lane >> 4;
     // 32-bit byte offsets from the uniform base (r, ldg <= 16448: below 2^32 bytes).
     // Loads: B(k = x, j = row) = G(row0 + lr, column x = 4kk + lk).
     // Stores: D(i = y, j = row), y = 16yt + MF::row(lane, v).
-    char *__restrict__ base = reinterpret_cast<char *>(M);
     const unsigned row_off = (unsigned)(row_base + lr) * (unsigned)sizeof(T);
     const unsigned col_bytes = (unsigned)a.ldg * (unsigned)sizeof(T);
-    auto load = [&](int strip, T *bv, const int *cp) {
-        const unsigned rb = (unsigned)(strip * 16) * (unsigned)sizeof(T) + row_off;
+    auto at_matrix = [&](int at) { return reinterpret_cast<char *>(kOne || at < nstrips ? M : M2); };
+    auto at_row = [&](int at) {
+        return (unsigned)((kOne || at < nstrips ? at : at - nstrips) * 16) * (unsigned)sizeof(T) + row_off;
+    };
+    auto load = [&](int at, T *bv, const int *cp) {
+        const char *base = at_matrix(at);
+        const unsigned rb = at_row(at);
 #pragma unroll
         for (int kk = 0; kk < 16; ++kk)
             bv[kk] = *reinterpret_cast<const T *>(base + ((unsigned)cp[4 * kk + lk] * col_bytes + rb));
     };
-    constexpr bool kPre = kWLds && kPrefetch && !kOne;
-    T bv[16], nx[16];
-    if (wave < nstrips) load(wave, bv, cols);
+    const int total = !kOne && M2 ? 2 * nstrips : nstrips;
+    T bv[16];
+    if (wave < total) load(wave, bv, cols);
 #pragma unroll
     for (int q = 0; q < kW4; ++q) {
-        const int idx = (threadIdx.x + q * NT) * 4;
+        const int idx = (tid + q * NT) * 4;
         T *const w = Wl + (idx / kB2) * kLd + idx % kB2;
 #pragma unroll
         for (int e = 0; e < 4; ++e) w[e] = wreg[q][e];
     }
     __syncthreads();
 #pragma unroll 1
-    for (int strip = wave; strip < nstrips; strip += kOne ? nstrips : NW) {
-        // With kWLds, the opaque zero wz keeps the compiler from hoisting the
-        // column offsets and the 64 W operands into registers across strips.
+    for (int at = wave; at < total; at += kOne ? total : NW) {
+        // With several strips, the opaque zero wz keeps the compiler from
+        // hoisting the column offsets and the 64 W operands into registers
+        // across strips.
         int wz = 0;
-        if (kWLds && !kOne) asm volatile("" : "+v"(wz));
-        if (kPre)  // next strip in flight during the products; the last re-reads its own rows
-            load(strip + NW < nstrips ? strip + NW : strip, nx, cols + wz);
-        else if (!kOne && strip != wave)
-            load(strip, bv, cols + wz);
+        if (!kOne) asm volatile("" : "+v"(wz));
+        if (!kOne && at != wave) load(at, bv, cols + wz);
         const T *Wp = Wl + wz + lk * kLd + lr;
         typename MF<T>::acc acc[4];
 #pragma unroll
@@ -1231,17 +1253,14 @@ __device__ __forceinline__ void update_rows(const BlockArgsT<T> &a, int k, T *__
                 acc[yt] = MF<T>::mma(aw, bv[kk], acc[yt]);
             }
         const int *cp = cols + wz;
-        const unsigned rb = (unsigned)(strip * 16) * (unsigned)sizeof(T) + row_off;
+        char *const base = at_matrix(at);
+        const unsigned rb = at_row(at);
 #pragma unroll
         for (int yt = 0; yt < 4; ++yt)
 #pragma unroll
             for (int v = 0; v < 4; ++v)
                 *reinterpret_cast<T *>(base + ((unsigned)cp[yt * 16 + MF<T>::row(lane, v)] * col_bytes + rb)) =
                     acc[yt][v];
-        if (kPre) {
-#pragma unroll
-            for (int kk = 0; kk < 16; ++kk) bv[kk] = nx[kk];
-        }
     }
 }
 

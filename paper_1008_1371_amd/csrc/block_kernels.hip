@@ -52,7 +52,7 @@ __global__ __launch_bounds__(256) void block_gram_kernel(BlockArgsT<T> a)
 {
     __shared__ T red[kGramRed];
     if (!bind_problem(a)) return;
-    gram_pair<T>(a, blockIdx.x, blockIdx.y, red);
+    gram_pair<T>(a, blockIdx.x, blockIdx.y, red, threadIdx.x);
 }
 
 template <typename T>
@@ -60,7 +60,7 @@ __global__ __launch_bounds__(1024) void block_inner_circle_kernel(BlockArgsT<T> 
 {
     __shared__ CircleLds L;
     if (!bind_problem(a)) return;
-    inner_circle_pair<T, 1024>(a, blockIdx.x, L);
+    inner_circle_pair<T, 1024>(a, blockIdx.x, L, threadIdx.x);
 }
 
 // With NT = kCrossThreads (single solves) the workgroups after the block
@@ -70,6 +70,7 @@ template <typename T, int NT>
 __global__ __launch_bounds__(NT, 4) void block_inner_cross_kernel(BlockArgsT<T> a)
 {
     __shared__ CrossLds<T> L;
+    __shared__ int live;  // some cross pair fails the skip test
     if constexpr (NT == kCrossThreads) {
         if ((int)blockIdx.x >= a.nb / 2) {
             v_update_role(a, (int)blockIdx.x - a.nb / 2);
@@ -77,7 +78,7 @@ __global__ __launch_bounds__(NT, 4) void block_inner_cross_kernel(BlockArgsT<T> 
         }
     }
     if (!bind_problem(a)) return;
-    inner_cross_pair<T, NT>(a, blockIdx.x, L);
+    inner_cross_pair<T, NT>(a, blockIdx.x, L, live, threadIdx.x);
 }
 
 // launches).
@@ -107,7 +108,7 @@ __global__ __launch_bounds__(256, 4) void block_update_kernel(BlockArgsT<T> a)
     T *__restrict__ M = t < tiles_g ? a.G : a.V;
     const int row_base = (t < tiles_g ? t : t - tiles_g) * kRows;
     const int nstrips = min(kRows, a.ldg - row_base) / 16;
-    update_rows<T, 256, true, false, kUpdLd, true>(a, k, M, row_base, nstrips, mask, Wl, cols, tl);
+    update_rows<T, 256, kUpdLd, true>(a, k, M, nullptr, row_base, nstrips, mask, Wl, cols, tl, threadIdx.x);
 }
 
 // V update of the previous outer step inside an inner-solve launch: workgroup
@@ -135,7 +136,7 @@ __device__ void v_update_role(const BlockArgsT<T> &a, int role)
     if (!mask) return;
     const int row_base = tile * kRoleRows;
     const int nstrips = min(kRoleRows, a.ldg - row_base) / 16;
-    update_rows<T, kCrossThreads, true, false, kLdV, true>(v, k, a.V, row_base, nstrips, mask, Wl, cols, tl);
+    update_rows<T, kCrossThreads, kLdV, true>(v, k, a.V, nullptr, row_base, nstrips, mask, Wl, cols, tl, threadIdx.x);
 }
 
 // Outer stepper start (nb/2 slots, antidiagonal over blocks).

@@ -28,15 +28,17 @@ namespace hsvd {
 
 using namespace gemm;
 
+constexpr int kTile = 128;  // rows and columns of a tile of C
+
 template <bool TA, bool SGN, bool SYM>
 __global__ __launch_bounds__(256, 2) void gemm_f64_kernel(GemmArgs g)
 {
-    __shared__ GemmLds L;
+    __shared__ GemmLds<kTile> L;
     const int z = blockIdx.z;
     // block-pair form: pair zg, K split ks (see GemmArgs)
     const int zg = g.blk ? z / g.ksplit : z, ks = g.blk ? z % g.ksplit : 0;
     if (g.flag && ((g.flag[zg] != 0) != (g.want != 0))) return;
-    const int tiles_m = (g.M + kTM - 1) / kTM, tiles_n = (g.N + kTN - 1) / kTN;
+    const int tiles_m = (g.M + kTile - 1) / kTile, tiles_n = (g.N + kTile - 1) / kTile;
     int tm, tn;
     if (SYM) {
         // upper triangle, tm <= tn, numbered column by column
@@ -56,7 +58,7 @@ __global__ __launch_bounds__(256, 2) void gemm_f64_kernel(GemmArgs g)
         tm = t / tiles_n;
         tn = t % tiles_n;
     }
-    gemm_tile<TA, SGN, SYM, false>(g, z, zg, ks, tm, tn, L);
+    gemm_tile<TA, SGN, SYM, kTile>(g, z, zg, ks, tm, tn, L, threadIdx.x);
 }
 
 hipError_t launch_gemm(hipStream_t st, const GemmArgs &g, int nprob, bool trans_a, bool signed_b, bool symmetric)
@@ -65,7 +67,7 @@ hipError_t launch_gemm(hipStream_t st, const GemmArgs &g, int nprob, bool trans_
     if (symmetric && (!trans_a || g.M != g.N || (g.map & 4))) return hipErrorInvalidValue;
     if (g.map && (!g.blk || g.bw < 1 || g.ksplit < 1 || nprob % g.ksplit)) return hipErrorInvalidValue;
     if (g.M == 0 || g.N == 0) return hipSuccess;
-    const int tm = (g.M + kTM - 1) / kTM, tn = (g.N + kTN - 1) / kTN;
+    const int tm = (g.M + kTile - 1) / kTile, tn = (g.N + kTile - 1) / kTile;
     const dim3 grid(symmetric ? tm * (tm + 1) / 2 : tm * tn, 1, nprob);
     if (symmetric) {
         if (signed_b) gemm_f64_kernel<true, true, true><<<grid, 256, 0, st>>>(g);
