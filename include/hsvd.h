@@ -97,9 +97,10 @@ typedef struct {
                         group's)                                               */
     int persistent;  /* pairwise path: 0 = one launch per parallel step (replayed from a
                         HIP graph when graph = 1) and the stop rule checked on the host
-                        after every sweep -- except bordered orders up to 128 with the
-                        modified modulus ordering, which one workgroup solves in one
-                        launch; 1 = all sweeps in one persistent cooperative
+                        after every sweep -- except, with the modified modulus ordering,
+                        bordered orders up to 128, which one workgroup solves in one
+                        launch, and up to 2048, which take four steps' worth of pairs
+                        per launch; 1 = all sweeps in one persistent cooperative
                         launch: a pair waits only for the two visits of the previous
                         step that last held its columns (per-column visit counts), and
                         the diagonal sort and the stop rule (eq. 4.2) run on the device
@@ -110,7 +111,7 @@ typedef struct {
 
 /* Kernel classes timed in hsvd_info (index into the kernel_* arrays). */
 enum {
-    HSVD_K_PAIR_STEP = 0,      /* pairwise path: one parallel step of pivot pairs          */
+    HSVD_K_PAIR_STEP = 0,      /* pairwise path: launches of pivot pairs (see persistent)   */
     HSVD_K_BLOCK_GRAM = 1,     /* block path, FP64: Gram matrices G_P^T G_P                */
     HSVD_K_BLOCK_INNER = 2,    /* block path, FP64: inner rotations of each block pair     */
     HSVD_K_BLOCK_UPDATE = 3,   /* block path, FP64: [G_P | V_P] <- [G_P | V_P] W           */

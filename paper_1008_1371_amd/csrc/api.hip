@@ -183,6 +183,10 @@ Layout make_layout(int n, int r, int ldg, bool want_v, int pairs, int splits, in
     L.off_ver = take(sizeof(unsigned int) * r);
     L.off_pctl = take(sizeof(PersistCtl));
     const size_t bb = (size_t)b2 * b2;
+    // rotations of the pairwise path's tiles, two sets
+    const size_t tiles = pairs ? 0 : (size_t)tile_count(r);
+    L.off_tprm = take(sizeof(double2) * 2 * tiles * kTileW * kTileW);
+    L.off_tmask = take(sizeof(unsigned) * 2 * tiles * kTileW);
     L.off_P = take(sizeof(double) * (size_t)pairs * splits * bb);
     // W and the touched-column masks are double-buffered by step parity: the
     // V update of a step runs inside the next step's inner launch
@@ -229,6 +233,10 @@ Workspace carve(void *base, const Layout &L)
     w.ctl = reinterpret_cast<Ctl *>(b + L.off_ctl);
     w.ver = reinterpret_cast<unsigned int *>(b + L.off_ver);
     w.pctl = reinterpret_cast<PersistCtl *>(b + L.off_pctl);
+    if (L.pairs == 0) {
+        w.tprm = reinterpret_cast<double2 *>(b + L.off_tprm);
+        w.tmask = reinterpret_cast<unsigned *>(b + L.off_tmask);
+    }
     if (L.pairs > 0) {
         w.P = reinterpret_cast<double *>(b + L.off_P);
         w.W = reinterpret_cast<double *>(b + L.off_W);
@@ -952,7 +960,7 @@ hsvd_status solve_canonical(hsvd_ctx *ctx, const double *G, int lda, int n, int 
         a.ordering = prm.ordering;
         a.tol = tol;
         a.tthresh = tthresh;
-        // The r (or r - 1) dependent step launches of a sweep are captured
+        // The dependent launches of a sweep (r or r - 1 steps, or tiles) are captured
         // once as a HIP graph and replayed every sweep (the stepper state
         // lives in device memory and every launch's arguments repeat from
         // sweep to sweep); a step moves only a few MB at moderate n, so the
@@ -1005,14 +1013,42 @@ hsvd_status solve_canonical(hsvd_ctx *ctx, const double *G, int lda, int n, int 
             else if (ctx->host_pctl->stop == 1) converged = true;
             if (status == HSVD_OK && !converged) status = HSVD_E_NOCONV;
         }
+        // Modified modulus sweeps go in tiles, four steps' worth of pairs per
+        // launch, as long as LDS holds the eight columns of one (2048 rows;
+        // there 133 -> 62 ms for three sweeps of n = 2048, and n = 129 5.5 ->
+        // 3.0 ms for a solve); round-robin pairs depend on each other in
+        // another way.
+        const bool tiled = prm.ordering == HSVD_ORD_MODMOD && ldg <= kTileMaxLdg;
+        TileArgs ta;
+        ta.G = a.G;
+        ta.V = a.V;
+        ta.ldg = ldg;
+        ta.r = r;
+        ta.p = p;
+        ta.d = w.d;
+        ta.rho = w.rho;
+        ta.C = w.C;
+        ta.nrot = w.nrot;
+        ta.nskip = w.nskip;
+        ta.maxt = w.maxt;
+        ta.ctl = w.ctl;
+        ta.tol = tol;
+        ta.tthresh = tthresh;
+        ta.prm = w.tprm;
+        ta.rmask = w.tmask;
+        const int launches = tiled ? tile_steps(r) + (a.V ? 1 : 0) : steps_per_sweep;
+        auto launch_step = [&](hipStream_t on, int k) -> hipError_t {
+            if (tiled) return launch_pair_tiles(on, ta, k);
+            a.step = k;
+            return launch_pair_step(on, a);
+        };
         SweepGraph sg(ctx, st);
         hipStream_t q = st;
         const bool graph = prm.graph && mode.graphs && !prm.persistent;
         if (graph) {
             HSVD_TRY(sg.begin(q));
-            for (int k = 0; k < steps_per_sweep; ++k) {
-                a.step = k;
-                const hipError_t le = launch_pair_step(q, a);
+            for (int k = 0; k < launches; ++k) {
+                const hipError_t le = launch_step(q, k);
                 if (le != hipSuccess) {
                     sg.abort(q);
                     return HSVD_E_DEVICE;
@@ -1025,14 +1061,11 @@ hsvd_status solve_canonical(hsvd_ctx *ctx, const double *G, int lda, int n, int 
             if (graph) {
                 HSVD_TRY(hipGraphLaunch(sg.exec, q));
             } else {
-                for (int k = 0; k < steps_per_sweep; ++k) {
-                    a.step = k;
-                    HSVD_TRY(launch_pair_step(q, a));
-                }
+                for (int k = 0; k < launches; ++k) HSVD_TRY(launch_step(q, k));
             }
             if (timing) HSVD_TRY(hipEventRecord(ev[3], q));
-            klaunch[HSVD_K_PAIR_STEP] += steps_per_sweep;
-            ktimed[HSVD_K_PAIR_STEP] += steps_per_sweep;
+            klaunch[HSVD_K_PAIR_STEP] += launches;
+            ktimed[HSVD_K_PAIR_STEP] += launches;
             steps += steps_per_sweep;
             if (prm.sort) HSVD_TRY(launch_sort(q, w.d, w.rho, w.dtmp, w.rtmp, r, p));
             HSVD_TRY(launch_sweep_reduce(q, w, r / 2));

@@ -48,6 +48,8 @@ struct Workspace {
     int *rho = nullptr;       // r: physical column at each position
     double *dtmp = nullptr;   // r: sort scratch
     int *rtmp = nullptr;      // 2r: sort scratch (moved rho, ranks)
+    double2 *tprm = nullptr;   // pairwise tiles: rotations of two steps
+    unsigned *tmask = nullptr; // pairwise tiles: which pairs rotate
     int4 *S = nullptr;        // r/2: modified modulus stepper state per slot (ip, jp, iblk, jblk)
     int *C = nullptr;         // r/2: per-slot convergence code of the current sweep (eq. 4.2)
     unsigned int *nrot = nullptr;   // r/2: per-slot rotations in the current sweep
@@ -78,7 +80,7 @@ struct Layout {
     int n = 0, r = 0, ldg = 0, pairs = 0, splits = 0, b2 = 0;
     size_t bytes = 0;
     size_t off_G, off_V, off_d, off_rho, off_dtmp, off_rtmp, off_S, off_C, off_nrot, off_nskip,
-        off_nact, off_ntc, off_maxt, off_ctl, off_ver, off_pctl, off_P, off_W, off_active, off_S2, off_G32, off_V32, off_P32, off_W32,
+        off_nact, off_ntc, off_maxt, off_ctl, off_ver, off_pctl, off_tprm, off_tmask, off_P, off_W, off_active, off_S2, off_G32, off_V32, off_P32, off_W32,
         off_T1, off_T2, off_G2, off_V2, off_blk, off_pl, off_rho2, off_wact;
     bool mixed = false, wide = false;
 };
@@ -386,6 +388,34 @@ struct SmallArgs {
     Ctl *ctl;
 };
 hipError_t launch_pair_small(hipStream_t st, const SmallArgs &a);
+
+// Pairwise sweeps in tiles of kTileW x kTileW pairs (modified modulus ordering,
+// ldg <= kTileMaxLdg; pair_tile.hip): launches 0 .. tile_steps(r) of a sweep,
+// the last one only for V.
+constexpr int kTileW = 4;
+constexpr int kTileMaxLdg = 2048;
+inline int tile_count(int r) { return (r / 2 + kTileW - 1) / kTileW; }
+inline int tile_steps(int r) { return 2 * tile_count(r) + ((r / 2) % kTileW ? 2 : 1); }
+struct TileArgs {
+    double *G, *V;  // V: nullptr or its columns
+    int ldg, r, p;
+    double *d;
+    const int *rho;
+    int *C;
+    unsigned *nrot, *nskip;
+    double *maxt;
+    Ctl *ctl;
+    double tol, tthresh;
+    // the rotations (t, c; c < 0: trigonometric) of each tile and the pairs
+    // that rotate, two sets: a step's are applied to V in the next launch
+    double2 *prm;     // 2 x tiles x kTileW^2
+    unsigned *rmask;  // 2 x tiles x kTileW
+    // set by the launcher
+    int S, SV, vparts;
+    const double2 *prm_v;
+    const unsigned *rmask_v;
+};
+hipError_t launch_pair_tiles(hipStream_t st, TileArgs a, int step);
 
 template <typename T>
 struct BlockArgsT {

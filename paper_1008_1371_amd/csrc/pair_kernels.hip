@@ -1,7 +1,9 @@
 // Pairwise one-sided Jacobi HSVD kernels for gfx950 (FP64).
 //
 // One parallel step (Sec. 2: a set of disjoint pivot pairs) is one launch of
-// pair_step_kernel with one workgroup per pair slot.  The workgroup keeps the
+// pair_step_kernel with one workgroup per pair slot (round-robin ordering, and
+// columns above 2048 rows; pair_small.hip and pair_tile.hip take the others).
+// The workgroup keeps the
 // two G columns in registers between the dot product and the update, so a
 // rotated pair moves exactly 2 reads + 2 writes of G and of V columns, and a
 // skipped pair only the 2 G reads.  Columns are column-major with a leading
