@@ -183,10 +183,6 @@ Layout make_layout(int n, int r, int ldg, bool want_v, int pairs, int splits, in
     L.off_ver = take(sizeof(unsigned int) * r);
     L.off_pctl = take(sizeof(PersistCtl));
     const size_t bb = (size_t)b2 * b2;
-    // rotations of the pairwise path's tiles, two sets
-    const size_t tiles = pairs ? 0 : (size_t)tile_count(r);
-    L.off_tprm = take(sizeof(double2) * 2 * tiles * kTileW * kTileW);
-    L.off_tmask = take(sizeof(unsigned) * 2 * tiles * kTileW);
     L.off_P = take(sizeof(double) * (size_t)pairs * splits * bb);
     // W and the touched-column masks are double-buffered by step parity: the
     // V update of a step runs inside the next step's inner launch
@@ -209,7 +205,13 @@ Layout make_layout(int n, int r, int ldg, bool want_v, int pairs, int splits, in
     L.off_pl = take(wide ? sizeof(int) * (size_t)r : 0);
     L.off_rho2 = take(wide ? sizeof(int) * (size_t)r : 0);
     L.off_wact = take(wide ? sizeof(int) * (size_t)pairs : 0);
+    // rotations of the pairwise path's tiles, two sets; last, as a solve whose
+    // fixed scratch ends before them goes step by step
     L.bytes = o;
+    const size_t tiles = pairs == 0 && ldg <= kTileMaxLdg ? (size_t)tile_count(r) : 0;
+    L.off_tprm = take(sizeof(double2) * 2 * tiles * kTileW * kTileW);
+    L.off_tmask = take(sizeof(unsigned) * 2 * tiles * kTileW);
+    L.tile_bytes = o;
     return L;
 }
 
@@ -850,10 +852,11 @@ hsvd_status solve_canonical(hsvd_ctx *ctx, const double *G, int lda, int n, int 
     const Layout L = make_layout(n, r, ldg, acc_v, pairs, splits, block ? 2 * b : 0, mixed);
     hsvd_status s = HSVD_OK;
     void *base = mode.ws;
+    const bool tile_space = !base || L.tile_bytes <= mode.ws_cap;
     if (base) {
         if (L.bytes > mode.ws_cap) return mode.too_big;
     } else {
-        s = ensure_ws(ctx, L.bytes);
+        s = ensure_ws(ctx, L.tile_bytes);
         if (s != HSVD_OK) return s;
         base = ctx->ws;
     }
@@ -1018,7 +1021,7 @@ hsvd_status solve_canonical(hsvd_ctx *ctx, const double *G, int lda, int n, int 
         // there 133 -> 62 ms for three sweeps of n = 2048, and n = 129 5.5 ->
         // 3.0 ms for a solve); round-robin pairs depend on each other in
         // another way.
-        const bool tiled = prm.ordering == HSVD_ORD_MODMOD && ldg <= kTileMaxLdg;
+        const bool tiled = prm.ordering == HSVD_ORD_MODMOD && ldg <= kTileMaxLdg && tile_space;
         TileArgs ta;
         ta.G = a.G;
         ta.V = a.V;

@@ -78,10 +78,10 @@ struct Workspace {
 
 struct Layout {
     int n = 0, r = 0, ldg = 0, pairs = 0, splits = 0, b2 = 0;
-    size_t bytes = 0;
+    size_t bytes = 0, tile_bytes = 0;  // without and with the pairwise tiles' rotations
     size_t off_G, off_V, off_d, off_rho, off_dtmp, off_rtmp, off_S, off_C, off_nrot, off_nskip,
-        off_nact, off_ntc, off_maxt, off_ctl, off_ver, off_pctl, off_tprm, off_tmask, off_P, off_W, off_active, off_S2, off_G32, off_V32, off_P32, off_W32,
-        off_T1, off_T2, off_G2, off_V2, off_blk, off_pl, off_rho2, off_wact;
+        off_nact, off_ntc, off_maxt, off_ctl, off_ver, off_pctl, off_P, off_W, off_active, off_S2, off_G32, off_V32, off_P32, off_W32,
+        off_T1, off_T2, off_G2, off_V2, off_blk, off_pl, off_rho2, off_wact, off_tprm, off_tmask;
     bool mixed = false, wide = false;
 };
 
