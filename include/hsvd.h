@@ -89,9 +89,9 @@ typedef struct {
                         one persistent launch (the others, and the full-block
                         method, in launches grouped by bordered order); 1 =
                         grouped launches for every problem; 2 (default) = the
-                        schedule hsvd_autotune_batched chose for the precision,
-                        0 before tuning.  FP64: 0 and 1 give bit-identical
-                        results.  Mixed: each gives a valid mixed trajectory (the
+                        schedule hsvd_autotune_batched chose for the precision;
+                        before tuning 0, but for few FP64 problems 1.  FP64: 0
+                        and 1 give bit-identical results.  Mixed: each gives a valid mixed trajectory (the
                         FP64 sweeps of a problem start at the stepper phase its
                         own FP32 sweeps left, in the grouped launches at the
                         group's)                                               */
@@ -245,18 +245,20 @@ hsvd_status hsvd_solve_noalloc(hsvd_ctx *ctx, const double *G, int lda, int n, i
  *                    skips, active_pairs; ms_total is the device time of the
  *                    whole batched call; the kernel_* arrays are zero.
  * Problems of the block-oriented method with n <= 256 run in one persistent
- * launch (prm->batch_mode = 0; with the default 2, before tuning or when
- * hsvd_autotune_batched chose it for the precision; captured as a HIP graph
- * when prm->graph is set): each workgroup takes problems from a device work queue,
- * largest n first, and solves each one completely -- Gram, inner rotations
+ * launch (prm->batch_mode = 0; with the default 2 when hsvd_autotune_batched
+ * chose it for the precision, or before tuning unless the problems are few and
+ * FP64; captured as a HIP graph when prm->graph is set): each workgroup takes
+ * problems from a device work queue, largest n first, and solves each one completely -- Gram, inner rotations
  * and update of every block pair, sort and the stop rule of eq. (4.2) per
  * sweep; with mixed precision first the FP32 sweeps, the switch rule and the
  * J-re-orthogonalisation of V -- then output extraction, with no host round
  * trip.  The other problems (n > 256, the full-block method, batch_mode = 1,
- * or 2 when tuning chose the grouped launches) are grouped by their bordered
- * order (a multiple of 2b); each
+ * or 2 when tuning chose the grouped launches or, before tuning, for few FP64
+ * problems) are grouped by their bordered order (a multiple of 2b); each
  * group runs as one sequence of launches that covers all of its problems,
- * with the stop rule decided per problem on the device.  In FP64 both forms
+ * with the stop rule decided per problem on the device, groups of few problems
+ * side by side on streams of the context (forked from its stream and joined to
+ * it).  In FP64 both forms
  * give bit-identical results (in mixed precision see batch_mode).  Returns
  * HSVD_OK when every problem converged, else the status of the first problem
  * that did not.  Synchronises. */
@@ -308,7 +310,8 @@ hsvd_status hsvd_autotune_batched(hsvd_ctx *ctx, int batch, const int *n, const 
 
 /* The sweep schedule hsvd_solve_batched takes with batch_mode = 2 for
  * `precision` (HSVD_FP64 or HSVD_MIXED): *mode = 0 (one persistent launch),
- * 1 (launches grouped by order), or -1 (not tuned: the persistent launch).
+ * 1 (launches grouped by order), or -1 (not tuned: the persistent launch, or
+ * the grouped ones for few FP64 problems).
  * Errors: HSVD_E_INVAL (ctx or mode NULL, another precision). */
 hsvd_status hsvd_batched_schedule(const hsvd_ctx *ctx, int precision, int *mode);
 

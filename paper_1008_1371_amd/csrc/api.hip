@@ -13,6 +13,8 @@
 #include <algorithm>
 #include <mutex>
 #include <new>
+#include <type_traits>
+#include <utility>
 #include <vector>
 
 #include "internal.h"
@@ -28,7 +30,9 @@ struct hsvd_ctx {
     hsvd::PersistCtl *host_pctl = nullptr;   // pinned, in the same allocation
     std::vector<hipEvent_t> events;          // reusable timing events
     hipStream_t cap = nullptr;               // non-blocking stream for graph capture (default priority)
-    hipEvent_t join = nullptr;               // orders the capture stream with the caller's stream
+    hipEvent_t join = nullptr;               // orders the context's streams with the caller's stream
+    std::vector<hipStream_t> group_streams;  // non-blocking, one per group of a batch that runs beside others
+    int *host_active = nullptr;              // pinned, in the allocation of host_ctl: a count per group
     struct Tune {
         int valid = 0, algo = 0, wg = 0;
     } tune[16];                              // autotuner choice per size bucket (log2 of n, rounded up)
@@ -51,6 +55,7 @@ static __device__ __align__(256) unsigned char scratch[HSVD_NOALLOC_BYTES];
 
 namespace {
 
+constexpr int kMaxGroups = 16;  // bordered orders of a batch: 64, 128, .. 1024
 constexpr int kMaxDevices = 64;
 std::mutex g_scratch_mu;
 void *g_scratch_ptr[kMaxDevices] = {};
@@ -337,12 +342,14 @@ hsvd_status hsvd_init(hsvd_ctx **out, int device, void *hip_stream)
     ctx->stream = static_cast<hipStream_t>(hip_stream);
     void *h = nullptr;
     const size_t pctl_at = align_up(sizeof(Ctl), 64);
-    if (hipHostMalloc(&h, pctl_at + sizeof(PersistCtl), hipHostMallocDefault) != hipSuccess) {
+    const size_t active_at = align_up(pctl_at + sizeof(PersistCtl), 64);
+    if (hipHostMalloc(&h, active_at + sizeof(int) * kMaxGroups, hipHostMallocDefault) != hipSuccess) {
         delete ctx;
         return HSVD_E_DEVICE;
     }
     ctx->host_ctl = static_cast<Ctl *>(h);
     ctx->host_pctl = reinterpret_cast<PersistCtl *>(static_cast<char *>(h) + pctl_at);
+    ctx->host_active = reinterpret_cast<int *>(static_cast<char *>(h) + active_at);
     if (!scratch_address(device)) {
         hipHostFree(h);
         delete ctx;
@@ -363,6 +370,7 @@ hsvd_status hsvd_destroy(hsvd_ctx *ctx)
     if (ctx->aux) hipFree(ctx->aux);
     if (ctx->host_ctl) hipHostFree(ctx->host_ctl);
     if (ctx->cap) hipStreamDestroy(ctx->cap);
+    for (hipStream_t q : ctx->group_streams) hipStreamDestroy(q);
     if (ctx->join) hipEventDestroy(ctx->join);
     delete ctx;
     return HSVD_OK;
@@ -1641,123 +1649,428 @@ extern "C" hsvd_status hsvd_batched_schedule(const hsvd_ctx *ctx, int precision,
     return HSVD_OK;
 }
 
-// FP32 phase of a batched mixed solve for one group, then the
-// J-re-orthogonalisation of each problem's V and G1 = G X -- the steps of a
-// single mixed solve, per problem.  FP32 block sweeps run until every problem
-// has left FP32 by its own switch rule (a problem out of FP32 is skipped by
-// the later FP32 launches); the Newton-Schulz iteration runs on the whole
-// group with the batched FP64 MFMA products, each problem applying its
-// corrections until its own residual stops falling quadratically.  The FP64
-// sweeps then start from (G1, V0 = X), or from G for a problem that restarts
-// (rank flag in its FP32 phase, or a final residual above the accepted one).
-static hsvd_status batch_mixed_phase(hsvd_ctx *ctx, hipStream_t st, const BatchGroup &g, const BatchMixed &m,
-                                     const BlockArgsT<double> &ba, int4 *S2, int pairs, int steps_per_sweep,
-                                     int max_sweeps, bool sort, long long &gstep, int *host_active, int &sweeps32,
-                                     const double *Gin)
-{
-    HSVD_TRY(launch_batch_mixed_init(st, g, m));
+// The problems of one bordered order in launches that cover all of them, with
+// the stop rule decided per problem on the device.  Its phases enqueue work on
+// the group's stream and never wait, so that the sweeps of several groups
+// overlap: a group of a few problems fills a small part of the chip.  24
+// problems of order 257 .. 640, six groups: 55 ms one group after the other,
+// 25 side by side.
+struct GroupJob {
+    const std::vector<int> *ids = nullptr;
+    int K = 0, r = 0, ldg = 0, nb = 0, pairs = 0, steps = 0;  // steps: per sweep
+    bool sort = true, mixed = false, acc_v = true;
+    hipStream_t q = nullptr;
+    int *host_active = nullptr;  // pinned: problems still running
+    bool live = true;            // in the current phase
+    std::vector<int> hn, hp;
+    std::vector<long long> hoff, hvoff;
+    std::vector<double> htol, htth;
+    BatchGroup g, g32;
+    BatchMixed m{};
+    BlockArgs ba;
     BlockArgsT<float> fa;
-    fa.G = m.G32;
-    fa.V = m.V32;
-    fa.ldg = ba.ldg;
-    fa.r = ba.r;
-    fa.p = 0;
-    fa.nb = ba.nb;
-    fa.rho = ba.rho;
-    fa.ordering = ba.ordering;
-    // the FP32 partial Grams and W in the space of the FP64 ones
-    fa.partial = reinterpret_cast<float *>(ba.partial);
-    fa.splits = ba.splits;
-    fa.rows_per_split = ba.rows_per_split;
-    fa.W = reinterpret_cast<float *>(ba.W);
-    fa.active = ba.active;
-    fa.C = ba.C;
-    fa.nrot = ba.nrot;
-    fa.nskip = ba.nskip;
-    fa.nact = ba.nact;
-    fa.ntc = ba.ntc;
-    fa.maxt = ba.maxt;
-    fa.ctl = ba.ctl;
-    fa.tol = 0.0;
-    fa.tthresh = 0.0;
-    fa.inner_sweeps = ba.inner_sweeps;
-    fa.nprob = ba.nprob;
-    fa.done = m.done32;
-    fa.pvec = ba.pvec;
-    fa.tolvec = m.tol32;
-    fa.tthvec = m.tth32;
-    BatchGroup g32 = g;
-    g32.done = m.done32;  // the sort of the FP32 phase skips problems out of it
-    sweeps32 = 0;
-    for (int sw = 0; sw < max_sweeps; ++sw) {
-        for (int k = 0; k < steps_per_sweep; ++k, ++gstep) {
-            fa.step = k;
-            fa.S_in = S2 + (gstep & 1) * pairs;
-            fa.S_out = S2 + ((gstep + 1) & 1) * pairs;
-            HSVD_TRY(launch_block_gram<float>(st, fa));
-            HSVD_TRY(launch_block_inner<float>(st, fa));
-            HSVD_TRY(launch_block_update<float>(st, fa));
+    GemmArgs sy, xt;
+    int4 *S2 = nullptr;
+    long long gstep = 0;
+    hipGraph_t graph = nullptr;
+    hipGraphExec_t exec = nullptr;
+
+    // Device space of the group: its size, and with a base its pointers.
+    size_t bind(char *base)
+    {
+        size_t o = 0;
+        auto take = [&](auto *&ptr, size_t count) {
+            const size_t at = take_bytes(o, sizeof(*ptr) * count);
+            if (base) ptr = reinterpret_cast<std::remove_reference_t<decltype(ptr)>>(base + at);
+        };
+        const size_t k = (size_t)K, mat = (size_t)ldg * r * k, bb = (size_t)4 * block_width() * block_width();
+        const size_t slots = (size_t)pairs * k, mk = mixed ? k : 0, mmat = mixed ? mat : 0;
+        take(g.ids, k);
+        take(g.n, k);
+        take(g.p, k);
+        take(g.done, k);
+        take(g.status, k);
+        take(g.sweeps, k);
+        take(g.off, k);
+        take(g.voff, k);
+        take(g.tol, k);
+        take(g.tth, k);
+        take(g.active_count, 1);
+        take(g.G, mat);
+        take(g.V, acc_v ? mat : 0);
+        take(g.d, (size_t)r * k);
+        take(g.dtmp, (size_t)r * k);
+        take(g.rho, (size_t)r * k);
+        take(g.rtmp, (size_t)r * k);
+        take(g.C, slots);
+        take(g.nrot, slots);
+        take(g.nskip, slots);
+        take(g.nact, slots);
+        take(g.ntc, slots);
+        take(g.maxt, slots);
+        take(g.ctl, k);
+        take(S2, 2 * (size_t)pairs);
+        take(ba.partial, slots * bb);
+        take(ba.W, slots * bb);
+        take(ba.active, slots);
+        // mixed: FP32 copies, the Newton-Schulz products and the per-problem
+        // state (the FP32 partial Grams and W live in the FP64 ones' space)
+        take(m.G32, mmat);
+        take(m.V32, mmat);
+        take(m.T1, mmat);
+        take(m.T2, mmat);
+        take(m.done32, mk);
+        take(m.sweeps32, mk);
+        take(m.prev_maxt, mk);
+        take(m.prev_frac, mk);
+        take(m.tol32, mk);
+        take(m.tth32, mk);
+        take(m.apply, mk);
+        take(m.nsdone, mk);
+        take(m.nsprev, mk);
+        take(m.nsiters, mk);
+        take(m.restart, mk);
+        if (!acc_v) g.V = nullptr;
+        return o;
+    }
+
+    // The group's arguments, its metadata to the device, set-up and the first sort.
+    hipError_t start(const double *G, const hsvd_params &prm, int max_sweeps)
+    {
+        g.nprob = K;
+        g.r = r;
+        g.ldg = ldg;
+        g.pairs = pairs;
+        g.max_sweeps = max_sweeps;
+        ba.G = g.G;
+        ba.V = g.V;
+        ba.ldg = ldg;
+        ba.r = r;
+        ba.p = 0;
+        ba.nb = nb;
+        ba.rho = g.rho;
+        ba.ordering = prm.ordering;
+        ba.splits = 1;
+        ba.rows_per_split = ldg;
+        ba.C = g.C;
+        ba.nrot = g.nrot;
+        ba.nskip = g.nskip;
+        ba.nact = g.nact;
+        ba.ntc = g.ntc;
+        ba.maxt = g.maxt;
+        ba.ctl = g.ctl;
+        ba.tol = 0.0;
+        ba.tthresh = 0.0;
+        ba.inner_sweeps = prm.inner_sweeps;
+        ba.nprob = K;
+        ba.done = g.done;
+        ba.pvec = g.p;
+        ba.tolvec = g.tol;
+        ba.tthvec = g.tth;
+        hipError_t e;
+        auto up = [&](const void *dst, const void *src, size_t bytes) {
+            return hipMemcpyAsync(const_cast<void *>(dst), src, bytes, hipMemcpyHostToDevice, q);
+        };
+        if ((e = up(g.ids, ids->data(), sizeof(int) * K)) != hipSuccess) return e;
+        if ((e = up(g.n, hn.data(), sizeof(int) * K)) != hipSuccess) return e;
+        if ((e = up(g.p, hp.data(), sizeof(int) * K)) != hipSuccess) return e;
+        if ((e = up(g.off, hoff.data(), sizeof(long long) * K)) != hipSuccess) return e;
+        if ((e = up(g.voff, hvoff.data(), sizeof(long long) * K)) != hipSuccess) return e;
+        if ((e = up(g.tol, htol.data(), sizeof(double) * K)) != hipSuccess) return e;
+        if ((e = up(g.tth, htth.data(), sizeof(double) * K)) != hipSuccess) return e;
+        if ((e = launch_batch_setup(q, g, G, acc_v)) != hipSuccess) return e;
+        if ((e = launch_block_stepper_init(q, S2, nb)) != hipSuccess) return e;
+        return sort ? launch_batch_sort(q, g) : hipSuccess;
+    }
+
+    hipError_t count_running()
+    {
+        return hipMemcpyAsync(host_active, g.active_count, sizeof(int), hipMemcpyDeviceToHost, q);
+    }
+
+    // The outer steps of one sweep.
+    template <typename T>
+    hipError_t enqueue_steps(BlockArgsT<T> &a)
+    {
+        for (int k = 0; k < steps; ++k, ++gstep) {
+            a.step = k;
+            a.S_in = S2 + (gstep & 1) * pairs;
+            a.S_out = S2 + ((gstep + 1) & 1) * pairs;
+            hipError_t e;
+            if ((e = launch_block_gram<T>(q, a)) != hipSuccess) return e;
+            if ((e = launch_block_inner<T>(q, a)) != hipSuccess) return e;
+            if ((e = launch_block_update<T>(q, a)) != hipSuccess) return e;
         }
-        HSVD_TRY(launch_batch_colnorm32(st, g, m));
-        if (sort) HSVD_TRY(launch_batch_sort(st, g32));
-        HSVD_TRY(launch_batch_decide32(st, g, m));
-        HSVD_TRY(hipMemcpyAsync(host_active, g.active_count, sizeof(int), hipMemcpyDeviceToHost, st));
-        HSVD_TRY(hipStreamSynchronize(st));
-        ++sweeps32;
-        if (*host_active == 0) break;
+        return hipSuccess;
+    }
+
+    // Mixed precision -- the steps of a single mixed solve, per problem.  FP32
+    // block sweeps run until every problem has left FP32 by its own switch
+    // rule (a problem out of FP32 is skipped by the later FP32 launches); the
+    // Newton-Schulz iteration runs on the whole group with the batched FP64
+    // MFMA products, each problem applying its corrections until its own
+    // residual stops falling quadratically.  The FP64 sweeps then start from
+    // (G1, V0 = X), or from G for a problem that restarts (rank flag in its
+    // FP32 phase, or a final residual above the accepted one).
+    hipError_t mixed_start(const hsvd_params &prm)
+    {
+        m.accept = prm.reorth_accept;
+        fa.G = m.G32;
+        fa.V = m.V32;
+        fa.ldg = ba.ldg;
+        fa.r = ba.r;
+        fa.p = 0;
+        fa.nb = ba.nb;
+        fa.rho = ba.rho;
+        fa.ordering = ba.ordering;
+        // the FP32 partial Grams and W in the space of the FP64 ones
+        fa.partial = reinterpret_cast<float *>(ba.partial);
+        fa.splits = ba.splits;
+        fa.rows_per_split = ba.rows_per_split;
+        fa.W = reinterpret_cast<float *>(ba.W);
+        fa.active = ba.active;
+        fa.C = ba.C;
+        fa.nrot = ba.nrot;
+        fa.nskip = ba.nskip;
+        fa.nact = ba.nact;
+        fa.ntc = ba.ntc;
+        fa.maxt = ba.maxt;
+        fa.ctl = ba.ctl;
+        fa.tol = 0.0;
+        fa.tthresh = 0.0;
+        fa.inner_sweeps = ba.inner_sweeps;
+        fa.nprob = ba.nprob;
+        fa.done = m.done32;
+        fa.pvec = ba.pvec;
+        fa.tolvec = m.tol32;
+        fa.tthvec = m.tth32;
+        g32 = g;
+        g32.done = m.done32;  // the sort of the FP32 phase skips problems out of it
+        return launch_batch_mixed_init(q, g, m);
+    }
+    hipError_t sweep32()
+    {
+        hipError_t e;
+        if ((e = enqueue_steps(fa)) != hipSuccess) return e;
+        if ((e = launch_batch_colnorm32(q, g, m)) != hipSuccess) return e;
+        if (sort && (e = launch_batch_sort(q, g32)) != hipSuccess) return e;
+        if ((e = launch_batch_decide32(q, g, m)) != hipSuccess) return e;
+        return count_running();
     }
     // V = V32 promoted; Newton-Schulz X <- X (3I - J X^T J X) / 2 per problem,
     // on the FP64 MFMA products with the problem in blockIdx.z
-    HSVD_TRY(launch_batch_promote(st, g, m));
-    const int r = g.r, ld = g.ldg;
-    const long long mat = (long long)g.ldg * g.r;
-    GemmArgs sy;  // T2 = X^T J X for the problems still iterating
-    sy.A = g.V;
-    sy.B = g.V;
-    sy.C = m.T2;
-    sy.M = sy.N = sy.K = r;
-    sy.lda = sy.ldb = sy.ldc = ld;
-    sy.sa = sy.sb = sy.sc = mat;
-    sy.pvec = g.p;
-    sy.flag = m.nsdone;
-    sy.want = 0;
-    GemmArgs xt = sy;  // T1 = X T2 where the correction applies
-    xt.B = m.T2;
-    xt.C = m.T1;
-    xt.pvec = nullptr;
-    xt.flag = m.apply;
-    xt.want = 1;
-    for (int it = 0; it <= 6; ++it) {
-        HSVD_TRY(launch_gemm(st, sy, g.nprob, true, true, true));
-        HSVD_TRY(launch_batch_ns_form(st, g, m));  // T2 = (3I - J X^T J X) / 2, residuals
-        HSVD_TRY(launch_batch_ns_decide(st, g, m, it, it == 6));
-        HSVD_TRY(hipMemcpyAsync(host_active, g.active_count, sizeof(int), hipMemcpyDeviceToHost, st));
-        HSVD_TRY(hipStreamSynchronize(st));
-        if (*host_active == 0) break;
-        HSVD_TRY(launch_gemm(st, xt, g.nprob, false, false, false));
-        HSVD_TRY(launch_batch_copy_if(st, g, m.T1, g.V, m.apply, false));
+    hipError_t reorth_start()
+    {
+        sy.A = g.V;  // T2 = X^T J X for the problems still iterating
+        sy.B = g.V;
+        sy.C = m.T2;
+        sy.M = sy.N = sy.K = r;
+        sy.lda = sy.ldb = sy.ldc = ldg;
+        sy.sa = sy.sb = sy.sc = (long long)ldg * r;
+        sy.pvec = g.p;
+        sy.flag = m.nsdone;
+        sy.want = 0;
+        xt = sy;  // T1 = X T2 where the correction applies
+        xt.B = m.T2;
+        xt.C = m.T1;
+        xt.pvec = nullptr;
+        xt.flag = m.apply;
+        xt.want = 1;
+        return launch_batch_promote(q, g, m);
     }
-    // problems whose X is not J-orthogonal to working accuracy (or whose FP32
-    // phase saw a rank flag) restart from G in FP64; the others go on from
-    // G1 = G X (apply marks them)
-    HSVD_TRY(launch_batch_ns_accept(st, g, m));
-    GemmArgs gx = sy;
-    gx.A = g.G;
-    gx.B = g.V;
-    gx.C = m.T1;
-    gx.pvec = nullptr;
-    gx.flag = m.apply;
-    gx.want = 1;
-    HSVD_TRY(launch_gemm(st, gx, g.nprob, false, false, false));
-    HSVD_TRY(launch_batch_copy_if(st, g, m.T1, g.G, m.apply, false));
-    BatchGroup gr = g;
-    gr.only = m.restart;
-    HSVD_TRY(launch_batch_setup(st, gr, Gin, true));
-    // the kept diagonal of G1 and the sort, as after a sweep
-    HSVD_TRY(launch_batch_colnorm(st, g, false));
-    if (sort) HSVD_TRY(launch_batch_sort(st, g));
-    return HSVD_OK;
-}
+    hipError_t reorth_test(int it)
+    {
+        hipError_t e;
+        if ((e = launch_gemm(q, sy, g.nprob, true, true, true)) != hipSuccess) return e;
+        // T2 = (3I - J X^T J X) / 2, residuals
+        if ((e = launch_batch_ns_form(q, g, m)) != hipSuccess) return e;
+        if ((e = launch_batch_ns_decide(q, g, m, it, it == 6)) != hipSuccess) return e;
+        return count_running();
+    }
+    hipError_t reorth_correct()
+    {
+        const hipError_t e = launch_gemm(q, xt, g.nprob, false, false, false);
+        return e != hipSuccess ? e : launch_batch_copy_if(q, g, m.T1, g.V, m.apply, false);
+    }
+    hipError_t reorth_end(const double *Gin)
+    {
+        // problems whose X is not J-orthogonal to working accuracy (or whose
+        // FP32 phase saw a rank flag) restart from G in FP64; the others go on
+        // from G1 = G X (apply marks them)
+        hipError_t e;
+        if ((e = launch_batch_ns_accept(q, g, m)) != hipSuccess) return e;
+        GemmArgs gx = sy;
+        gx.A = g.G;
+        gx.B = g.V;
+        gx.C = m.T1;
+        gx.pvec = nullptr;
+        gx.flag = m.apply;
+        gx.want = 1;
+        if ((e = launch_gemm(q, gx, g.nprob, false, false, false)) != hipSuccess) return e;
+        if ((e = launch_batch_copy_if(q, g, m.T1, g.G, m.apply, false)) != hipSuccess) return e;
+        BatchGroup gr = g;
+        gr.only = m.restart;
+        if ((e = launch_batch_setup(q, gr, Gin, true)) != hipSuccess) return e;
+        // the kept diagonal of G1 and the sort, as after a sweep
+        if ((e = launch_batch_colnorm(q, g, false)) != hipSuccess) return e;
+        return sort ? launch_batch_sort(q, g) : hipSuccess;
+    }
+
+    // One FP64 sweep: the outer steps, the kept diagonal, the sort, the stop rule.
+    hipError_t sweep()
+    {
+        hipError_t e;
+        if ((e = enqueue_steps(ba)) != hipSuccess) return e;
+        if ((e = launch_batch_colnorm(q, g, false)) != hipSuccess) return e;
+        if (sort && (e = launch_batch_sort(q, g)) != hipSuccess) return e;
+        if ((e = launch_batch_reduce_decide(q, g)) != hipSuccess) return e;
+        return count_running();
+    }
+    // The sweep as a graph: steps is even for the modified modulus ordering,
+    // so the stepper's double buffer is in the same phase at every sweep and
+    // one captured sweep serves them all (round-robin keeps no state).
+    hipError_t capture()
+    {
+        hipError_t e = hipStreamBeginCapture(q, hipStreamCaptureModeThreadLocal);
+        if (e != hipSuccess) return e;
+        const long long g0 = gstep;
+        const hipError_t se = sweep();
+        gstep = g0;
+        e = hipStreamEndCapture(q, &graph);
+        if (se != hipSuccess) return se;
+        if (e != hipSuccess) return e;
+        return hipGraphInstantiate(&exec, graph, nullptr, nullptr, 0);
+    }
+    hipError_t run_sweep(bool make_graph)
+    {
+        if (make_graph) {
+            const hipError_t e = capture();
+            if (e != hipSuccess) return e;
+        }
+        if (!exec) return sweep();
+        gstep += steps;
+        return hipGraphLaunch(exec, q);
+    }
+};
+
+// Groups that run side by side, each on a stream of its own that starts after
+// the caller's and that the caller's waits for at the end, whatever happens.
+struct GroupSet {
+    hsvd_ctx *ctx;
+    hipStream_t st;
+    std::vector<GroupJob> jobs;
+    GroupSet(hsvd_ctx *c, hipStream_t s) : ctx(c), st(s) {}
+    GroupSet(const GroupSet &) = delete;
+    GroupSet &operator=(const GroupSet &) = delete;
+    hipError_t open()
+    {
+        hipError_t e;
+        while (ctx->group_streams.size() < jobs.size()) {
+            hipStream_t q = nullptr;
+            if ((e = hipStreamCreateWithFlags(&q, hipStreamNonBlocking)) != hipSuccess) return e;
+            ctx->group_streams.push_back(q);
+        }
+        if (!ctx->join && (e = hipEventCreateWithFlags(&ctx->join, hipEventDisableTiming)) != hipSuccess) return e;
+        if ((e = hipEventRecord(ctx->join, st)) != hipSuccess) return e;
+        for (size_t i = 0; i < jobs.size(); ++i) {
+            if ((e = hipStreamWaitEvent(ctx->group_streams[i], ctx->join, 0)) != hipSuccess) return e;
+            jobs[i].q = ctx->group_streams[i];
+        }
+        return hipSuccess;
+    }
+    ~GroupSet()
+    {
+        for (GroupJob &j : jobs) {
+            if (!j.q) continue;
+            (void)hipStreamSynchronize(j.q);
+            if (j.exec) (void)hipGraphExecDestroy(j.exec);
+            if (j.graph) (void)hipGraphDestroy(j.graph);
+            if (hipEventRecord(ctx->join, j.q) == hipSuccess) (void)hipStreamWaitEvent(st, ctx->join, 0);
+        }
+    }
+    // Rounds of `work` (enqueues one round of a job) until no job has a problem
+    // running, or `limit` rounds.
+    template <typename Work, typename After>
+    hipError_t rounds(int limit, Work work, After after)
+    {
+        hipError_t e;
+        for (GroupJob &j : jobs) j.live = true;
+        for (int it = 0; it < limit; ++it) {
+            bool any = false;
+            for (GroupJob &j : jobs)
+                if (j.live && (e = work(j, it)) != hipSuccess) return e;
+            for (GroupJob &j : jobs) {
+                if (!j.live) continue;
+                if ((e = hipStreamSynchronize(j.q)) != hipSuccess) return e;
+                j.live = *j.host_active != 0;
+                any = any || j.live;
+                if (j.live && (e = after(j)) != hipSuccess) return e;
+            }
+            if (!any) break;
+        }
+        return hipSuccess;
+    }
+    // The whole solve of every job; results per problem into pinfo.
+    hsvd_status run(const double *G, const hsvd_params &prm, int max_sweeps, double *sigma, double *U, double *V,
+                    double *lambda, std::vector<hsvd_info> &pinfo)
+    {
+        const bool mixed = prm.precision == HSVD_MIXED;
+        auto none = [](GroupJob &) { return hipSuccess; };
+        for (GroupJob &j : jobs) HSVD_TRY(j.start(G, prm, max_sweeps));
+        if (mixed) {
+            for (GroupJob &j : jobs) HSVD_TRY(j.mixed_start(prm));
+            HSVD_TRY(rounds(max_sweeps, [](GroupJob &j, int) { return j.sweep32(); }, none));
+            for (GroupJob &j : jobs) HSVD_TRY(j.reorth_start());
+            HSVD_TRY(rounds(7, [](GroupJob &j, int it) { return j.reorth_test(it); },
+                            [](GroupJob &j) { return j.reorth_correct(); }));
+            for (GroupJob &j : jobs) HSVD_TRY(j.reorth_end(G));
+        }
+        const bool graph = prm.graph != 0;
+        HSVD_TRY(rounds(max_sweeps, [graph](GroupJob &j, int it) { return j.run_sweep(graph && it == 0); }, none));
+        for (GroupJob &j : jobs) HSVD_TRY(launch_batch_finalize(j.q, j.g, sigma, U, V, lambda));
+        for (GroupJob &j : jobs) {
+            const int K = j.K;
+            std::vector<int> hs(K), hsw(K), h32(K), hni(K), hrs(K);
+            std::vector<double> hres(K);
+            std::vector<Ctl> hctl(K);
+            auto down = [&](void *dst, const void *src, size_t bytes) {
+                return hipMemcpyAsync(dst, src, bytes, hipMemcpyDeviceToHost, j.q);
+            };
+            HSVD_TRY(down(hs.data(), j.g.status, sizeof(int) * K));
+            HSVD_TRY(down(hsw.data(), j.g.sweeps, sizeof(int) * K));
+            HSVD_TRY(down(hctl.data(), j.g.ctl, sizeof(Ctl) * K));
+            if (mixed) {
+                // per-problem FP32 sweeps, corrections, final residuals, restarts
+                HSVD_TRY(down(h32.data(), j.m.sweeps32, sizeof(int) * K));
+                HSVD_TRY(down(hni.data(), j.m.nsiters, sizeof(int) * K));
+                HSVD_TRY(down(hrs.data(), j.m.restart, sizeof(int) * K));
+                HSVD_TRY(down(hres.data(), j.m.nsprev, sizeof(double) * K));
+            }
+            HSVD_TRY(hipStreamSynchronize(j.q));
+            for (int z = 0; z < K; ++z) {
+                hsvd_info &pi = pinfo[(*j.ids)[z]];
+                pi.status = hs[z];
+                pi.sweeps = hsw[z];
+                pi.code = hctl[z].code;
+                pi.r = j.r;
+                pi.block = block_width();
+                pi.ldg = j.ldg;
+                pi.max_t_last = hctl[z].maxt;
+                pi.rotations = (long long)hctl[z].rot;
+                pi.skips = (long long)hctl[z].skip;
+                pi.steps = (long long)hsw[z] * j.steps;
+                pi.active_pairs = (long long)hctl[z].act;
+                if (mixed) {
+                    pi.sweeps_fp32 = h32[z];
+                    pi.reorth_iters = hni[z];
+                    pi.fp64_restart = hrs[z];
+                    pi.reorth_resid = hres[z] <= 1.0 ? hres[z] : 0.0;
+                }
+            }
+        }
+        return HSVD_OK;
+    }
+};
 
 // The problems `ids` (FP64, block-oriented, n <= kPersistMaxOrder) in one
 // persistent launch: a work queue of the problem indices, largest n first
@@ -1952,14 +2265,29 @@ extern "C" hsvd_status hsvd_solve_batched(hsvd_ctx *ctx, int batch, const int *n
     if (s != HSVD_OK) return s;
     hipEvent_t *ev = ctx->events.data();
 
-    // FP64 block-oriented problems with n <= kPersistMaxOrder: one persistent
-    // launch (batch_mode 0); the others grouped by bordered order r = n
-    // rounded up to 2b, one sequence of launches per group
+    int cus = 0;
+    HSVD_TRY(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, ctx->device));
+    // block-oriented problems with n <= kPersistMaxOrder: one persistent launch
+    // (batch_mode 0); the others grouped by bordered order r = n rounded up to
+    // 2b, one sequence of launches per group
     std::vector<int> pers;
     std::vector<std::vector<int>> groups(1024 / (2 * b) + 1);
     // batch_mode 2: the schedule the autotuner chose for this precision, else
-    // the persistent launch
-    const int sched = prm.batch_mode == 2 ? std::max(0, ctx->batch_sched[mixed ? 1 : 0]) : prm.batch_mode;
+    // the persistent launch, but for few FP64 problems (bit-identical in both)
+    // the grouped ones, whose launches spread a problem's block pairs over the
+    // chip.  ms, persistent / grouped: 16 problems of n ~ U{8..256} 13.5 / 6.3,
+    // 300 15.4 / 12.0, 500 17.9 / 20.6; U{250..256} 16 14.1 / 5.1, 300 32.8 /
+    // 23.6, 500 37.3 / 37.0; U{65..128} 100 4.0 / 3.0, 200 4.2 / 4.3, 300 5.3 /
+    // 5.4; U{8..64} 100 1.7 / 1.6, 300 1.9 / 2.2.
+    int few = 0, few_max = 0;
+    for (int k = 0; k < batch; ++k)
+        if (n[k] <= kPersistMaxOrder) {
+            ++few;
+            few_max = std::max(few_max, n[k]);
+        }
+    const int untuned = !mixed && few <= (few_max > 128 ? 5 * cus / 4 : cus / 2) ? 1 : 0;
+    const int tuned = ctx->batch_sched[mixed ? 1 : 0];
+    const int sched = prm.batch_mode == 2 ? (tuned >= 0 ? tuned : untuned) : prm.batch_mode;
     const bool persist_ok = prm.inner_sweeps == 0 && sched == 0;
     for (int k = 0; k < batch; ++k) {
         if (persist_ok && n[k] <= kPersistMaxOrder)
@@ -1975,266 +2303,52 @@ extern "C" hsvd_status hsvd_solve_batched(hsvd_ctx *ctx, int batch, const int *n
     s = batch_persistent(ctx, st, pers, n.data(), p.data(), off.data(), voff.data(), G, prm, max_sweeps, want_v, sigma,
                          U, V, lambda, pinfo);
     if (s != HSVD_OK) return s;
-    for (size_t gi = 1; gi < groups.size(); ++gi) {
-        const std::vector<int> &ids = groups[gi];
-        if (ids.empty()) continue;
-        const int K = (int)ids.size();
-        const int r = (int)gi * 2 * b, ldg = r, nb = r / b, pairs = nb / 2;
-        const int steps_per_sweep = prm.ordering == HSVD_ORD_MODMOD ? nb : nb - 1;
-        const size_t mat = (size_t)ldg * r, bb = (size_t)4 * b * b;
-        // workspace of the group
-        size_t o = 0;
-        const size_t o_ids = take_bytes(o, sizeof(int) * K), o_n = take_bytes(o, sizeof(int) * K);
-        const size_t o_p = take_bytes(o, sizeof(int) * K), o_done = take_bytes(o, sizeof(int) * K);
-        const size_t o_stat = take_bytes(o, sizeof(int) * K), o_sw = take_bytes(o, sizeof(int) * K);
-        const size_t o_off = take_bytes(o, sizeof(long long) * K), o_voff = take_bytes(o, sizeof(long long) * K);
-        const size_t o_tol = take_bytes(o, sizeof(double) * K), o_tth = take_bytes(o, sizeof(double) * K);
-        const size_t o_cnt = take_bytes(o, sizeof(int));
-        const size_t o_G = take_bytes(o, sizeof(double) * mat * K);
-        const size_t o_V = take_bytes(o, acc_v ? sizeof(double) * mat * K : 0);
-        const size_t o_d = take_bytes(o, sizeof(double) * r * K), o_dt = take_bytes(o, sizeof(double) * r * K);
-        const size_t o_rho = take_bytes(o, sizeof(int) * r * K), o_rt = take_bytes(o, sizeof(int) * r * K);
-        const size_t o_C = take_bytes(o, sizeof(int) * pairs * K);
-        const size_t o_nr = take_bytes(o, sizeof(unsigned) * pairs * K);
-        const size_t o_ns = take_bytes(o, sizeof(unsigned) * pairs * K);
-        const size_t o_na = take_bytes(o, sizeof(unsigned) * pairs * K);
-        const size_t o_ntc = take_bytes(o, sizeof(unsigned) * pairs * K);
-        const size_t o_mt = take_bytes(o, sizeof(double) * pairs * K);
-        const size_t o_ctl = take_bytes(o, sizeof(Ctl) * K);
-        const size_t o_S2 = take_bytes(o, sizeof(int4) * 2 * pairs);
-        const size_t o_P = take_bytes(o, sizeof(double) * pairs * bb * K);
-        const size_t o_W = take_bytes(o, sizeof(double) * pairs * bb * K);
-        const size_t o_act = take_bytes(o, sizeof(unsigned long long) * pairs * K);
-        // mixed: FP32 copies, the Newton-Schulz products and the per-problem
-        // state (the FP32 partial Grams and W live in the FP64 ones' space)
-        const size_t mx_mat = mixed ? mat * K : 0, mx_k = mixed ? (size_t)K : 0;
-        const size_t o_G32 = take_bytes(o, sizeof(float) * mx_mat), o_V32 = take_bytes(o, sizeof(float) * mx_mat);
-        const size_t o_T1 = take_bytes(o, sizeof(double) * mx_mat), o_T2 = take_bytes(o, sizeof(double) * mx_mat);
-        const size_t o_d32 = take_bytes(o, sizeof(int) * mx_k), o_s32 = take_bytes(o, sizeof(int) * mx_k);
-        const size_t o_pm = take_bytes(o, sizeof(double) * mx_k), o_pf = take_bytes(o, sizeof(double) * mx_k);
-        const size_t o_t32 = take_bytes(o, sizeof(double) * mx_k), o_h32 = take_bytes(o, sizeof(double) * mx_k);
-        const size_t o_ap = take_bytes(o, sizeof(int) * mx_k), o_nd = take_bytes(o, sizeof(int) * mx_k);
-        const size_t o_np = take_bytes(o, sizeof(double) * mx_k);
-        const size_t o_ni = take_bytes(o, sizeof(int) * mx_k), o_rs = take_bytes(o, sizeof(int) * mx_k);
-        s = ensure_ws(ctx, o);
+    // Groups run side by side as long as their block pairs together are few
+    // (four per compute unit: beyond, each fills the chip by itself and only
+    // the workspace would grow).
+    for (size_t gi = 1; gi < groups.size();) {
+        GroupSet set(ctx, st);
+        long long total = 0;
+        for (; gi < groups.size(); ++gi) {
+            const std::vector<int> &ids = groups[gi];
+            if (ids.empty()) continue;
+            const long long slots = (long long)ids.size() * (long long)gi;
+            if (!set.jobs.empty() && total + slots > 4LL * cus) break;
+            total += slots;
+            GroupJob j;
+            j.ids = &ids;
+            j.K = (int)ids.size();
+            j.r = j.ldg = (int)gi * 2 * b;
+            j.nb = j.r / b;
+            j.pairs = j.nb / 2;
+            j.steps = prm.ordering == HSVD_ORD_MODMOD ? j.nb : j.nb - 1;
+            j.sort = prm.sort != 0;
+            j.mixed = mixed;
+            j.acc_v = acc_v;
+            for (int k : ids) {
+                const double tol = prm.tol > 0.0 ? prm.tol : 1e-15 * n[k];
+                j.hn.push_back(n[k]);
+                j.hp.push_back(p[k]);
+                j.hoff.push_back(off[k]);
+                j.hvoff.push_back(voff[k]);
+                j.htol.push_back(tol);
+                j.htth.push_back(prm.t_thresh > 0.0 ? prm.t_thresh : sqrt(tol) / 2.0);
+            }
+            set.jobs.push_back(std::move(j));
+        }
+        if (set.jobs.empty()) break;
+        size_t bytes = 0;
+        std::vector<size_t> at;
+        for (GroupJob &j : set.jobs) at.push_back(take_bytes(bytes, j.bind(nullptr)));
+        s = ensure_ws(ctx, bytes);
         if (s != HSVD_OK) return s;
-        char *base = static_cast<char *>(ctx->ws);
-        // per-problem metadata
-        std::vector<int> hn(K), hp(K);
-        std::vector<long long> hoff(K), hvoff(K);
-        std::vector<double> htol(K), htth(K);
-        for (int z = 0; z < K; ++z) {
-            const int k = ids[z];
-            hn[z] = n[k];
-            hp[z] = p[k];
-            hoff[z] = off[k];
-            hvoff[z] = voff[k];
-            htol[z] = prm.tol > 0.0 ? prm.tol : 1e-15 * n[k];
-            htth[z] = prm.t_thresh > 0.0 ? prm.t_thresh : sqrt(htol[z]) / 2.0;
+        for (size_t i = 0; i < set.jobs.size(); ++i) {
+            set.jobs[i].bind(static_cast<char *>(ctx->ws) + at[i]);
+            set.jobs[i].host_active = ctx->host_active + i;
         }
-        HSVD_TRY(hipMemcpyAsync(base + o_ids, ids.data(), sizeof(int) * K, hipMemcpyHostToDevice, st));
-        HSVD_TRY(hipMemcpyAsync(base + o_n, hn.data(), sizeof(int) * K, hipMemcpyHostToDevice, st));
-        HSVD_TRY(hipMemcpyAsync(base + o_p, hp.data(), sizeof(int) * K, hipMemcpyHostToDevice, st));
-        HSVD_TRY(hipMemcpyAsync(base + o_off, hoff.data(), sizeof(long long) * K, hipMemcpyHostToDevice, st));
-        HSVD_TRY(hipMemcpyAsync(base + o_voff, hvoff.data(), sizeof(long long) * K, hipMemcpyHostToDevice, st));
-        HSVD_TRY(hipMemcpyAsync(base + o_tol, htol.data(), sizeof(double) * K, hipMemcpyHostToDevice, st));
-        HSVD_TRY(hipMemcpyAsync(base + o_tth, htth.data(), sizeof(double) * K, hipMemcpyHostToDevice, st));
-        HSVD_TRY(hipStreamSynchronize(st));
-
-        BatchGroup g;
-        g.nprob = K;
-        g.r = r;
-        g.ldg = ldg;
-        g.pairs = pairs;
-        g.max_sweeps = max_sweeps;
-        g.ids = reinterpret_cast<int *>(base + o_ids);
-        g.n = reinterpret_cast<int *>(base + o_n);
-        g.p = reinterpret_cast<int *>(base + o_p);
-        g.off = reinterpret_cast<long long *>(base + o_off);
-        g.voff = reinterpret_cast<long long *>(base + o_voff);
-        g.tol = reinterpret_cast<double *>(base + o_tol);
-        g.tth = reinterpret_cast<double *>(base + o_tth);
-        g.done = reinterpret_cast<int *>(base + o_done);
-        g.status = reinterpret_cast<int *>(base + o_stat);
-        g.sweeps = reinterpret_cast<int *>(base + o_sw);
-        g.active_count = reinterpret_cast<int *>(base + o_cnt);
-        g.G = reinterpret_cast<double *>(base + o_G);
-        g.V = acc_v ? reinterpret_cast<double *>(base + o_V) : nullptr;
-        g.d = reinterpret_cast<double *>(base + o_d);
-        g.dtmp = reinterpret_cast<double *>(base + o_dt);
-        g.rho = reinterpret_cast<int *>(base + o_rho);
-        g.rtmp = reinterpret_cast<int *>(base + o_rt);
-        g.C = reinterpret_cast<int *>(base + o_C);
-        g.nrot = reinterpret_cast<unsigned *>(base + o_nr);
-        g.nskip = reinterpret_cast<unsigned *>(base + o_ns);
-        g.nact = reinterpret_cast<unsigned *>(base + o_na);
-        g.ntc = reinterpret_cast<unsigned *>(base + o_ntc);
-        g.maxt = reinterpret_cast<double *>(base + o_mt);
-        g.ctl = reinterpret_cast<Ctl *>(base + o_ctl);
-        int4 *S2 = reinterpret_cast<int4 *>(base + o_S2);
-
-        HSVD_TRY(launch_batch_setup(st, g, G, acc_v));
-        HSVD_TRY(launch_block_stepper_init(st, S2, nb));
-        if (prm.sort) HSVD_TRY(launch_batch_sort(st, g));
-
-        BlockArgs ba;
-        ba.G = g.G;
-        ba.V = g.V;
-        ba.ldg = ldg;
-        ba.r = r;
-        ba.p = 0;
-        ba.nb = nb;
-        ba.rho = g.rho;
-        ba.ordering = prm.ordering;
-        ba.partial = reinterpret_cast<double *>(base + o_P);
-        ba.splits = 1;
-        ba.rows_per_split = ldg;
-        ba.W = reinterpret_cast<double *>(base + o_W);
-        ba.active = reinterpret_cast<unsigned long long *>(base + o_act);
-        ba.C = g.C;
-        ba.nrot = g.nrot;
-        ba.nskip = g.nskip;
-        ba.nact = g.nact;
-        ba.ntc = g.ntc;
-        ba.maxt = g.maxt;
-        ba.ctl = g.ctl;
-        ba.tol = 0.0;
-        ba.tthresh = 0.0;
-        ba.inner_sweeps = prm.inner_sweeps;
-        ba.nprob = K;
-        ba.done = g.done;
-        ba.pvec = g.p;
-        ba.tolvec = g.tol;
-        ba.tthvec = g.tth;
-        long long gstep = 0;
-        int gsweeps = 0;
-        int *host_active = &ctx->host_ctl->code;  // pinned scratch for the count of running problems
-        if (mixed) {
-            BatchMixed m;
-            m.G32 = reinterpret_cast<float *>(base + o_G32);
-            m.V32 = reinterpret_cast<float *>(base + o_V32);
-            m.T1 = reinterpret_cast<double *>(base + o_T1);
-            m.T2 = reinterpret_cast<double *>(base + o_T2);
-            m.done32 = reinterpret_cast<int *>(base + o_d32);
-            m.sweeps32 = reinterpret_cast<int *>(base + o_s32);
-            m.prev_maxt = reinterpret_cast<double *>(base + o_pm);
-            m.prev_frac = reinterpret_cast<double *>(base + o_pf);
-            m.tol32 = reinterpret_cast<double *>(base + o_t32);
-            m.tth32 = reinterpret_cast<double *>(base + o_h32);
-            m.apply = reinterpret_cast<int *>(base + o_ap);
-            m.nsdone = reinterpret_cast<int *>(base + o_nd);
-            m.nsprev = reinterpret_cast<double *>(base + o_np);
-            m.nsiters = reinterpret_cast<int *>(base + o_ni);
-            m.restart = reinterpret_cast<int *>(base + o_rs);
-            m.accept = prm.reorth_accept;
-            int sw32 = 0;
-            s = batch_mixed_phase(ctx, st, g, m, ba, S2, pairs, steps_per_sweep, max_sweeps, prm.sort != 0, gstep,
-                                  host_active, sw32, G);
-            if (s != HSVD_OK) return s;
-            // per-problem FP32 sweeps, corrections, final residuals, restarts
-            std::vector<int> h32(K), hni(K), hrs(K);
-            std::vector<double> hres(K);
-            HSVD_TRY(hipMemcpyAsync(h32.data(), m.sweeps32, sizeof(int) * K, hipMemcpyDeviceToHost, st));
-            HSVD_TRY(hipMemcpyAsync(hni.data(), m.nsiters, sizeof(int) * K, hipMemcpyDeviceToHost, st));
-            HSVD_TRY(hipMemcpyAsync(hrs.data(), m.restart, sizeof(int) * K, hipMemcpyDeviceToHost, st));
-            HSVD_TRY(hipMemcpyAsync(hres.data(), m.nsprev, sizeof(double) * K, hipMemcpyDeviceToHost, st));
-            HSVD_TRY(hipStreamSynchronize(st));
-            for (int z = 0; z < K; ++z) {
-                hsvd_info &pi = pinfo[ids[z]];
-                pi.sweeps_fp32 = h32[z];
-                pi.reorth_iters = hni[z];
-                pi.fp64_restart = hrs[z];
-                pi.reorth_resid = hres[z] <= 1.0 ? hres[z] : 0.0;
-            }
-        }
-        // one sweep: the outer steps, the kept diagonal, the sort, the stop rule
-        auto enqueue_sweep = [&](hipStream_t q, bool timed) -> hipError_t {
-            for (int k = 0; k < steps_per_sweep; ++k, ++gstep) {
-                ba.step = k;
-                ba.S_in = S2 + (gstep & 1) * pairs;
-                ba.S_out = S2 + ((gstep + 1) & 1) * pairs;
-                hipEvent_t *e = ev + 4 + 4 * k;
-                hipError_t er;
-                if (timed && (er = hipEventRecord(e[0], q)) != hipSuccess) return er;
-                if ((er = launch_block_gram<double>(q, ba)) != hipSuccess) return er;
-                if (timed && (er = hipEventRecord(e[1], q)) != hipSuccess) return er;
-                if ((er = launch_block_inner<double>(q, ba)) != hipSuccess) return er;
-                if (timed && (er = hipEventRecord(e[2], q)) != hipSuccess) return er;
-                if ((er = launch_block_update<double>(q, ba)) != hipSuccess) return er;
-                if (timed && (er = hipEventRecord(e[3], q)) != hipSuccess) return er;
-            }
-            hipError_t er;
-            if ((er = launch_batch_colnorm(q, g, false)) != hipSuccess) return er;
-            if (prm.sort && (er = launch_batch_sort(q, g)) != hipSuccess) return er;
-            if ((er = launch_batch_reduce_decide(q, g)) != hipSuccess) return er;
-            return hipMemcpyAsync(host_active, g.active_count, sizeof(int), hipMemcpyDeviceToHost, q);
-        };
-        hipGraphExec_t exec = nullptr;
-        hipGraph_t graph = nullptr;
-        hipStream_t q = st;
-        if (prm.graph) {
-            // steps_per_sweep is even for the modified modulus ordering, so the
-            // stepper's double buffer is in the same phase at every sweep and
-            // one captured sweep serves them all (round-robin keeps no state)
-            if (!ctx->cap) HSVD_TRY(hipStreamCreateWithFlags(&ctx->cap, hipStreamNonBlocking));
-            if (!ctx->join) HSVD_TRY(hipEventCreateWithFlags(&ctx->join, hipEventDisableTiming));
-            q = ctx->cap;
-            HSVD_TRY(hipEventRecord(ctx->join, st));
-            HSVD_TRY(hipStreamWaitEvent(q, ctx->join, 0));
-            HSVD_TRY(hipStreamBeginCapture(q, hipStreamCaptureModeThreadLocal));
-            const long long g0 = gstep;
-            const hipError_t ce = enqueue_sweep(q, false);
-            gstep = g0;
-            hipError_t ee = hipStreamEndCapture(q, &graph);
-            if (ce != hipSuccess || ee != hipSuccess) {
-                if (graph) hipGraphDestroy(graph);
-                return HSVD_E_DEVICE;
-            }
-            if (hipGraphInstantiate(&exec, graph, nullptr, nullptr, 0) != hipSuccess) {
-                hipGraphDestroy(graph);
-                return HSVD_E_DEVICE;
-            }
-        }
-        for (int sw = 0; sw < max_sweeps; ++sw) {
-            if (prm.graph) {
-                HSVD_TRY(hipGraphLaunch(exec, q));
-                gstep += steps_per_sweep;
-            } else {
-                HSVD_TRY(enqueue_sweep(q, false));
-            }
-            HSVD_TRY(hipStreamSynchronize(q));
-            const int active = *host_active;
-            ++gsweeps;
-            if (active == 0) break;
-        }
-        if (prm.graph) {
-            hipGraphExecDestroy(exec);
-            hipGraphDestroy(graph);
-            HSVD_TRY(hipEventRecord(ctx->join, q));
-            HSVD_TRY(hipStreamWaitEvent(st, ctx->join, 0));
-        }
-        HSVD_TRY(launch_batch_finalize(st, g, sigma, U, want_v ? V : nullptr, lambda));
-        std::vector<int> hs(K), hsw(K);
-        std::vector<Ctl> hctl(K);
-        HSVD_TRY(hipMemcpyAsync(hs.data(), g.status, sizeof(int) * K, hipMemcpyDeviceToHost, st));
-        HSVD_TRY(hipMemcpyAsync(hsw.data(), g.sweeps, sizeof(int) * K, hipMemcpyDeviceToHost, st));
-        HSVD_TRY(hipMemcpyAsync(hctl.data(), g.ctl, sizeof(Ctl) * K, hipMemcpyDeviceToHost, st));
-        HSVD_TRY(hipStreamSynchronize(st));
-        for (int z = 0; z < K; ++z) {
-            hsvd_info &pi = pinfo[ids[z]];
-            pi.status = hs[z];
-            pi.sweeps = hsw[z];
-            pi.code = hctl[z].code;
-            pi.r = r;
-            pi.block = b;
-            pi.ldg = ldg;
-            pi.max_t_last = hctl[z].maxt;
-            pi.rotations = (long long)hctl[z].rot;
-            pi.skips = (long long)hctl[z].skip;
-            pi.steps = (long long)hsw[z] * steps_per_sweep;
-            pi.active_pairs = (long long)hctl[z].act;
-        }
-        (void)gsweeps;
+        HSVD_TRY(set.open());
+        s = set.run(G, prm, max_sweeps, sigma, U, want_v ? V : nullptr, lambda, pinfo);
+        if (s != HSVD_OK) return s;
     }
     HSVD_TRY(hipEventRecord(ev[1], st));
     HSVD_TRY(hipStreamSynchronize(st));
