@@ -13,6 +13,7 @@
 #include <algorithm>
 #include <mutex>
 #include <new>
+#include <thread>
 #include <type_traits>
 #include <utility>
 #include <vector>
@@ -1654,14 +1655,14 @@ extern "C" hsvd_status hsvd_batched_schedule(const hsvd_ctx *ctx, int precision,
 // the group's stream and never wait, so that the sweeps of several groups
 // overlap: a group of a few problems fills a small part of the chip.  24
 // problems of order 257 .. 640, six groups: 55 ms one group after the other,
-// 25 side by side.
+// 27 side by side (30 when the groups waited for each other after every sweep,
+// 34 with two groups to a stream).
 struct GroupJob {
     const std::vector<int> *ids = nullptr;
     int K = 0, r = 0, ldg = 0, nb = 0, pairs = 0, steps = 0;  // steps: per sweep
     bool sort = true, mixed = false, acc_v = true;
     hipStream_t q = nullptr;
     int *host_active = nullptr;  // pinned: problems still running
-    bool live = true;            // in the current phase
     std::vector<int> hn, hp;
     std::vector<long long> hoff, hvoff;
     std::vector<double> htol, htth;
@@ -1674,6 +1675,9 @@ struct GroupJob {
     long long gstep = 0;
     hipGraph_t graph = nullptr;
     hipGraphExec_t exec = nullptr;
+
+    // A sweep's time, in steps that leave the chip partly idle.
+    double load() const { return steps * (1.0 + (double)pairs * K / 256.0); }
 
     // Device space of the group: its size, and with a base its pointers.
     size_t bind(char *base)
@@ -1953,8 +1957,8 @@ struct GroupJob {
     }
 };
 
-// Groups that run side by side, each on a stream of its own that starts after
-// the caller's and that the caller's waits for at the end, whatever happens.
+// Groups that run side by side, on streams that start after the caller's and
+// that the caller's waits for at the end, whatever happens.
 struct GroupSet {
     hsvd_ctx *ctx;
     hipStream_t st;
@@ -1962,6 +1966,8 @@ struct GroupSet {
     GroupSet(hsvd_ctx *c, hipStream_t s) : ctx(c), st(s) {}
     GroupSet(const GroupSet &) = delete;
     GroupSet &operator=(const GroupSet &) = delete;
+    // A stream per group, the longest first (HIP deals a few hardware queues to
+    // the streams, and groups on one queue take turns).
     hipError_t open()
     {
         hipError_t e;
@@ -1972,6 +1978,7 @@ struct GroupSet {
         }
         if (!ctx->join && (e = hipEventCreateWithFlags(&ctx->join, hipEventDisableTiming)) != hipSuccess) return e;
         if ((e = hipEventRecord(ctx->join, st)) != hipSuccess) return e;
+        std::stable_sort(jobs.begin(), jobs.end(), [](const GroupJob &x, const GroupJob &y) { return x.load() > y.load(); });
         for (size_t i = 0; i < jobs.size(); ++i) {
             if ((e = hipStreamWaitEvent(ctx->group_streams[i], ctx->join, 0)) != hipSuccess) return e;
             jobs[i].q = ctx->group_streams[i];
@@ -1988,25 +1995,39 @@ struct GroupSet {
             if (hipEventRecord(ctx->join, j.q) == hipSuccess) (void)hipStreamWaitEvent(st, ctx->join, 0);
         }
     }
-    // Rounds of `work` (enqueues one round of a job) until no job has a problem
-    // running, or `limit` rounds.
+    // Rounds of `work` (enqueues one round of a job), each job at its own pace,
+    // until it has no problem running, or `limit` rounds.
     template <typename Work, typename After>
     hipError_t rounds(int limit, Work work, After after)
     {
         hipError_t e;
-        for (GroupJob &j : jobs) j.live = true;
-        for (int it = 0; it < limit; ++it) {
-            bool any = false;
-            for (GroupJob &j : jobs)
-                if (j.live && (e = work(j, it)) != hipSuccess) return e;
-            for (GroupJob &j : jobs) {
-                if (!j.live) continue;
-                if ((e = hipStreamSynchronize(j.q)) != hipSuccess) return e;
-                j.live = *j.host_active != 0;
-                any = any || j.live;
-                if (j.live && (e = after(j)) != hipSuccess) return e;
+        std::vector<int> done(jobs.size(), 0);
+        size_t running = limit > 0 ? jobs.size() : 0;
+        for (size_t i = 0; i < running; ++i)
+            if ((e = work(jobs[i], 0)) != hipSuccess) return e;
+        std::vector<char> live(jobs.size(), 1);
+        while (running > 0) {
+            for (size_t i = 0; i < jobs.size(); ++i) {
+                if (!live[i]) continue;
+                GroupJob &j = jobs[i];
+                if (running == 1) {
+                    if ((e = hipStreamSynchronize(j.q)) != hipSuccess) return e;
+                } else if ((e = hipStreamQuery(j.q)) == hipErrorNotReady) {
+                    (void)hipGetLastError();  // not an error of a later launch
+                    std::this_thread::yield();
+                    continue;
+                } else if (e != hipSuccess) {
+                    return e;
+                }
+                live[i] = *j.host_active != 0;
+                if (live[i] && (e = after(j)) != hipSuccess) return e;
+                if (live[i] && ++done[i] < limit) {
+                    if ((e = work(j, done[i])) != hipSuccess) return e;
+                } else {
+                    live[i] = 0;
+                    --running;
+                }
             }
-            if (!any) break;
         }
         return hipSuccess;
     }
@@ -2110,7 +2131,7 @@ static hsvd_status batch_persistent(hsvd_ctx *ctx, hipStream_t st, const std::ve
     const size_t o_act = take_bytes(o, sizeof(unsigned long long) * batch);
     const size_t o_s32 = take_bytes(o, sizeof(int) * batch), o_ni = take_bytes(o, sizeof(int) * batch);
     const size_t o_rs = take_bytes(o, sizeof(int) * batch), o_nr = take_bytes(o, sizeof(double) * batch);
-    const size_t o_slots = take_bytes(o, persist_slot_bytes() * (size_t)wgs);
+    const size_t o_slots = take_bytes(o, persist_slot_bytes(prm.precision == HSVD_MIXED) * (size_t)wgs);
     hsvd_status s = ensure_ws(ctx, o);
     if (s != HSVD_OK) return s;
     char *base = static_cast<char *>(ctx->ws);
@@ -2275,10 +2296,11 @@ extern "C" hsvd_status hsvd_solve_batched(hsvd_ctx *ctx, int batch, const int *n
     // batch_mode 2: the schedule the autotuner chose for this precision, else
     // the persistent launch, but for few FP64 problems (bit-identical in both)
     // the grouped ones, whose launches spread a problem's block pairs over the
-    // chip.  ms, persistent / grouped: 16 problems of n ~ U{8..256} 13.5 / 6.3,
-    // 300 15.4 / 12.0, 500 17.9 / 20.6; U{250..256} 16 14.1 / 5.1, 300 32.8 /
-    // 23.6, 500 37.3 / 37.0; U{65..128} 100 4.0 / 3.0, 200 4.2 / 4.3, 300 5.3 /
-    // 5.4; U{8..64} 100 1.7 / 1.6, 300 1.9 / 2.2.
+    // chip.  ms, persistent / grouped: 16 problems of n ~ U{8..256} 13.5 / 5.5,
+    // 300 15.6 / 11.6, 500 18.1 / 17.7; U{250..256} 16 14.0 / 5.0, 300 33.0 /
+    // 22.9, 500 37.6 / 35.1; U{100..220} 300 16.7 / 12.4, 500 20.0 / 21.8;
+    // U{65..128} 100 4.0 / 3.0, 200 4.2 / 4.3, 300 5.3 / 5.4; U{8..64} 100 1.7
+    // / 1.6, 300 1.9 / 2.2.
     int few = 0, few_max = 0;
     for (int k = 0; k < batch; ++k)
         if (n[k] <= kPersistMaxOrder) {
@@ -2338,15 +2360,16 @@ extern "C" hsvd_status hsvd_solve_batched(hsvd_ctx *ctx, int batch, const int *n
         }
         if (set.jobs.empty()) break;
         size_t bytes = 0;
-        std::vector<size_t> at;
-        for (GroupJob &j : set.jobs) at.push_back(take_bytes(bytes, j.bind(nullptr)));
+        for (GroupJob &j : set.jobs) take_bytes(bytes, j.bind(nullptr));
         s = ensure_ws(ctx, bytes);
         if (s != HSVD_OK) return s;
-        for (size_t i = 0; i < set.jobs.size(); ++i) {
-            set.jobs[i].bind(static_cast<char *>(ctx->ws) + at[i]);
-            set.jobs[i].host_active = ctx->host_active + i;
-        }
         HSVD_TRY(set.open());
+        bytes = 0;
+        for (size_t i = 0; i < set.jobs.size(); ++i) {
+            GroupJob &j = set.jobs[i];
+            j.bind(static_cast<char *>(ctx->ws) + take_bytes(bytes, j.bind(nullptr)));
+            j.host_active = ctx->host_active + i;
+        }
         s = set.run(G, prm, max_sweeps, sigma, U, want_v ? V : nullptr, lambda, pinfo);
         if (s != HSVD_OK) return s;
     }

@@ -236,7 +236,7 @@ struct SlotLayout {
     size_t G, V, P, W, d, rho, S, C, nrot, nskip, nact, ntc, maxt, active, ctl, G32, V32, T1, T2, bytes;
 };
 
-__host__ __device__ inline SlotLayout slot_layout()
+__host__ __device__ inline SlotLayout slot_layout(bool mixed)
 {
     SlotLayout s;
     size_t o = 0;
@@ -262,11 +262,11 @@ __host__ __device__ inline SlotLayout slot_layout()
     s.active = take(sizeof(unsigned long long) * kPMaxPairs);
     s.ctl = take(sizeof(Ctl));
     // mixed precision: FP32 working copies, FP64 product scratch
-    const size_t mat32 = sizeof(float) * (size_t)kPMaxR * kPMaxR;
+    const size_t mat32 = mixed ? sizeof(float) * (size_t)kPMaxR * kPMaxR : 0;
     s.G32 = take(mat32);
     s.V32 = take(mat32);
-    s.T1 = take(mat);
-    s.T2 = take(mat);
+    s.T1 = take(mixed ? mat : 0);
+    s.T2 = take(mixed ? mat : 0);
     s.bytes = o;
     return s;
 }
@@ -331,7 +331,7 @@ __device__ void persist_solve(const PersistArgs &pa, int z, char *slot, PersistL
 {
     constexpr int NT = 256 * GR;
     const int tid = threadIdx.x;
-    const SlotLayout sl = slot_layout();
+    const SlotLayout sl = slot_layout(pa.mixed != 0);
     const int n = pa.n[z], p = pa.p[z];
     const int r = (n + kB2 - 1) / kB2 * kB2, ldg = r, nb = r / kB, pairs = nb / 2;
     const int steps_per_sweep = pa.ordering == HSVD_ORD_MODMOD ? nb : nb - 1;
@@ -719,7 +719,7 @@ template <int GR>
 __global__ __launch_bounds__(256 * GR, 4) void batch_persist_kernel(PersistArgs pa)
 {
     __shared__ int s_idx;
-    char *slot = pa.slots + (size_t)blockIdx.x * slot_layout().bytes;
+    char *slot = pa.slots + (size_t)blockIdx.x * slot_layout(pa.mixed != 0).bytes;
     for (;;) {
         if (threadIdx.x == 0) s_idx = atomicAdd(pa.next, 1);
         __syncthreads();
@@ -732,7 +732,7 @@ __global__ __launch_bounds__(256 * GR, 4) void batch_persist_kernel(PersistArgs 
 
 __global__ void persist_zero_kernel(int *next) { *next = 0; }
 
-size_t persist_slot_bytes() { return slot_layout().bytes; }
+size_t persist_slot_bytes(bool mixed) { return slot_layout(mixed).bytes; }
 
 int persist_blocks_per_cu(int threads)
 {

@@ -55,15 +55,15 @@ __global__ __launch_bounds__(256) void block_gram_kernel(BlockArgsT<T> a)
     gram_pair<T>(a, blockIdx.x, blockIdx.y, red, threadIdx.x);
 }
 
-template <typename T>
-__global__ __launch_bounds__(1024) void block_inner_circle_kernel(BlockArgsT<T> a)
+template <typename T, int NT>
+__global__ __launch_bounds__(NT, 4) void block_inner_circle_kernel(BlockArgsT<T> a)
 {
     __shared__ CircleLds L;
     if (!bind_problem(a)) return;
-    inner_circle_pair<T, 1024>(a, blockIdx.x, L, threadIdx.x);
+    inner_circle_pair<T, NT>(a, blockIdx.x, L, threadIdx.x);
 }
 
-// With NT = kCrossThreads (single solves) the workgroups after the block
+// With NT = kCrossThreads and a single solve the workgroups after the block
 // pairs' own apply the previous outer step's W to V (v_update_role).
 constexpr int kCrossThreads = 512;
 template <typename T, int NT>
@@ -221,21 +221,31 @@ hipError_t launch_block_gram(hipStream_t st, const BlockArgsT<T> &a)
 
 int v_update_role_wgs(int pairs, int ldg) { return pairs * ((ldg + kRoleRows - 1) / kRoleRows); }
 
+// Threads per block pair of an inner launch: with more pairs than the 256
+// compute units hold one of each, throughput counts -- 256 threads, whose four
+// waves share the work about evenly, four pairs per compute unit -- and below
+// it latency.  FP64 us per launch, 64 / 1024 pairs: cross 16.4 with 512
+// threads, 19.0 / 52 with 256; circle 45 / 180 with 1024, 70 / 120 with 256.
+constexpr int kWidePairs = 256;
+
 template <typename T>
 hipError_t launch_block_inner(hipStream_t st, const BlockArgsT<T> &a)
 {
+    const int total = a.nb / 2 * a.nprob;
     // only the cross steps carry V-update workgroups (the first step of a
     // sweep has no previous step in it; the full-block method updates V in
     // its update launches)
     if (a.step == 0 || a.inner_sweeps > 0) {
         if (a.vprev_wgs > 0) return hipErrorInvalidValue;
-        block_inner_circle_kernel<T><<<dim3(a.nb / 2, 1, a.nprob), 1024, 0, st>>>(a);
+        const dim3 grid(a.nb / 2, 1, a.nprob);
+        if (total > 2 * kWidePairs)
+            block_inner_circle_kernel<T, 256><<<grid, 256, 0, st>>>(a);
+        else
+            block_inner_circle_kernel<T, 1024><<<grid, 1024, 0, st>>>(a);
         return hipGetLastError();
     }
     if (a.vprev_wgs > 0 && a.nprob > 1) return hipErrorInvalidValue;
-    if (a.nprob > 1) {
-        // batched: throughput over latency -- 256 threads per block pair, its
-        // four waves sharing the work about evenly, four pairs per CU
+    if (a.nprob > 1 && total > kWidePairs) {
         block_inner_cross_kernel<T, 256><<<dim3(a.nb / 2, 1, a.nprob), 256, 0, st>>>(a);
     } else {
         block_inner_cross_kernel<T, kCrossThreads><<<dim3(a.nb / 2 + a.vprev_wgs, 1, a.nprob), kCrossThreads, 0, st>>>(a);

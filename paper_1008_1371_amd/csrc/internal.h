@@ -591,7 +591,7 @@ struct PersistArgs {
     double *nsres = nullptr;
     char *slots = nullptr;
 };
-size_t persist_slot_bytes();
+size_t persist_slot_bytes(bool mixed);
 // Resident workgroups per compute unit at 256, 512 or 1024 threads each (one
 // block pair at a time per 256 threads); 0 for another count.
 int persist_blocks_per_cu(int threads);

@@ -23,13 +23,12 @@ def _run(ctx, ns, Gs, **prm):
 # compute unit, 256 of them: 700 problems of one pair, 300 of two, the rest),
 # as graphs and as stream launches.  A problem's mixed trajectory depends on
 # its group's sweeps only.
-@pytest.mark.parametrize("graph", [1, 0])
 @pytest.mark.parametrize("precision", [0, 1])
-@pytest.mark.parametrize("orders", [[300], [40, 100, 180, 250, 310, 390, 450], [33] * 700 + [65] * 300 + [130, 257, 700]])
+@pytest.mark.parametrize("orders,graph", [([300], 1), ([300], 0), ([40, 100, 180, 250, 310, 390, 450], 1),
+                                          ([40, 100, 180, 250, 310, 390, 450], 0),
+                                          ([33] * 700 + [65] * 300 + [130, 257, 700], 1)])
 def test_groups_side_by_side(hsvd_ctx, orders, precision, graph):
     import torch
-    if len(orders) > 100 and not graph:
-        pytest.skip("the large batch once")
     say("groups", len(orders), precision, graph)
     Gs = [W.gaussian(n, seed=k) for k, n in enumerate(orders)]
     prm = dict(precision=precision, graph=graph, batch_mode=1)
