@@ -90,7 +90,7 @@ def parse():
                     help="block width of the FP64 block path (0: the library's default, 32); 64 runs the wide "
                          "block path, FP64 only")
     ap.add_argument("--persistent", type=int, default=0, choices=[0, 1, 2],
-                    help="pairwise path: 0 one launch per step (graph replay), 1 one persistent launch with "
+                    help="pairwise path: 0 launches of one step or of tiles (graph replay), 1 one persistent launch with "
                          "per-column readiness between steps, 2 the same with a grid barrier per step")
     ap.add_argument("--also", default="graded4096_k1e6_p0.5",
                     help="a second workload timed beside the headline (mixed and FP64, errors against its stored "
