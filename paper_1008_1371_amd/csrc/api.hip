@@ -2250,7 +2250,7 @@ extern "C" hsvd_status hsvd_solve_batched(hsvd_ctx *ctx, int batch, const int *n
                                           const long long *off_in, const long long *voff_in, const double *G,
                                           const hsvd_params *prm_in, double *sigma, double *U, double *V,
                                           double *lambda, hsvd_info *info)
-{
+try {
     if (!ctx || batch < 0) return HSVD_E_INVAL;
     if (batch == 0) return HSVD_OK;
     if (!n_in || !p_in || !off_in || !voff_in || !G || !sigma) return HSVD_E_INVAL;
@@ -2387,6 +2387,8 @@ extern "C" hsvd_status hsvd_solve_batched(hsvd_ctx *ctx, int batch, const int *n
         HSVD_TRY(hipStreamSynchronize(st));
     }
     return result;
+} catch (const std::bad_alloc &) {
+    return HSVD_E_NOMEM;  // host memory; streams of a group have been waited for
 }
 
 extern "C" {
