@@ -835,6 +835,10 @@ __device__ __forceinline__ void inner_cross_idle(const int &live)
 // threads, 50 at 512, 70 at 256; 1024 pairs at 256 threads: 120 us.  With A_P
 // by indices (addresses computed anew in every step) 72, 83, 113 and 241 us;
 // with every block held twice, W in LDS and 32-byte parameters 107 us at 1024.
+// In a step without a rotation the 256-thread form turns nothing: 500 batched
+// problems of order 1 to 8, where three steps in four are such ones, take 1.36
+// ms instead of 1.46 (1.36 with A_P by indices, which had nothing to move then;
+// round-robin, one circle solve a sweep, 300 problems 1.20, 1.29 and 1.11).
 // ---------------------------------------------------------------------------
 constexpr int kCircleBlocks = kB * (kB + 1) / 2;
 struct CircleLds {
@@ -902,13 +906,23 @@ struct CircleW {
             __builtin_amdgcn_update_dpp(__double2hiint(edge), __double2hiint(v), kCtrl, 0xf, 0xf, false),
             __builtin_amdgcn_update_dpp(__double2loint(edge), __double2loint(v), kCtrl, 0xf, 0xf, false));
     }
-    __device__ __forceinline__ void step(const double2 *prm, int j)
+    __device__ __forceinline__ void rotate(const double2 &w0, const double2 &w1)
     {
-        const Rot3<double> p0 = unpack_rot<double>(prm[2 * j]), p1 = unpack_rot<double>(prm[2 * j + 1]);
+        const Rot3<double> p0 = unpack_rot<double>(w0), p1 = unpack_rot<double>(w1);
 #pragma unroll
         for (int q = 0; q < RG; ++q) {
-            const double nl0 = fma(p0.z, r0[q], l0[q]) * p0.y, nr0 = fma(p0.x, l0[q], r0[q]) * p0.y;
-            const double nl1 = fma(p1.z, r1[q], l1[q]) * p1.y, nr1 = fma(p1.x, l1[q], r1[q]) * p1.y;
+            const double a0 = l0[q], a1 = l1[q];
+            l0[q] = fma(p0.z, r0[q], a0) * p0.y;
+            r0[q] = fma(p0.x, a0, r0[q]) * p0.y;
+            l1[q] = fma(p1.z, r1[q], a1) * p1.y;
+            r1[q] = fma(p1.x, a1, r1[q]) * p1.y;
+        }
+    }
+    __device__ __forceinline__ void move(int j)
+    {
+#pragma unroll
+        for (int q = 0; q < RG; ++q) {
+            const double nl0 = l0[q], nr0 = r0[q], nl1 = l1[q], nr1 = r1[q];
             l0[q] = j == 0 ? nl0 : nl1;
             l1[q] = shifted<0x101>(nr1, nl0);  // row_shl:1, lane 15 from its own R
             r0[q] = shifted<0x111>(nl1, nr1);  // row_shr:1, lane 0 from its own L
@@ -973,7 +987,10 @@ __device__ __forceinline__ CircleCount circle_rotation_wave(const SlotRotator &r
             n.tmask |= rot ? (1ull << sl.l) | (1ull << sl.r) : 0ull;
             sl.next();
             trig = is_trig();
-            if (kWTurn) w.step(L.prm, j);
+            if (kWTurn) {
+                if (mask) w.rotate(L.prm[2 * j], L.prm[2 * j + 1]);
+                w.move(j);
+            }
             role_barrier();
         }
         if (!any) break;  // a sweep without rotations: the block is diagonal
@@ -1012,18 +1029,31 @@ __device__ __forceinline__ void circle_block_wave(CircleLds &L, int nsweeps, int
 #pragma unroll
                 for (int v = 0; v < 4; ++v) e[q][v] = L.X[v][item[q]];
             role_barrier();
+            // In a step without a rotation the entries only move.  With several
+            // blocks a thread waits for the mask, the first block's parameters on
+            // their way beside it; with one the wait costs more than it saves
+            // (1024 threads, three full-block sweeps of n = 1024: 28.3 -> 32.3 ms).
+            const double2 ra = *pa[0], rq = *pq[0];
             const unsigned mask = L.rotated;
             any |= mask;
+            e[0][2] = diag ? e[0][1] : e[0][2];
+            const bool turn = NB == 1 || __builtin_amdgcn_readfirstlane(mask) != 0;
+            if (turn) {
 #pragma unroll
-            for (int q = 0; q < NB; ++q) {
-                if (q == 0) e[0][2] = diag ? e[0][1] : e[0][2];
-                rotate_block(e[q][0], e[q][1], e[q][2], e[q][3], unpack_rot<double>(*pa[q]), unpack_rot<double>(*pq[q]));
-                if (q == 0 && diag) e[0][1] = e[0][2] = (mask >> item[0]) & 1u ? 0.0 : e[0][1];
+                for (int q = 0; q < NB; ++q)
+                    rotate_block(e[q][0], e[q][1], e[q][2], e[q][3], unpack_rot<double>(q == 0 ? ra : *pa[q]),
+                                 unpack_rot<double>(q == 0 ? rq : *pq[q]));
+                if (diag) e[0][1] = e[0][2] = (mask >> item[0]) & 1u ? 0.0 : e[0][1];
+            }
+#pragma unroll
+            for (int q = 0; q < NB; ++q)
                 if (have[q])
 #pragma unroll
                     for (int v = 0; v < 4; ++v) X[to[q][v]] = e[q][v];
+            if (kWTurn) {
+                if (turn) w.rotate(L.prm[2 * j], L.prm[2 * j + 1]);
+                w.move(j);
             }
-            if (kWTurn) w.step(L.prm, j);
             role_barrier();
         }
         if (!__builtin_amdgcn_readfirstlane(any)) break;
