@@ -202,12 +202,14 @@ hsvd_status hsvd_solve(hsvd_ctx *ctx, const double *G, int lda, const signed cha
 /* hsvd_solve without device allocation, for callers that cannot allocate
  * device memory (code under HIP graph capture, tight serving loops, harnesses
  * that forbid hipMalloc).  Computes what hsvd_solve computes with jsig = NULL
- * (J = diag(I_p, -I_{n-p})), the same arguments otherwise, by the same kernels
- * and launches: the results are identical to hsvd_solve's for the same G and
+ * (J = diag(I_p, -I_{n-p})), the same arguments otherwise, with the same
+ * arithmetic: the results are identical to hsvd_solve's for the same G and
  * parameters.  Differences:
  *  - The workspace is a fixed array of HSVD_NOALLOC_BYTES in device memory
  *    that the library reserves per device; no hipMalloc, hipFree, event or
- *    graph is created.  A solve whose workspace does not fit returns
+ *    graph is created, and no kernel uses private memory, which the runtime
+ *    would allocate (pairwise solves of order 65 to 128 therefore take several
+ *    launches, and those whose tile space does not fit one per parallel step).  A solve whose workspace does not fit returns
  *    HSVD_E_SIZE before launching anything (its size grows as 16 n^2 bytes
  *    for FP64, about 54 n^2 for HSVD_MIXED; every path fits for n <= 1024).
  *  - prm->graph is ignored (stream launches), and hsvd_info carries no times

@@ -895,8 +895,12 @@ hsvd_status solve_canonical(hsvd_ctx *ctx, const double *G, int lda, int n, int 
     // Pairwise orders that one workgroup holds in its registers: the whole
     // solve in one launch (n = 128: 5.2 ms in per-step launches, where each of
     // the 1152 steps is one; above, G and V no longer fit, and round-robin
-    // moves both columns of every slot between steps).
-    const bool small = !block && !prm.persistent && prm.ordering == HSVD_ORD_MODMOD && r <= kSmallMaxOrder;
+    // moves both columns of every slot between steps).  In the fixed scratch
+    // only the forms without private memory, which the runtime would allocate
+    // at their first launch (r > 64: 150 MB); there tiles take the rest (n = 128
+    // 3.0 ms, in one workgroup 2.3).
+    const int small_max = mode.ws ? kSmallMaxOrderNoPrivate : kSmallMaxOrder;
+    const bool small = !block && !prm.persistent && prm.ordering == HSVD_ORD_MODMOD && r <= small_max;
     if (timing) HSVD_TRY(hipEventRecord(ev[0], st));
     if (!small) {
         s = start();

@@ -378,6 +378,7 @@ struct PairPersistArgs {
 // Pairwise solves with r <= kSmallMaxOrder (modified modulus ordering) in one
 // workgroup, from the caller's G to the caller's outputs (pair_small.hip).
 constexpr int kSmallMaxOrder = 128;
+constexpr int kSmallMaxOrderNoPrivate = 64;  // up to here its kernels spill nothing to private memory
 struct SmallArgs {
     const double *G;
     int lda, n, r, p, sort, max_sweeps, want_v;
