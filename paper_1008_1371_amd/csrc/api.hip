@@ -280,6 +280,16 @@ using namespace hsvd;
         if (e_ != hipSuccess) return HSVD_E_DEVICE; \
     } while (0)
 
+// Device memory; on failure the runtime's last error is cleared, which the next
+// launch's check -- of the library or of the caller -- would take for its own.
+static hsvd_status device_alloc(void **p, size_t bytes)
+{
+    if (hipMalloc(p, bytes) == hipSuccess) return HSVD_OK;
+    (void)hipGetLastError();
+    *p = nullptr;
+    return HSVD_E_NOMEM;
+}
+
 static hsvd_status ensure_ws(hsvd_ctx *ctx, size_t bytes)
 {
     if (ctx->ws_bytes >= bytes) return HSVD_OK;
@@ -289,11 +299,9 @@ static hsvd_status ensure_ws(hsvd_ctx *ctx, size_t bytes)
         ctx->ws = nullptr;
         ctx->ws_bytes = 0;
     }
-    void *p = nullptr;
-    if (hipMalloc(&p, bytes) != hipSuccess) return HSVD_E_NOMEM;
-    ctx->ws = p;
-    ctx->ws_bytes = bytes;
-    return HSVD_OK;
+    const hsvd_status s = device_alloc(&ctx->ws, bytes);
+    if (s == HSVD_OK) ctx->ws_bytes = bytes;
+    return s;
 }
 
 static hsvd_status ensure_events(hsvd_ctx *ctx, size_t count)
@@ -1361,9 +1369,9 @@ hsvd_status ensure_aux(hsvd_ctx *ctx, size_t bytes)
         ctx->aux = nullptr;
         ctx->aux_bytes = 0;
     }
-    if (hipMalloc(&ctx->aux, bytes) != hipSuccess) return HSVD_E_NOMEM;
-    ctx->aux_bytes = bytes;
-    return HSVD_OK;
+    const hsvd_status s = device_alloc(&ctx->aux, bytes);
+    if (s == HSVD_OK) ctx->aux_bytes = bytes;
+    return s;
 }
 
 }  // namespace
