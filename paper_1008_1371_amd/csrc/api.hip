@@ -2128,7 +2128,7 @@ static hsvd_status batch_persistent(hsvd_ctx *ctx, hipStream_t st, const std::ve
         ctx->persist_threads[bucket] ? ctx->persist_threads[bucket] : persist_default_threads(K, nmax, cus);
     const int per_cu = persist_blocks_per_cu(threads);
     if (per_cu < 1 || cus < 1) return HSVD_E_DEVICE;
-    const int wgs = std::min(K, per_cu * cus);
+    int wgs = std::min(K, per_cu * cus);
     // the work queue: problem indices by n, largest first (stable)
     std::vector<int> order(ids);
     std::stable_sort(order.begin(), order.end(), [&](int x, int y) { return n[x] > n[y]; });
@@ -2143,8 +2143,12 @@ static hsvd_status batch_persistent(hsvd_ctx *ctx, hipStream_t st, const std::ve
     const size_t o_act = take_bytes(o, sizeof(unsigned long long) * batch);
     const size_t o_s32 = take_bytes(o, sizeof(int) * batch), o_ni = take_bytes(o, sizeof(int) * batch);
     const size_t o_rs = take_bytes(o, sizeof(int) * batch), o_nr = take_bytes(o, sizeof(double) * batch);
-    const size_t o_slots = take_bytes(o, persist_slot_bytes(prm.precision == HSVD_MIXED) * (size_t)wgs);
-    hsvd_status s = ensure_ws(ctx, o);
+    const size_t o_slots = o;
+    // fewer workgroups where memory is short: the results do not depend on them
+    hsvd_status s;
+    while ((s = ensure_ws(ctx, o_slots + persist_slot_bytes(prm.precision == HSVD_MIXED) * (size_t)wgs)) == HSVD_E_NOMEM &&
+           wgs > 1)
+        wgs = (wgs + 1) / 2;
     if (s != HSVD_OK) return s;
     char *base = static_cast<char *>(ctx->ws);
     HSVD_TRY(hipMemcpyAsync(base + o_order, order.data(), sizeof(int) * K, hipMemcpyHostToDevice, st));
@@ -2372,8 +2376,15 @@ try {
         }
         if (set.jobs.empty()) break;
         size_t bytes = 0;
-        for (GroupJob &j : set.jobs) take_bytes(bytes, j.bind(nullptr));
-        s = ensure_ws(ctx, bytes);
+        for (;;) {
+            bytes = 0;
+            for (GroupJob &j : set.jobs) take_bytes(bytes, j.bind(nullptr));
+            s = ensure_ws(ctx, bytes);
+            if (s != HSVD_E_NOMEM || set.jobs.size() == 1) break;
+            // too little memory for all of them at once: the last one in the next set
+            gi = (size_t)set.jobs.back().pairs;
+            set.jobs.pop_back();
+        }
         if (s != HSVD_OK) return s;
         HSVD_TRY(set.open());
         bytes = 0;
