@@ -89,8 +89,9 @@ typedef struct {
                         one persistent launch (the others, and the full-block
                         method, in launches grouped by bordered order); 1 =
                         grouped launches for every problem; 2 (default) = the
-                        schedule hsvd_autotune_batched chose for the precision;
-                        before tuning 0, but for few FP64 problems 1.  FP64: 0
+                        schedule hsvd_autotune_batched chose for the precision
+                        on a batch of about as many problems; else 0, but for
+                        few FP64 problems 1.  FP64: 0
                         and 1 give bit-identical results.  Mixed: each gives a valid mixed trajectory (the
                         FP64 sweeps of a problem start at the stepper phase its
                         own FP32 sweeps left, in the grouped launches at the
@@ -248,15 +249,15 @@ hsvd_status hsvd_solve_noalloc(hsvd_ctx *ctx, const double *G, int lda, int n, i
  *                    whole batched call; the kernel_* arrays are zero.
  * Problems of the block-oriented method with n <= 256 run in one persistent
  * launch (prm->batch_mode = 0; with the default 2 when hsvd_autotune_batched
- * chose it for the precision, or before tuning unless the problems are few and
- * FP64; captured as a HIP graph when prm->graph is set): each workgroup takes
- * problems from a device work queue, largest n first, and solves each one completely -- Gram, inner rotations
- * and update of every block pair, sort and the stop rule of eq. (4.2) per
- * sweep; with mixed precision first the FP32 sweeps, the switch rule and the
+ * chose it for the precision, or without its choice unless the problems are few
+ * and FP64; captured as a HIP graph when prm->graph is set): each workgroup
+ * takes problems from a device work queue, largest n first, and solves each one
+ * completely -- Gram, inner rotations and update of every block pair, sort and
+ * the stop rule of eq. (4.2) per sweep; with mixed precision first the FP32 sweeps, the switch rule and the
  * J-re-orthogonalisation of V -- then output extraction, with no host round
  * trip.  The other problems (n > 256, the full-block method, batch_mode = 1,
- * or 2 when tuning chose the grouped launches or, before tuning, for few FP64
- * problems) are grouped by their bordered order (a multiple of 2b); each
+ * or 2 when tuning chose the grouped launches or, without its choice, for few
+ * FP64 problems) are grouped by their bordered order (a multiple of 2b); each
  * group runs as one sequence of launches that covers all of its problems,
  * with the stop rule decided per problem on the device, groups of few problems
  * side by side on streams of the context (forked from its stream and joined to
@@ -287,13 +288,15 @@ hsvd_status hsvd_autotune(hsvd_ctx *ctx, int n, int *best_algo, int *best_wg);
 /* Autotuner of the batched solver.  Block-oriented problems with n <= 256 run
  * in one persistent launch in which each workgroup solves whole problems;
  * its width (256, 512 or 1024 threads per problem: one, two or four of its
- * block pairs at a time) is a speed-only choice.  This call times the three widths on a sample of at most 4096 of the
- * given problems (every k-th, the ones with n <= 256; seeded synthetic entries,
- * uniform in [-1, 1) from a counter-based hash; V accumulated) and keeps the
- * fastest for the bucket of the sample's largest order ((0, 64], (64, 128],
- * (128, 192], (192, 256]) in the context; later hsvd_solve_batched calls whose
- * persistent problems fall in that bucket use it (before tuning the width follows
- * from the number of problems and the largest order).
+ * block pairs at a time) is a speed-only choice.  This call times the three
+ * widths on a sample of at most 4096 of the given problems (every k-th, the
+ * ones with n <= 256; seeded synthetic entries, uniform in [-1, 1) from a
+ * counter-based hash; V accumulated) and keeps the fastest in the context, for
+ * the bucket of the sample's largest order ((0, 64], (64, 128], (128, 192],
+ * (192, 256]) and the class of the number of problems with n <= 256 (per
+ * compute unit: up to 1/2, 5/4, 3, 7, above); later hsvd_solve_batched calls
+ * whose persistent problems fall in both use it, and in others the width
+ * follows from the number of problems and the largest order.
  * The results of a batched solve do not depend on the width (bit-identical).
  * Then, with the chosen width, it times the two sweep schedules (one persistent
  * launch, launches grouped by order; batch_mode 0 and 1) in FP64 and in mixed
@@ -301,10 +304,11 @@ hsvd_status hsvd_autotune(hsvd_ctx *ctx, int n, int *best_algo, int *best_wg);
  * 16384 of them (every k-th beyond; seeded synthetic entries as above: the
  * grouped launches gain with the number of problems per group, so a small
  * sample would not tell) and keeps the faster per precision for
- * hsvd_solve_batched calls with batch_mode = 2 (hsvd_batched_schedule reports
- * the choice).  Its inputs and outputs take three times their packed size in
+ * hsvd_solve_batched calls with batch_mode = 2 and a number of problems with
+ * n <= 256 in the same class (hsvd_batched_schedule reports the choice).  Its inputs and outputs take three times their packed size in
  * the context's auxiliary device buffer, kept until hsvd_destroy.  With HSVD_AUTOTUNE_CACHE
- * set the choices are written to that file too.
+ * set the choices are written to that file too (entries of a file without a
+ * class of the number of problems hold for every class).
  *   n, p          device or host arrays of `batch` entries (as hsvd_solve_batched).
  *   best_threads  host, may be NULL: the chosen width.
  *   ms            host, may be NULL: 3 floats, the time of each width (ms).
@@ -312,10 +316,12 @@ hsvd_status hsvd_autotune(hsvd_ctx *ctx, int n, int *best_algo, int *best_wg);
 hsvd_status hsvd_autotune_batched(hsvd_ctx *ctx, int batch, const int *n, const int *p, int *best_threads,
                                   float *ms);
 
-/* The sweep schedule hsvd_solve_batched takes with batch_mode = 2 for
- * `precision` (HSVD_FP64 or HSVD_MIXED): *mode = 0 (one persistent launch),
- * 1 (launches grouped by order), or -1 (not tuned: the persistent launch, or
- * the grouped ones for few FP64 problems).
+/* The sweep schedule that hsvd_autotune_batched chose last, or that hsvd_init
+ * read from the cache file, for `precision` (HSVD_FP64 or HSVD_MIXED):
+ * hsvd_solve_batched takes it with batch_mode = 2 for batches of the class that
+ * it was timed on.  *mode = 0 (one persistent launch), 1 (launches grouped by
+ * order), or -1 (not tuned: the persistent launch, or the grouped ones for few
+ * FP64 problems).
  * Errors: HSVD_E_INVAL (ctx or mode NULL, another precision). */
 hsvd_status hsvd_batched_schedule(const hsvd_ctx *ctx, int precision, int *mode);
 

@@ -18,6 +18,7 @@
 #include <utility>
 #include <vector>
 
+#include "batch_tune.h"
 #include "internal.h"
 
 struct hsvd_ctx {
@@ -37,13 +38,7 @@ struct hsvd_ctx {
     struct Tune {
         int valid = 0, algo = 0, wg = 0;
     } tune[16];                              // autotuner choice per size bucket (log2 of n, rounded up)
-    // threads per workgroup of the persistent batched kernel, by the bucket of
-    // the largest order in the launch ((0, 64], (64, 128], (128, 192],
-    // (192, 256]); 0 = the default
-    int persist_threads[4] = {0, 0, 0, 0};
-    // sweep schedule of batch_mode 2 per precision (FP64, mixed): 0 = one
-    // persistent launch, 1 = launches grouped by order; -1 = not tuned
-    int batch_sched[2] = {-1, -1};
+    hsvd::BatchTune batch_tune;              // autotuner choices of the batched solver
 };
 
 // Fixed device scratch of hsvd_solve_noalloc: the workspace of one solve,
@@ -106,20 +101,7 @@ void tune_load(hsvd_ctx *ctx)
             ctx->tune[b].wg = w;
         }
     }
-    // {"batched_bucket": B, "threads": T}
-    for (const char *q = strstr(buf, "\"batched_bucket\""); q; q = strstr(q + 1, "\"batched_bucket\"")) {
-        int b = -1, t = 0;
-        if (sscanf(q, "\"batched_bucket\": %d, \"threads\": %d", &b, &t) == 2 && b >= 0 && b < 4 &&
-            (t == 256 || t == 512 || t == 1024))
-            ctx->persist_threads[b] = t;
-    }
-    // {"batched_schedule": P, "mode": M}
-    for (const char *q = strstr(buf, "\"batched_schedule\""); q; q = strstr(q + 1, "\"batched_schedule\"")) {
-        int pr = -1, m = -1;
-        if (sscanf(q, "\"batched_schedule\": %d, \"mode\": %d", &pr, &m) == 2 && (pr == 0 || pr == 1) &&
-            (m == 0 || m == 1))
-            ctx->batch_sched[pr] = m;
-    }
+    ctx->batch_tune.read(buf);
 }
 
 void tune_save(const hsvd_ctx *ctx)
@@ -136,16 +118,7 @@ void tune_save(const hsvd_ctx *ctx)
                 ctx->tune[b].wg);
         first = false;
     }
-    for (int b = 0; b < 4; ++b) {
-        if (!ctx->persist_threads[b]) continue;
-        fprintf(f, "%s\n  {\"batched_bucket\": %d, \"threads\": %d}", first ? "" : ",", b, ctx->persist_threads[b]);
-        first = false;
-    }
-    for (int pr = 0; pr < 2; ++pr) {
-        if (ctx->batch_sched[pr] < 0) continue;
-        fprintf(f, "%s\n  {\"batched_schedule\": %d, \"mode\": %d}", first ? "" : ",", pr, ctx->batch_sched[pr]);
-        first = false;
-    }
+    ctx->batch_tune.write(f, first);
     fprintf(f, "\n]}\n");
     fclose(f);
 }
@@ -1564,13 +1537,19 @@ extern "C" hsvd_status hsvd_autotune_batched(hsvd_ctx *ctx, int batch, const int
     hsvd_params prm;
     hsvd_default_params(&prm);
     prm.batch_mode = 0;  // the widths are the persistent launch's
-    const int bucket = std::min(3, (nmax - 1) / 64);
-    const int saved = ctx->persist_threads[bucket];
+    // the choices hold for batches of about this many problems
+    int cus = 0, small = 0;
+    HSVD_TRY(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, ctx->device));
+    for (int k = 0; k < batch; ++k) small += n[k] <= kPersistMaxOrder ? 1 : 0;
+    const int count_class = BatchTune::count_class(small, cus);
+    // (the sample may fall in another class: a candidate stands for all of them)
+    const BatchTune saved = ctx->batch_tune;
+    int *const widths = ctx->batch_tune.threads[BatchTune::order_class(nmax)];
     const int cands[3] = {256, 512, 1024};
     int best = cands[0];
     float best_ms = 1e30f;
     for (int ci = 0; ci < 3; ++ci) {
-        ctx->persist_threads[bucket] = cands[ci];
+        std::fill(widths, widths + BatchTune::kCounts, cands[ci]);
         float ms = 0.f;
         for (int rep = 0; rep < 2; ++rep) {  // the first run also warms up
             HSVD_TRY(hipEventRecord(ev[0], st));
@@ -1579,7 +1558,7 @@ extern "C" hsvd_status hsvd_autotune_batched(hsvd_ctx *ctx, int batch, const int
                                    reinterpret_cast<double *>(base + o_s), reinterpret_cast<double *>(base + o_U),
                                    reinterpret_cast<double *>(base + o_V), nullptr, nullptr);
             if (s != HSVD_OK && s != HSVD_E_NOCONV) {
-                ctx->persist_threads[bucket] = saved;
+                ctx->batch_tune = saved;
                 return s;
             }
             HSVD_TRY(hipEventRecord(ev[1], st));
@@ -1592,7 +1571,8 @@ extern "C" hsvd_status hsvd_autotune_batched(hsvd_ctx *ctx, int batch, const int
             best = cands[ci];
         }
     }
-    ctx->persist_threads[bucket] = best;
+    ctx->batch_tune = saved;
+    widths[count_class] = best;
     // The sweep schedule per precision, with the chosen width: one persistent
     // launch against launches grouped by order, timed on the problems whose
     // schedule it decides (n <= kPersistMaxOrder), all of them up to 16384
@@ -1600,8 +1580,6 @@ extern "C" hsvd_status hsvd_autotune_batched(hsvd_ctx *ctx, int batch, const int
     // problems per group, so a small sample would not tell.
     std::vector<int> an, ap;
     {
-        int small = 0;
-        for (int k = 0; k < batch; ++k) small += n[k] <= kPersistMaxOrder ? 1 : 0;
         const int stride2 = (small + 16383) / 16384;
         int seen = 0;
         for (int k = 0; k < batch; ++k) {
@@ -1648,7 +1626,7 @@ extern "C" hsvd_status hsvd_autotune_batched(hsvd_ctx *ctx, int batch, const int
                 HSVD_TRY(hipEventElapsedTime(&sched_ms[mode], ev[0], ev[1]));
             }
         }
-        ctx->batch_sched[pr] = sched_ms[1] < sched_ms[0] ? 1 : 0;
+        ctx->batch_tune.sched[pr][count_class] = ctx->batch_tune.last[pr] = sched_ms[1] < sched_ms[0] ? 1 : 0;
     }
     tune_save(ctx);
     if (best_threads) *best_threads = best;
@@ -1658,7 +1636,7 @@ extern "C" hsvd_status hsvd_autotune_batched(hsvd_ctx *ctx, int batch, const int
 extern "C" hsvd_status hsvd_batched_schedule(const hsvd_ctx *ctx, int precision, int *mode)
 {
     if (!ctx || !mode || (precision != HSVD_FP64 && precision != HSVD_MIXED)) return HSVD_E_INVAL;
-    *mode = ctx->batch_sched[precision == HSVD_MIXED ? 1 : 0];
+    *mode = ctx->batch_tune.last[precision == HSVD_MIXED ? 1 : 0];
     return HSVD_OK;
 }
 
@@ -2123,9 +2101,7 @@ static hsvd_status batch_persistent(hsvd_ctx *ctx, hipStream_t st, const std::ve
     HSVD_TRY(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, ctx->device));
     int nmax = 0;
     for (int k : ids) nmax = std::max(nmax, n[k]);
-    const int bucket = std::min(3, (nmax - 1) / 64);
-    const int threads =
-        ctx->persist_threads[bucket] ? ctx->persist_threads[bucket] : persist_default_threads(K, nmax, cus);
+    const int threads = ctx->batch_tune.threads_for(K, nmax, cus);
     const int per_cu = persist_blocks_per_cu(threads);
     if (per_cu < 1 || cus < 1) return HSVD_E_DEVICE;
     int wgs = std::min(K, per_cu * cus);
@@ -2309,23 +2285,15 @@ try {
     // 2b, one sequence of launches per group
     std::vector<int> pers;
     std::vector<std::vector<int>> groups(1024 / (2 * b) + 1);
-    // batch_mode 2: the schedule the autotuner chose for this precision, else
-    // the persistent launch, but for few FP64 problems (bit-identical in both)
-    // the grouped ones, whose launches spread a problem's block pairs over the
-    // chip.  ms, persistent / grouped: 16 problems of n ~ U{8..256} 13.5 / 5.5,
-    // 300 15.6 / 11.6, 500 18.1 / 17.7; U{250..256} 16 14.0 / 5.0, 300 33.0 /
-    // 22.9, 500 37.6 / 35.1; U{100..220} 300 16.7 / 12.4, 500 20.0 / 21.8;
-    // U{65..128} 100 4.0 / 3.0, 200 4.2 / 4.3, 300 5.3 / 5.4; U{8..64} 100 1.7
-    // / 1.6, 300 1.9 / 2.2.
+    // batch_mode 2: the schedule the autotuner chose for batches like this one,
+    // else by the number of problems and the largest order
     int few = 0, few_max = 0;
     for (int k = 0; k < batch; ++k)
         if (n[k] <= kPersistMaxOrder) {
             ++few;
             few_max = std::max(few_max, n[k]);
         }
-    const int untuned = !mixed && few <= (few_max > 128 ? 5 * cus / 4 : cus / 2) ? 1 : 0;
-    const int tuned = ctx->batch_sched[mixed ? 1 : 0];
-    const int sched = prm.batch_mode == 2 ? (tuned >= 0 ? tuned : untuned) : prm.batch_mode;
+    const int sched = prm.batch_mode == 2 ? ctx->batch_tune.schedule_for(few, few_max, cus, mixed) : prm.batch_mode;
     const bool persist_ok = prm.inner_sweeps == 0 && sched == 0;
     for (int k = 0; k < batch; ++k) {
         if (persist_ok && n[k] <= kPersistMaxOrder)

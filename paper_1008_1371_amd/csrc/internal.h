@@ -556,20 +556,6 @@ hipError_t launch_batch_copy_if(hipStream_t st, const BatchGroup &g, const doubl
 // skip / act, indexed by problem.  slots: one slot of persist_slot_bytes()
 // per workgroup.
 constexpr int kPersistMaxOrder = 256;
-// Threads per workgroup before the autotuner has chosen, for `problems` of at
-// most nmax columns on `cus` compute units.  Threads beyond 256 work on further
-// block pairs of the same problem, so a workgroup is no wider than the largest
-// problem's pairs; few problems want the shortest solve, many the smallest
-// workgroups (a compute unit then holds four problems in different phases).
-// FP64, n ~ U{8..256}, 256 compute units, ms at 256 / 512 / 1024 threads:
-// 300 problems 23.6 / 17.9 / 15.7, 600 29.1 / 23.8 / 19.6, 1000 39.1 / 28.7 /
-// 29.8, 1500 46.8 / 42.0 / 44.1, 2200 58.9 / 61.3 / 65.4; U{8..128}, 400
-// problems 6.0 / 4.4 / 4.4; mixed precision in the same proportions.
-inline int persist_default_threads(int problems, int nmax, int cus)
-{
-    const int widest = nmax <= 64 ? 256 : (nmax <= 128 ? 512 : 1024);
-    return std::min(widest, problems <= 3 * cus ? 1024 : (problems <= 7 * cus ? 512 : 256));
-}
 struct PersistArgs {
     int batch = 0;
     const int *order = nullptr;  // problem indices, largest n first

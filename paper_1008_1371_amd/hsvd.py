@@ -291,8 +291,8 @@ def hsvd_autotune(ctx: Context, n: int):
 
 
 def hsvd_batched_schedule(ctx: Context, precision: int) -> int:
-    """The sweep schedule batch_mode 2 takes for `precision`: 0 persistent,
-    1 grouped, -1 not tuned."""
+    """The sweep schedule tuned last for `precision`, which batch_mode 2 takes
+    for batches of that size class: 0 persistent, 1 grouped, -1 not tuned."""
     m = ctypes.c_int()
     _check(lib().hsvd_batched_schedule(ctx.handle, int(precision), ctypes.byref(m)), "hsvd_batched_schedule")
     return m.value
@@ -301,7 +301,8 @@ def hsvd_batched_schedule(ctx: Context, precision: int) -> int:
 def hsvd_autotune_batched(ctx: Context, ns, ps):
     """Times the persistent batched kernel's widths (256 / 512 / 1024 threads
     per problem) on a sample of the given orders and keeps the fastest for
-    their size bucket, then the two sweep schedules per precision; returns
+    their size bucket and number, then the two sweep schedules per precision;
+    returns
     (threads, {threads: ms})."""
     import numpy as np
     n_a = np.ascontiguousarray(ns, dtype=np.int32)
