@@ -266,7 +266,8 @@ hsvd_status hsvd_solve_noalloc(hsvd_ctx *ctx, const double *G, int lda, int n, i
  * HSVD_E_NOMEM.  In FP64 both forms
  * give bit-identical results (in mixed precision see batch_mode).  Returns
  * HSVD_OK when every problem converged, else the status of the first problem
- * that did not.  Synchronises. */
+ * that did not.  Synchronises; while groups run, the calling thread looks after
+ * them and keeps its processor busy. */
 hsvd_status hsvd_solve_batched(hsvd_ctx *ctx, int batch, const int *n, const int *p, const long long *off,
                                const long long *voff, const double *G, const hsvd_params *prm, double *sigma,
                                double *U, double *V, double *lambda, hsvd_info *info);

@@ -1667,7 +1667,7 @@ struct GroupJob {
     hipGraphExec_t exec = nullptr;
 
     // A sweep's time, in steps that leave the chip partly idle.
-    double load() const { return steps * (1.0 + (double)pairs * K / 256.0); }
+    double load(int cus) const { return steps * (1.0 + (double)pairs * K / cus); }
 
     // Device space of the group: its size, and with a base its pointers.
     size_t bind(char *base)
@@ -1958,7 +1958,7 @@ struct GroupSet {
     GroupSet &operator=(const GroupSet &) = delete;
     // A stream per group, the longest first (HIP deals a few hardware queues to
     // the streams, and groups on one queue take turns).
-    hipError_t open()
+    hipError_t open(int cus)
     {
         hipError_t e;
         while (ctx->group_streams.size() < jobs.size()) {
@@ -1968,7 +1968,8 @@ struct GroupSet {
         }
         if (!ctx->join && (e = hipEventCreateWithFlags(&ctx->join, hipEventDisableTiming)) != hipSuccess) return e;
         if ((e = hipEventRecord(ctx->join, st)) != hipSuccess) return e;
-        std::stable_sort(jobs.begin(), jobs.end(), [](const GroupJob &x, const GroupJob &y) { return x.load() > y.load(); });
+        std::stable_sort(jobs.begin(), jobs.end(),
+                         [cus](const GroupJob &x, const GroupJob &y) { return x.load(cus) > y.load(cus); });
         for (size_t i = 0; i < jobs.size(); ++i) {
             if ((e = hipStreamWaitEvent(ctx->group_streams[i], ctx->join, 0)) != hipSuccess) return e;
             jobs[i].q = ctx->group_streams[i];
@@ -1986,7 +1987,10 @@ struct GroupSet {
         }
     }
     // Rounds of `work` (enqueues one round of a job), each job at its own pace,
-    // until it has no problem running, or `limit` rounds.
+    // until it has no problem running, or `limit` rounds.  The host asks the
+    // streams in turn; a stream synchronisation, as the last job gets, keeps its
+    // thread as busy (one group of n = 1000, or 24 problems of order 257 .. 640
+    // one group after the other: all of the call's time in both).
     template <typename Work, typename After>
     hipError_t rounds(int limit, Work work, After after)
     {
@@ -2083,7 +2087,7 @@ struct GroupSet {
     }
 };
 
-// The problems `ids` (FP64, block-oriented, n <= kPersistMaxOrder) in one
+// The problems `ids` (block-oriented, n <= kPersistMaxOrder) in one
 // persistent launch: a work queue of the problem indices, largest n first
 // (the longest solves start first; the short ones fill in at the end), one
 // workgroup slot of device memory per resident workgroup, per-problem results
@@ -2354,7 +2358,7 @@ try {
             set.jobs.pop_back();
         }
         if (s != HSVD_OK) return s;
-        HSVD_TRY(set.open());
+        HSVD_TRY(set.open(cus));
         bytes = 0;
         for (size_t i = 0; i < set.jobs.size(); ++i) {
             GroupJob &j = set.jobs[i];

@@ -732,7 +732,7 @@ __device__ __forceinline__ void cross_w_wave(CrossLds<T> &L, int nsteps, int wro
 template <typename T, int NT>
 __device__ __forceinline__ void inner_cross_pair(const BlockArgsT<T> &a, int k, CrossLds<T> &L, int &live, int tid)
 {
-    static_assert(NT == 256 || NT == 512 || NT == 1024, "thread count");
+    static_assert(NT == 256 || NT == 512, "thread count");
     double *const buf = L.buf;
     const int lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -832,12 +832,12 @@ __device__ __forceinline__ void inner_cross_idle(const int &live)
 // cycles of 1500) and then the block waves' one (parameters, rotation, writes),
 // a barrier between them; with four pairs per compute unit the vector
 // instructions.  Launches over 64 pairs (FP64, one sweep): 45 us at 1024
-// threads, 50 at 512, 70 at 256; 1024 pairs at 256 threads: 120 us.  With A_P
-// by indices (addresses computed anew in every step) 72, 83, 113 and 241 us;
-// with every block held twice, W in LDS and 32-byte parameters 107 us at 1024.
+// threads, 70 at 256; 1024 pairs at 256 threads: 120 us.  With A_P by indices
+// (addresses computed anew in every step) 72, 113 and 241 us; with every block
+// held twice, W in LDS and 32-byte parameters 107 us at 1024.
 // In a step without a rotation the 256-thread form turns nothing: 500 batched
-// problems of order 1 to 8, where three steps in four are such ones, take 1.36
-// ms instead of 1.46 (1.36 with A_P by indices, which had nothing to move then;
+// problems of order 1 to 8, where most steps are such ones, take 1.36 ms
+// instead of 1.46 (1.36 with A_P by indices, which had nothing to move then;
 // round-robin, one circle solve a sweep, 300 problems 1.20, 1.29 and 1.11).
 // ---------------------------------------------------------------------------
 constexpr int kCircleBlocks = kB * (kB + 1) / 2;
@@ -1064,7 +1064,7 @@ __device__ __forceinline__ void circle_block_wave(CircleLds &L, int nsweeps, int
 template <typename T, int NT>
 __device__ __forceinline__ void inner_circle_pair(const BlockArgsT<T> &a, int k, CircleLds &L, int tid)
 {
-    static_assert(NT == 256 || NT == 512 || NT == 1024, "thread count");
+    static_assert(NT == 256 || NT == 1024, "thread count");
     const int lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int2 IJ = outer_pair(a, k);

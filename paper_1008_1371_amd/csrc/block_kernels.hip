@@ -12,10 +12,11 @@
 //                        method (eqs. 2.2-2.5, in the short-chain form of
 //                        rotation_params_fast) applied two-sided to A_P and to
 //                        the columns of the accumulated W, in a parallel inner
-//                        ordering (circle kernel: A_P and W in LDS; cross
-//                        kernel: both in registers).  With V carried, extra
-//                        workgroups of the cross kernel apply the previous
-//                        step's W to V.
+//                        ordering.  W sits in registers; A_P in LDS in the
+//                        circle kernel, in registers in the cross kernel,
+//                        whose tiles hand their borders on through LDS.  With
+//                        V carried, extra workgroups of the cross kernel apply
+//                        the previous step's W to V.
 //   block_update_kernel  [G_P | V_P] <- [G_P | V_P] W on MFMA, row tiles
 //                        (G alone when V's half runs in the inner launch).
 //
@@ -81,7 +82,6 @@ __global__ __launch_bounds__(NT, 4) void block_inner_cross_kernel(BlockArgsT<T> 
     inner_cross_pair<T, NT>(a, blockIdx.x, L, live, threadIdx.x);
 }
 
-// launches).
 // Tiles of the update kernel: rows [t * rows, (t + 1) * rows) of G for
 // t < tiles_g, of V after that; a.tile0 shifts the tile index (G-only and
 // V-only launches).  The tile runs along blockIdx.x and the block pair along

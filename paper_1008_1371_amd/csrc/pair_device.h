@@ -7,8 +7,11 @@
 namespace hsvd {
 
 // Correctly rounded quotient and square root for operands whose exponents are
-// moderate (|exponent| below 500, x > 2^-767): the refinement of the general
-// sequences without their scaling steps, which do nothing there.
+// moderate (|exponent| below 500, x > 2^-767): the quotient from the hardware's
+// reciprocal estimate by two Newton-Raphson steps and a corrected product, the
+// root from its reciprocal square root estimate by Goldschmidt's iteration and
+// two corrections.  They give the bits of the operators / and sqrt, less the
+// scaling steps, which do nothing in that range.
 __device__ __forceinline__ double div_lean(double n, double d)
 {
     double r = __builtin_amdgcn_rcp(d);

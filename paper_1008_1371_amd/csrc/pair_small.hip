@@ -19,7 +19,7 @@
 //
 // The sums run in the order of the per-step kernel (fma chain over e, then
 // the butterfly over 64 rows: l ^ 32, l ^ 16, l ^ 8 inside a wave, l ^ 4, l ^ 2,
-// l ^ 1 over the waves), and rotation_params_lean rounds the operations of
+// l ^ 1 over the waves), and slot_rotation rounds the operations of
 // rotation_params, so the results are bit-identical to the per-step launches.
 //
 // What bounds it: the dependent chain of a step -- partial sums, eight-way
