@@ -2383,7 +2383,10 @@ try {
     }
     return result;
 } catch (const std::bad_alloc &) {
-    return HSVD_E_NOMEM;  // host memory; streams of a group have been waited for
+    // host memory; a group's streams have been waited for, a persistent launch
+    // outside a graph has not
+    (void)hipStreamSynchronize(ctx->stream);
+    return HSVD_E_NOMEM;
 }
 
 extern "C" {
