@@ -157,7 +157,7 @@ __device__ __noinline__ void phase_circle(int q0, int pairs)
 {
     const int g = group_index(), q = __builtin_amdgcn_readfirstlane(q0) + g;
     if (q < __builtin_amdgcn_readfirstlane(pairs))
-        inner_circle_pair<T, 256>(args_of<T>(), q, lds<GR>().group[g].circle, group_tid());
+        inner_circle_pair<T, 256, true>(args_of<T>(), q, lds<GR>().group[g].circle, group_tid());
     else
         inner_circle_idle();
 }
@@ -398,6 +398,7 @@ __device__ void persist_solve(const PersistArgs &pa, int z, char *slot, PersistL
         a.nact[tid] = 0;
         a.ntc[tid] = 0;
         a.maxt[tid] = 0.0;
+        a.active[tid] = ~0ull;  // no pair before the first
         if (pa.ordering == HSVD_ORD_MODMOD) S[tid] = modmod_start(tid, nb);
     }
     if (tid == 0) {

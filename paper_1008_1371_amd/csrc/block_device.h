@@ -835,10 +835,12 @@ __device__ __forceinline__ void inner_cross_idle(const int &live)
 // threads, 70 at 256; 1024 pairs at 256 threads: 120 us.  With A_P by indices
 // (addresses computed anew in every step) 72, 113 and 241 us; with every block
 // held twice, W in LDS and 32-byte parameters 107 us at 1024.
-// In a step without a rotation the 256-thread form turns nothing: 500 batched
-// problems of order 1 to 8, where most steps are such ones, take 1.36 ms
-// instead of 1.46 (1.36 with A_P by indices, which had nothing to move then;
-// round-robin, one circle solve a sweep, 300 problems 1.20, 1.29 and 1.11).
+// Where the persistent batched kernel's last pair of a slot had few touched
+// columns, steps without a rotation turn nothing (circle_block_wave): batches
+// of 200 / 300 / 500 problems of order 1 to 8, where most steps are such ones,
+// take 1.21 / 1.27 / 1.38 ms instead of 1.30 / 1.32 / 1.42 (1.21 / 1.25 / 1.36
+// with A_P by indices, which had nothing to move then; round-robin, one circle
+// solve a sweep, 300 problems 1.20, 1.28 and 1.10).
 // ---------------------------------------------------------------------------
 constexpr int kCircleBlocks = kB * (kB + 1) / 2;
 struct CircleLds {
@@ -1000,7 +1002,12 @@ __device__ __forceinline__ CircleCount circle_rotation_wave(const SlotRotator &r
 }
 
 // NB blocks of A_P per thread (items tid0 + nthreads q), and W when kWTurn.
-template <int NB, bool kWTurn>
+// kSparse: a step without a rotation turns nothing and only moves the entries.
+// The others then wait for the step's mask before they turn: with few problems
+// per compute unit, where the chain counts, up to 2% of a solve (300 problems of
+// order 100 to 128: 5.52 -> 5.60 ms), and in the 1024-thread form more than it
+// saves (three full-block sweeps of n = 1024: 28.3 -> 32.3 ms).
+template <int NB, bool kWTurn, bool kSparse>
 __device__ __forceinline__ void circle_block_wave(CircleLds &L, int nsweeps, int tid0, int nthreads, CircleW<4> &w)
 {
     const int j = threadIdx.x & 15;
@@ -1029,27 +1036,30 @@ __device__ __forceinline__ void circle_block_wave(CircleLds &L, int nsweeps, int
 #pragma unroll
                 for (int v = 0; v < 4; ++v) e[q][v] = L.X[v][item[q]];
             role_barrier();
-            // In a step without a rotation the entries only move.  With several
-            // blocks a thread waits for the mask, the first block's parameters on
-            // their way beside it; with one the wait costs more than it saves
-            // (1024 threads, three full-block sweeps of n = 1024: 28.3 -> 32.3 ms).
-            const double2 ra = *pa[0], rq = *pq[0];
+            double2 ra, rq;  // kSparse: on their way beside the mask
+            if (kSparse) {
+                ra = *pa[0];
+                rq = *pq[0];
+            }
             const unsigned mask = L.rotated;
             any |= mask;
             e[0][2] = diag ? e[0][1] : e[0][2];
-            const bool turn = NB == 1 || __builtin_amdgcn_readfirstlane(mask) != 0;
-            if (turn) {
+            auto rotate = [&](int q) {
+                rotate_block(e[q][0], e[q][1], e[q][2], e[q][3], unpack_rot<double>(kSparse && q == 0 ? ra : *pa[q]),
+                             unpack_rot<double>(kSparse && q == 0 ? rq : *pq[q]));
+                if (q == 0 && diag) e[0][1] = e[0][2] = (mask >> item[0]) & 1u ? 0.0 : e[0][1];
+            };
+            const bool turn = !kSparse || __builtin_amdgcn_readfirstlane(mask) != 0;
+            if (kSparse && turn)
 #pragma unroll
-                for (int q = 0; q < NB; ++q)
-                    rotate_block(e[q][0], e[q][1], e[q][2], e[q][3], unpack_rot<double>(q == 0 ? ra : *pa[q]),
-                                 unpack_rot<double>(q == 0 ? rq : *pq[q]));
-                if (diag) e[0][1] = e[0][2] = (mask >> item[0]) & 1u ? 0.0 : e[0][1];
-            }
+                for (int q = 0; q < NB; ++q) rotate(q);
 #pragma unroll
-            for (int q = 0; q < NB; ++q)
+            for (int q = 0; q < NB; ++q) {
+                if (!kSparse) rotate(q);
                 if (have[q])
 #pragma unroll
                     for (int v = 0; v < 4; ++v) X[to[q][v]] = e[q][v];
+            }
             if (kWTurn) {
                 if (turn) w.rotate(L.prm[2 * j], L.prm[2 * j + 1]);
                 w.move(j);
@@ -1060,11 +1070,18 @@ __device__ __forceinline__ void circle_block_wave(CircleLds &L, int nsweeps, int
     }
 }
 
-// NT threads.  Every thread must call it (barriers).
-template <typename T, int NT>
+// Touched columns of the pair that the slot worked on before, up to which most
+// steps are taken to rotate nothing: m columns have at most m (m - 1) / 2 pairs
+// for 63 steps, and few of them rotate in the last sweeps.
+constexpr int kFewTouched = 16;
+
+// NT threads.  kSparse: a.active[k] holds the last pair's touched columns, and
+// with few of them steps without a rotation turn nothing.  Every thread must
+// call it (barriers).
+template <typename T, int NT, bool kSparse = false>
 __device__ __forceinline__ void inner_circle_pair(const BlockArgsT<T> &a, int k, CircleLds &L, int tid)
 {
-    static_assert(NT == 256 || NT == 1024, "thread count");
+    static_assert(NT == 256 || (NT == 1024 && !kSparse), "thread count");
     const int lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int2 IJ = outer_pair(a, k);
@@ -1076,6 +1093,7 @@ __device__ __forceinline__ void inner_circle_pair(const BlockArgsT<T> &a, int k,
     });
     __syncthreads();
     const int nsweeps = a.inner_sweeps > 0 ? a.inner_sweeps : 1;
+    const bool few = kSparse && __builtin_amdgcn_readfirstlane(__popcll(a.active[k])) <= kFewTouched;
     // W, four rows a lane: every wave of 256 threads, else the last four
     constexpr int kWWave = NT / 64 - 4;
     const bool wturn = wave >= kWWave;
@@ -1104,10 +1122,12 @@ __device__ __forceinline__ void inner_circle_pair(const BlockArgsT<T> &a, int k,
         if (tid == 0)
             so_far.write(a, k, o.nrot > 0 ? (o.maxt > tthresh ? 3 : 1) : 0, (int)o.rank, o.maxt, o.nrot, o.nskip,
                          ((unsigned long long)mhi << 32) | mlo);
+    } else if (few) {
+        if constexpr (kSparse) circle_block_wave<kNB, kWWave == 0, true>(L, nsweeps, tid - 64, kA, w);
     } else if (wturn) {
-        circle_block_wave<kNB, true>(L, nsweeps, tid - 64, kA, w);
+        circle_block_wave<kNB, true, false>(L, nsweeps, tid - 64, kA, w);
     } else {
-        circle_block_wave<kNB, false>(L, nsweeps, tid - 64, kA, w);
+        circle_block_wave<kNB, false, false>(L, nsweeps, tid - 64, kA, w);
     }
     if (wturn) w.store(a.W + (size_t)k * (kB2 * kB2), wrow, j);
 }
