@@ -24,10 +24,10 @@
 //
 // What bounds it: the dependent chain of a step -- partial sums, eight-way
 // sum, rotation (about 95 instructions of one wave), barriers -- up to n = 64
-// (3100 cycles a step there, 2250 at n = 16), and the FP64 issue rate of the
-// one compute unit at n = 128 (4200 cycles: G's 16 rows per wave and V's 19).
-// Whole calls: n = 16 883 us in per-step launches, 161 us here; n = 128 5.35
-// ms and 2.21 ms.
+// (2900 cycles a step there, 2230 at n = 16), and the FP64 issue rate of the
+// one compute unit at n = 128 (4160 cycles: G's 16 rows per wave and V's 19).
+// Whole calls: n = 16 883 us in per-step launches, 167 us here; n = 128 5.35
+// ms and 2.08 ms.
 #include "pair_device.h"
 
 namespace hsvd {
