@@ -12,20 +12,24 @@ GIB = 1 << 30
 
 
 class Held:
-    """All device memory but `keep` bytes, taken in blocks of at most 32 GiB."""
+    """All device memory but `keep` bytes.  Taken until no 64 MiB are left, as
+    the runtime gives up memory of its own (the kernels' private memory) when
+    an allocation would fail, and does not report it as free before."""
 
     def __init__(self, keep):
         import torch
+        torch.cuda.synchronize()
         torch.cuda.empty_cache()
+        kept = torch.empty(keep, dtype=torch.uint8, device="cuda:0")
         self.blocks = []
-        while True:
-            free = torch.cuda.mem_get_info()[0]
-            if free <= keep + (64 << 20):
-                break
+        size = 32 * GIB
+        while size >= 64 << 20:
             try:
-                self.blocks.append(torch.empty(min(free - keep, 32 * GIB), dtype=torch.uint8, device="cuda:0"))
+                self.blocks.append(torch.empty(size, dtype=torch.uint8, device="cuda:0"))
             except torch.cuda.OutOfMemoryError:
-                break
+                size //= 2
+        del kept
+        torch.cuda.empty_cache()
 
     def __enter__(self):
         return self
