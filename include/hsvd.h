@@ -261,9 +261,9 @@ hsvd_status hsvd_solve_noalloc(hsvd_ctx *ctx, const double *G, int lda, int n, i
  * group runs as one sequence of launches that covers all of its problems,
  * with the stop rule decided per problem on the device, groups of few problems
  * side by side on streams of the context (forked from its stream and joined to
- * it).  Where device memory is short, fewer workgroups are resident and fewer
- * groups run side by side, down to one, before the call gives up with
- * HSVD_E_NOMEM.  In FP64 both forms
+ * it).  Where less than 1 GiB of device memory would be left, fewer workgroups
+ * are resident and groups run one after the other; the call gives up with
+ * HSVD_E_NOMEM only where that does not fit either.  In FP64 both forms
  * give bit-identical results (in mixed precision see batch_mode).  Returns
  * HSVD_OK when every problem converged, else the status of the first problem
  * that did not.  Synchronises; while groups run, the calling thread looks after

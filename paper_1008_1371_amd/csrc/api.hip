@@ -277,6 +277,16 @@ static hsvd_status ensure_ws(hsvd_ctx *ctx, size_t bytes)
     return s;
 }
 
+// Whether a workspace of this size, wanted for speed alone, would leave the
+// device less than 1 GiB: streams, graphs and the kernels' private memory take
+// some (a stream's queue and its save area alone a few hundred MB).
+static bool memory_short(const hsvd_ctx *ctx, size_t bytes)
+{
+    size_t free_bytes = 0, total = 0;
+    if (bytes <= ctx->ws_bytes || hipMemGetInfo(&free_bytes, &total) != hipSuccess) return false;
+    return bytes + ((size_t)1 << 30) > free_bytes + ctx->ws_bytes;
+}
+
 static hsvd_status ensure_events(hsvd_ctx *ctx, size_t count)
 {
     while (ctx->events.size() < count) {
@@ -1956,16 +1966,24 @@ struct GroupSet {
     GroupSet(hsvd_ctx *c, hipStream_t s) : ctx(c), st(s) {}
     GroupSet(const GroupSet &) = delete;
     GroupSet &operator=(const GroupSet &) = delete;
+    // The streams there are for the jobs, created as far as memory for them goes.
+    size_t make_streams()
+    {
+        while (ctx->group_streams.size() < jobs.size()) {
+            hipStream_t q = nullptr;
+            if (hipStreamCreateWithFlags(&q, hipStreamNonBlocking) != hipSuccess) {
+                (void)hipGetLastError();  // not an error of a later launch
+                break;
+            }
+            ctx->group_streams.push_back(q);
+        }
+        return ctx->group_streams.size();
+    }
     // A stream per group, the longest first (HIP deals a few hardware queues to
     // the streams, and groups on one queue take turns).
     hipError_t open(int cus)
     {
         hipError_t e;
-        while (ctx->group_streams.size() < jobs.size()) {
-            hipStream_t q = nullptr;
-            if ((e = hipStreamCreateWithFlags(&q, hipStreamNonBlocking)) != hipSuccess) return e;
-            ctx->group_streams.push_back(q);
-        }
         if (!ctx->join && (e = hipEventCreateWithFlags(&ctx->join, hipEventDisableTiming)) != hipSuccess) return e;
         if ((e = hipEventRecord(ctx->join, st)) != hipSuccess) return e;
         std::stable_sort(jobs.begin(), jobs.end(),
@@ -2125,10 +2143,10 @@ static hsvd_status batch_persistent(hsvd_ctx *ctx, hipStream_t st, const std::ve
     const size_t o_rs = take_bytes(o, sizeof(int) * batch), o_nr = take_bytes(o, sizeof(double) * batch);
     const size_t o_slots = o;
     // fewer workgroups where memory is short: the results do not depend on them
+    const size_t slot = persist_slot_bytes(prm.precision == HSVD_MIXED);
+    while (wgs > 2 * cus && memory_short(ctx, o_slots + slot * (size_t)wgs)) wgs = (wgs + 1) / 2;
     hsvd_status s;
-    while ((s = ensure_ws(ctx, o_slots + persist_slot_bytes(prm.precision == HSVD_MIXED) * (size_t)wgs)) == HSVD_E_NOMEM &&
-           wgs > 1)
-        wgs = (wgs + 1) / 2;
+    while ((s = ensure_ws(ctx, o_slots + slot * (size_t)wgs)) == HSVD_E_NOMEM && wgs > 1) wgs = (wgs + 1) / 2;
     if (s != HSVD_OK) return s;
     char *base = static_cast<char *>(ctx->ws);
     HSVD_TRY(hipMemcpyAsync(base + o_order, order.data(), sizeof(int) * K, hipMemcpyHostToDevice, st));
@@ -2347,19 +2365,29 @@ try {
             set.jobs.push_back(std::move(j));
         }
         if (set.jobs.empty()) break;
-        size_t bytes = 0;
-        for (;;) {
-            bytes = 0;
-            for (GroupJob &j : set.jobs) take_bytes(bytes, j.bind(nullptr));
-            s = ensure_ws(ctx, bytes);
-            if (s != HSVD_E_NOMEM || set.jobs.size() == 1) break;
-            // too little memory for all of them at once: the last one in the next set
-            gi = (size_t)set.jobs.back().pairs;
-            set.jobs.pop_back();
+        // where memory is short, the first group alone, the others in the next sets
+        auto keep = [&](size_t count) {
+            if (count >= set.jobs.size()) return;
+            gi = (size_t)set.jobs[count].pairs;
+            set.jobs.erase(set.jobs.begin() + count, set.jobs.end());
+        };
+        auto total_bytes = [&] {
+            size_t o = 0;
+            for (GroupJob &j : set.jobs) take_bytes(o, j.bind(nullptr));
+            return o;
+        };
+        if (memory_short(ctx, total_bytes())) keep(1);
+        const size_t streams = set.make_streams();
+        if (streams == 0) return HSVD_E_NOMEM;
+        keep(streams);
+        s = ensure_ws(ctx, total_bytes());
+        if (s == HSVD_E_NOMEM && set.jobs.size() > 1) {
+            keep(1);
+            s = ensure_ws(ctx, total_bytes());
         }
         if (s != HSVD_OK) return s;
         HSVD_TRY(set.open(cus));
-        bytes = 0;
+        size_t bytes = 0;
         for (size_t i = 0; i < set.jobs.size(); ++i) {
             GroupJob &j = set.jobs[i];
             j.bind(static_cast<char *>(ctx->ws) + take_bytes(bytes, j.bind(nullptr)));
