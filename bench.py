@@ -38,7 +38,7 @@ MEASURED_TRAFFIC = {
     "mode": "mixed",
     "sources": ["paper_1008_1371_amd/csrc/block_kernels.hip", "paper_1008_1371_amd/csrc/block_device.h",
                 "paper_1008_1371_amd/csrc/api.hip", "paper_1008_1371_amd/csrc/internal.h"],
-    "sha256": "3d32cc56b6174e07925f57ce10766a9ce7e131ac8761c7d8377daed7c6d3a9c2",
+    "sha256": "7d3955adb70b740ee4554b2980594de26bcfac6cda00de1029c288d74248746c",
     "bytes_per_launch": {
         "block_gram_kernel<float>": (32853.6 * 2.0 + 5120.0 * 1.0) * 1024,
         "block_inner_kernel<float>": (23232.9 * 2.0 + 36427.1 * 1.0) * 1024,

@@ -279,7 +279,7 @@ static hsvd_status ensure_ws(hsvd_ctx *ctx, size_t bytes)
 
 // Whether a workspace of this size, wanted for speed alone, would leave the
 // device less than 1 GiB: streams, graphs and the kernels' private memory take
-// some (a stream's queue and its save area alone a few hundred MB).
+// some (a set of groups that just fitted could not create its streams).
 static bool memory_short(const hsvd_ctx *ctx, size_t bytes)
 {
     size_t free_bytes = 0, total = 0;
