@@ -38,7 +38,7 @@ MEASURED_TRAFFIC = {
     "mode": "mixed",
     "sources": ["paper_1008_1371_amd/csrc/block_kernels.hip", "paper_1008_1371_amd/csrc/block_device.h",
                 "paper_1008_1371_amd/csrc/api.hip", "paper_1008_1371_amd/csrc/internal.h"],
-    "sha256": "7d3955adb70b740ee4554b2980594de26bcfac6cda00de1029c288d74248746c",
+    "sha256": "5d6029824645ca368bad50362aad6ab119941ad2013cf4f12aa843f2f68afa44",
     "bytes_per_launch": {
         "block_gram_kernel<float>": (32853.6 * 2.0 + 5120.0 * 1.0) * 1024,
         "block_inner_kernel<float>": (23232.9 * 2.0 + 36427.1 * 1.0) * 1024,

@@ -1085,6 +1085,7 @@ __device__ __forceinline__ void inner_circle_pair(const BlockArgsT<T> &a, int k,
     const int lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int2 IJ = outer_pair(a, k);
+    const unsigned long long last = kSparse ? a.active[k] : 0ull;  // read ahead of its use
     // the sweep's counters so far, read ahead of their update at the end
     SweepSoFar so_far;
     if (tid == 0) so_far.read(a, k);
@@ -1093,7 +1094,7 @@ __device__ __forceinline__ void inner_circle_pair(const BlockArgsT<T> &a, int k,
     });
     __syncthreads();
     const int nsweeps = a.inner_sweeps > 0 ? a.inner_sweeps : 1;
-    const bool few = kSparse && __builtin_amdgcn_readfirstlane(__popcll(a.active[k])) <= kFewTouched;
+    const bool few = kSparse && __builtin_amdgcn_readfirstlane(__popcll(last)) <= kFewTouched;
     // W, four rows a lane: every wave of 256 threads, else the last four
     constexpr int kWWave = NT / 64 - 4;
     const bool wturn = wave >= kWWave;
